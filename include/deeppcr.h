@@ -44,8 +44,9 @@
  *     DEEPPCR_EINVAL (or DEEPPCR_EWORKSPACE for a short workspace) and
  *     launches nothing.  A HIP runtime error returns DEEPPCR_EHIP; its text is
  *     available from deeppcr_last_error().
- *   - Arithmetic is float32 with float32 accumulation (no reduced-precision
- *     matrix instructions).  Results are deterministic run to run.
+ *   - Arithmetic is float32 with float32 accumulation.  Where products run
+ *     on the bf16 matrix cores, each float32 value is carried by three bf16
+ *     parts that add up to it exactly.  Results are deterministic run to run.
  */
 #ifndef DEEPPCR_H
 #define DEEPPCR_H

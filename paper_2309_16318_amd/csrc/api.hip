@@ -562,6 +562,90 @@ hipError_t fused_rest_levels(const NewtonArgs& na, int B, int L, int w, const Ws
     });
 }
 
+// ------------------------------------------------- chunked MLP solve
+// Chunks and workspace of the chunked solve (panels.hip): P, q and the
+// solution at the chunk ends, and the buffers of a PCR sweep over them, all
+// in the space of the operator buffers A, which this path does not store.
+struct PanelPlan {
+    int C = 0, Lc = 0;      // C = 0: not for this shape
+    bool sweep = false;     // chunk ends by PCR levels, else by substitution
+    size_t P, q, xe, A[2], r[2];
+};
+
+PanelPlan panel_plan(int B, int L, int w, bool bwd) {
+    PanelPlan pl;
+    if (!panel_width(w)) return pl;
+    const int WP = panel_pad(w);
+    // rows that are not whole 16-byte vectors are addressed by 32-bit bytes
+    if (w != WP && (double)B * L * w >= (double)(1 << 30)) return pl;
+    const int rows = L + (bwd ? 1 : 0);
+    const Layout lo = layout(bwd ? DEEPPCR_OP_BWD : DEEPPCR_OP_FWD, B, L, w);
+    for (int C = panel_chunks(B, rows, w); C > 0; C = C * 3 / 4) {
+        pl.Lc = (rows + C - 1) / C;
+        pl.C = (rows + pl.Lc - 1) / pl.Lc;
+        const size_t Ce = pl.C > 1 ? pl.C - 1 : 0;
+        pl.sweep = Ce > 64;
+        const size_t nP = align_up((size_t)B * Ce * WP * WP * 4),
+                     nq = align_up((size_t)B * Ce * WP * 4);
+        size_t off = 0;
+        pl.P = off; off += nP;
+        pl.q = off; off += nq;
+        pl.xe = off; off += nq;
+        for (int i = 0; i < 2; ++i) {
+            pl.A[i] = off; off += pl.sweep ? nP : 0;
+            pl.r[i] = off; off += pl.sweep ? nq : 0;
+        }
+        // (one chunk needs no space)
+        if (off <= lo.r[0]) return pl;
+    }
+    pl.C = 0;
+    return pl;
+}
+
+// The solve of Eq. 3 (Eq. 12) for the layers described by `a`, whose d and r
+// are set; ws_base: the workspace.
+hipError_t panel_solve(bool bwd, PanelArgs a, const PanelPlan& pl, void* ws_base, hipStream_t st) {
+    char* base = (char*)ws_base;
+    const int WP = panel_pad(a.w), Ce = pl.C - 1;
+    a.rows = a.L + (bwd ? 1 : 0);
+    a.Lc = pl.Lc;
+    a.C = pl.C;
+    a.P = (float*)(base + pl.P);
+    a.q = (float*)(base + pl.q);
+    float* xe = (float*)(base + pl.xe);
+    const double w2 = (double)a.w * a.w, n = (double)a.B * a.L * a.w;
+    if (pl.C > 1) {
+        const double prow = (double)a.B * (pl.C - 2) * a.Lc;  // rows with a block product
+        const double bytes = 4.0 * (a.L * w2 + 2.0 * n + (double)a.B * Ce * w2);
+        hipError_t e = timed(DEEPPCR_KCLASS_PCR_LEVEL, bytes,
+                             prow * 2.0 * w2 * a.w + (double)a.B * a.L * 2.0 * w2, st,
+                             [&] { return launch_chunk_pass(bwd, a, st); });
+        if (e != hipSuccess) return e;
+        if (Ce == 1) {
+            xe = a.q;
+        } else {
+            const long long nv = (long long)Ce * WP;
+            const BlockSrc P{a.P, nv * WP, (long long)WP * WP, 0};
+            const VecSrc q{a.q, nv, WP};
+            const VecDst x{xe, nv, WP};
+            if (pl.sweep) {
+                float* A[2] = {(float*)(base + pl.A[0]), (float*)(base + pl.A[1])};
+                float* r[2] = {(float*)(base + pl.r[0]), (float*)(base + pl.r[1])};
+                e = pcr_sweep(P, q, x, a.B, Ce, WP, A, r, 0, 0, st);
+            } else {
+                e = timed(DEEPPCR_KCLASS_PCR_TAIL, 4.0 * a.B * Ce * ((double)WP * WP + 2.0 * WP),
+                          2.0 * a.B * Ce * (double)WP * WP, st, [&] {
+                    return launch_pcr_chain_subst(P, q, x, a.B, Ce, WP, 1, st);
+                });
+            }
+            if (e != hipSuccess) return e;
+        }
+    }
+    a.xe = xe;
+    return timed(DEEPPCR_KCLASS_PCR_TAIL, 4.0 * (a.L * w2 + 4.0 * n), 2.0 * a.B * a.L * w2, st,
+                 [&] { return launch_apply_pass(bwd, a, st); });
+}
+
 // Argument checks shared by the two forward entry points.
 int check_forward_args(const float* W, const float* bias, const float* z0, float* Z,
                        const float* Z_init, void* workspace, size_t workspace_bytes, int B,
@@ -636,6 +720,7 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
     }
     const long long n = (long long)B * L * w;
     const VecDst xd{ws.r[(num_passes(B, L, w) + 1) & 1], (long long)L * w, (long long)w};
+    const PanelPlan pl = panel_plan(B, L, w, false);
     const bool fused = layer_first_level(w);
     const NewtonArgs na{W, bias, z0, Z, ws.red, layer, alpha};
     unsigned* fslots = ws.red + kRedF;
@@ -650,7 +735,12 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
         // Layers, Jacobian blocks (forward order) and residuals at the iterate:
         // fused into the first PCR level, or evaluated into ws A[1], r[1].
         hipError_t e;
-        if (fused) {
+        if (pl.C > 0) {
+            e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 4.0 * n), 2.0 * B * L * w2, st, [&] {
+                return launch_layer_vectors(false, W, bias, z0, Z, ws.r[1], ws.r[0], ws.red, B, L,
+                                            w, layer, alpha, st);
+            });
+        } else if (fused) {
             e = fused_first_level(na, B, L, w, ws, xd, st);
         } else {
             e = timed(DEEPPCR_KCLASS_LAYER, eval_bytes, eval_flops, st, [&] {
@@ -675,7 +765,20 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
             if (e != hipSuccess) return hip_fail(e, "zero_words");
         }
         // The rest of the solve of Eq. 3 and the update Z += dZ.
-        if (fused) {
+        if (pl.C > 0) {
+            PanelArgs pa{};
+            pa.W = W;
+            pa.d = ws.r[1];
+            pa.r = ws.r[0];
+            pa.Z = Z;
+            pa.red = ws.red;
+            pa.B = B;
+            pa.L = L;
+            pa.w = w;
+            pa.residual = layer_residual(layer);
+            e = panel_solve(false, pa, pl, workspace, st);
+            if (e != hipSuccess) return hip_fail(e, "chunked solve");
+        } else if (fused) {
             e = fused_rest_levels(na, B, L, w, ws, xd, st);
             if (e != hipSuccess) return hip_fail(e, "newton levels");
         } else {
@@ -1078,6 +1181,31 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
     // w = 32, 64, 128 with paired levels: the first PCR pass forms the blocks
     // from the weights and c d, so the assembly writes only c d and the
     // right-hand side
+    const PanelPlan pl = panel_plan(B, L, w, true);
+    if (pl.C > 0) {
+        hipError_t e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 2.0 * B * L * w),
+                             2.0 * B * L * w2, st, [&] {
+            return launch_layer_vectors(true, W, bias, z0, Z, ws.dscale, nullptr, nullptr, B, L, w,
+                                        layer, alpha, st);
+        });
+        if (e != hipSuccess) return hip_fail(e, "layer_vectors");
+        PanelArgs pa{};
+        pa.W = W;
+        pa.d = ws.dscale;
+        pa.r = G;
+        pa.Lambda = Lambda;
+        pa.dz0 = dz0;
+        pa.B = B;
+        pa.L = L;
+        pa.w = w;
+        pa.residual = layer_residual(layer);
+        e = panel_solve(true, pa, pl, workspace, st);
+        if (e != hipSuccess) return hip_fail(e, "chunked solve");
+        e = timed(DEEPPCR_KCLASS_WGRAD, 4.0 * (3.0 * B * L * w + L * (w2 + w)), 2.0 * B * L * w2,
+                  st, [&] { return launch_wgrad(z0, Z, ws.dscale, Lambda, dW, db, B, L, w, st); });
+        if (e != hipSuccess) return hip_fail(e, "wgrad");
+        return DEEPPCR_OK;
+    }
     const bool from_weights = first_level_count(B, L, w) == 2;
     const BwdArgs bw{W, ws.dscale, layer_residual(layer) ? 1 : 0};
     const double jbytes = from_weights ? 0.0 : 4.0 * B * L * w2;

@@ -261,6 +261,39 @@ hipError_t launch_eval_small(bool bwd, const float* W, const float* bias, const 
                              unsigned* red, int B, int L, int w, int layer, float alpha,
                              hipStream_t stream);
 
+// ------------------------------------------------------- chunked MLP solve
+// The Newton solve (rows l = 0 .. L-1, operator of row l from layer l) and
+// the transposed solve (rows m = 0 .. L, operator of row m from layer L - m,
+// the last row being dz0) of MLP layers by chunks of Lc rows, widths
+// panel_width accepts; WP = panel_pad(w) is the padded width of P, q, xe.
+struct PanelArgs {
+    const float* W;   // [L, w, w]
+    const float* d;   // [B, L, w] c sigma'
+    const float* r;   // [B, L, w] residuals; transposed: G [B, w]
+    const float* xe;  // [B, C-1, WP] solution at the chunk ends
+    float* P;         // [B, C-1, WP, WP] chunk products (chunk 0 not written)
+    float* q;         // [B, C-1, WP] chunk vectors
+    float* Z;         // [B, L, w] iterate, updated by the apply pass
+    float* Lambda;    // [B, L, w]
+    float* dz0;       // [B, w]
+    unsigned* red;    // maxima of the update (apply pass)
+    int B, L, w;
+    int rows;         // L, transposed: L + 1
+    int Lc, C;        // rows per chunk, ceil(rows / Lc)
+    int residual;
+};
+bool panel_width(int w);
+int panel_pad(int w);
+int panel_chunks(int B, int rows, int w);  // 0: leave the shape to the PCR levels
+// d (and, forward, r with its maximum; clears the max|dZ|, max|Z| slots).
+hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, const float* z0,
+                                const float* Z, float* d, float* r, unsigned* red, int B, int L,
+                                int w, int layer, float alpha, hipStream_t st);
+// P of chunks 1 .. C-2 and q of chunks 0 .. C-2 (C >= 2).
+hipError_t launch_chunk_pass(bool bwd, const PanelArgs& a, hipStream_t st);
+// Every row from its chunk's x_in (xe of the chunk before; 0 in the first).
+hipError_t launch_apply_pass(bool bwd, const PanelArgs& a, hipStream_t st);
+
 // ------------------------------------------------------- sequential passes
 // Layers l0 .. l1-1 of the sequential forward pass (one workgroup per system;
 // reads Z[:, l0-1], or z0 when l0 = 0), and the sequential adjoint pass over

@@ -1,0 +1,801 @@
+// The Newton solve and the backward solve of MLP layers by row chunks, for
+// widths 9 to 128: the operators J_l = diag(d_l) W_l (+ I) (App. A.1) are
+// never stored.
+//
+// The rows of every system are cut into C consecutive chunks.  Inside a chunk
+// x_l = P_l x_in + q_l with x_in the row before it, so that
+//   1. chunk_pass forms, for every chunk but the first and the last, the
+//      product P of its operators, one block product per row (Alg. 1 forms
+//      one per row and level), and, beside it, every chunk's q;
+//   2. the chunk ends are a block-bidiagonal system of C - 1 rows with the
+//      operators P, solved by the PCR sweep or by substitution;
+//   3. apply_pass substitutes inside every chunk from its x_in, which also
+//      applies the Newton update, or writes the adjoints.
+// In exact arithmetic this is the solution of Eq. 3 (Eq. 12 for the
+// transposed system).  Per row it reads one weight block, shared by all
+// systems through the caches, and writes vectors only.
+//
+// All products run on the bf16 matrix cores at float32 precision: a float32
+// value is split into three bf16 parts (round to nearest, exact: 8 + 8 + 8
+// significant bits), and of the nine products of two split values the six
+// above 2^-24 are accumulated in float32, the five small ones in an
+// accumulator of their own.  Measured on one MI355X, the six cost 32 cycles
+// each per 32 x 32 x 16 tile against 8 x 64 cycles of float32 instructions:
+// 2.7 times the rate, with fewer roundings (one per 16 terms and part).
+#include "internal.h"
+
+namespace deeppcr {
+namespace {
+
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+
+constexpr int kThr = 256;
+
+// The three bf16 parts of two values, packed.
+struct Parts2 {
+    unsigned h, m, l;
+};
+__device__ __forceinline__ unsigned pack2(float x, float y) {
+    const b2 p = __builtin_convertvector(f2{x, y}, b2);
+    return __builtin_bit_cast(unsigned, p);
+}
+__device__ __forceinline__ float lo_f(unsigned p) { return __uint_as_float(p << 16); }
+__device__ __forceinline__ float hi_f(unsigned p) { return __uint_as_float(p & 0xffff0000u); }
+__device__ __forceinline__ Parts2 split2(float x, float y) {
+    Parts2 p;
+    p.h = pack2(x, y);
+    const float x1 = x - lo_f(p.h), y1 = y - hi_f(p.h);
+    p.m = pack2(x1, y1);
+    p.l = pack2(x1 - lo_f(p.m), y1 - hi_f(p.m));
+    return p;
+}
+// Eight values as three operand registers.
+struct Parts8 {
+    b8 h, m, l;
+};
+__device__ __forceinline__ Parts8 split8(const float (&v)[8]) {
+    u4 h, m, l;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const Parts2 p = split2(v[2 * j], v[2 * j + 1]);
+        h[j] = p.h;
+        m[j] = p.m;
+        l[j] = p.l;
+    }
+    return {__builtin_bit_cast(b8, h), __builtin_bit_cast(b8, m), __builtin_bit_cast(b8, l)};
+}
+
+__device__ __forceinline__ f16v mfma32(b8 a, b8 b, f16v c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f4 mfma16(b8 a, b8 b, f4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// c += A B at float32 precision: the leading products into c.x, the others into c.s.
+template <class V>
+struct Acc {
+    V x, s;
+};
+__device__ __forceinline__ void mac(Acc<f16v>& c, const Parts8& a, const Parts8& b) {
+    c.s = mfma32(a.l, b.h, c.s);
+    c.x = mfma32(a.h, b.h, c.x);
+    c.s = mfma32(a.m, b.m, c.s);
+    c.s = mfma32(a.h, b.l, c.s);
+    c.s = mfma32(a.m, b.h, c.s);
+    c.s = mfma32(a.h, b.m, c.s);
+}
+__device__ __forceinline__ void mac(Acc<f4>& c, const Parts8& a, const Parts8& b) {
+    c.s = mfma16(a.l, b.h, c.s);
+    c.x = mfma16(a.h, b.h, c.x);
+    c.s = mfma16(a.m, b.m, c.s);
+    c.s = mfma16(a.h, b.l, c.s);
+    c.s = mfma16(a.m, b.h, c.s);
+    c.s = mfma16(a.h, b.m, c.s);
+}
+
+// Rows of w floats read four at a time.  EXACT (w = the padded width): plain
+// 16-byte loads.  Otherwise rows start on any 4-byte boundary: buffer loads,
+// which the hardware bounds-checks per element against the tensor's (for
+// weights the layer's) end and fills with zeros beyond it.
+template <bool EXACT>
+struct Src {
+    const float* p;
+    __device__ __forceinline__ Src(const float* q, unsigned) : p(q) {}
+    __device__ __forceinline__ f4 at(unsigned off) const {
+        return *reinterpret_cast<const f4*>(p + off);
+    }
+    __device__ __forceinline__ float one(unsigned off) const { return p[off]; }
+};
+template <>
+struct Src<false> {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Src(const float* q, unsigned floats)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(q), 0, floats * 4u, 0x00027000)) {}
+    __device__ __forceinline__ f4 at(unsigned off) const {
+        return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, off * 4u, 0, 0));
+    }
+    __device__ __forceinline__ float one(unsigned off) const {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off * 4u, 0, 0));
+    }
+};
+
+// Elements i .. i + N - 1 of the row of w starting at float `row` of src;
+// zeros beyond the row's end.
+template <int N, bool EXACT>
+__device__ __forceinline__ void load_row(const Src<EXACT>& src, unsigned row, int i, int w,
+                                         float (&v)[N]) {
+#pragma unroll
+    for (int q = 0; q < N; q += 4) {
+        const f4 x = src.at(row + i + q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[q + e] = EXACT || i + q + e < w ? x[e] : 0.f;
+    }
+}
+template <int N, bool EXACT>
+__device__ __forceinline__ void store_row(float* p, int i, int w, const float (&v)[N]) {
+    if constexpr (EXACT) {
+#pragma unroll
+        for (int q = 0; q < N; q += 4)
+            *reinterpret_cast<f4*>(p + i + q) = f4{v[q], v[q + 1], v[q + 2], v[q + 3]};
+    } else {
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+            if (i + q < w) p[i + q] = v[q];
+    }
+}
+
+// ------------------------------------------------------------ shapes
+// Vector panels: 16 systems per group, a 16 x 16 x 32 tile per 16 rows.
+// Wave v of a group owns rows 16 MTW v ..; tile t's row index i stands for
+// row MTW i + t of them, so that a lane's results are 4 MTW consecutive rows.
+template <int WP>
+struct VecShape {
+    static constexpr int MTW = WP == 128 ? 2 : 1;
+    static constexpr int NR = 4 * MTW;             // consecutive rows per lane
+    static constexpr int KT = WP / 32;             // k tiles
+    static constexpr int WPG = WP / (16 * MTW);    // waves per group
+    static constexpr int GPW = 4 / WPG;            // groups per workgroup
+    static constexpr int BUF = KT * 3 * 1024;      // one vector panel in LDS, bytes
+    static constexpr int LDS = GPW * 2 * BUF;
+};
+// Product panels: 32 columns of one system's P per wave, all rows.
+template <int WP>
+struct ProdShape {
+    static constexpr int MT = WP / 32, KT = WP / 16;
+    static constexpr int SYS = 4 / MT;             // systems per workgroup
+    static constexpr int LPS = WP == 32 ? 4 : 1;   // layers a stage starts
+    static constexpr int WB = 4096 * 6;            // 4096 split weights, bytes
+    static constexpr int STAGE = WB + LPS * 512;   // and the layers' d, 128 floats each
+    static constexpr int LDS = 2 * STAGE;
+};
+
+// The rows of W_l (TRANS: of W_l^T) a lane multiplies with, for the vector
+// panels.  Where w is not the padded width, elements beyond a row's end hold
+// the next row's weights: they meet zeros of the panel, or (TRANS) give rows
+// that the caller drops.
+template <int WP, bool TRANS, bool EXACT>
+__device__ __forceinline__ void load_strip(const Src<EXACT>& Wl, int w, int base, int idx, int g,
+                                           float (&raw)[VecShape<WP>::MTW][VecShape<WP>::KT][8]) {
+    using S = VecShape<WP>;
+    if constexpr (!TRANS) {
+#pragma unroll
+        for (int t = 0; t < S::MTW; ++t) {
+            const unsigned row = (base + S::MTW * idx + t) * w + 8 * g;
+#pragma unroll
+            for (int k = 0; k < S::KT; ++k)
+#pragma unroll
+                for (int q = 0; q < 8; q += 4) {
+                    const f4 x = Wl.at(row + 32 * k + q);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) raw[t][k][q + e] = x[e];
+                }
+        }
+    } else {
+        const unsigned col = base + S::MTW * idx + 8 * g * w;
+#pragma unroll
+        for (int k = 0; k < S::KT; ++k)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if constexpr (EXACT && S::MTW == 2) {
+                    const f2 x = *reinterpret_cast<const f2*>(Wl.p + col + (32 * k + j) * w);
+                    raw[0][k][j] = x[0];
+                    raw[1][k][j] = x[1];
+                } else {
+#pragma unroll
+                    for (int t = 0; t < S::MTW; ++t)
+                        raw[t][k][j] = Wl.one(col + (32 * k + j) * w + t);
+                }
+            }
+    }
+}
+
+// A lane's NR rows of a vector panel as operand parts in LDS.
+template <int WP>
+__device__ __forceinline__ void put_panel(char* buf, int r0, int n,
+                                          const float (&x)[VecShape<WP>::NR]) {
+    using S = VecShape<WP>;
+    const int kt = r0 / 32, lane = n + 16 * ((r0 % 32) / 8);
+    char* p = buf + kt * 1024 + lane * 16 + (r0 % 8) * 2;
+    if constexpr (S::NR == 8) {
+        const Parts8 q = split8(x);
+        *reinterpret_cast<b8*>(p) = q.h;
+        *reinterpret_cast<b8*>(p + S::KT * 1024) = q.m;
+        *reinterpret_cast<b8*>(p + 2 * S::KT * 1024) = q.l;
+    } else {
+        const Parts2 a = split2(x[0], x[1]), b = split2(x[2], x[3]);
+        *reinterpret_cast<u2*>(p) = u2{a.h, b.h};
+        *reinterpret_cast<u2*>(p + S::KT * 1024) = u2{a.m, b.m};
+        *reinterpret_cast<u2*>(p + 2 * S::KT * 1024) = u2{a.l, b.l};
+    }
+}
+
+// ------------------------------------------------------------ vector panels
+// One chunk of the recurrence for 16 systems per group.  APPLY: from x_in to
+// every row; otherwise from zero to the chunk's last row, q.
+template <int WP, bool BWD, bool EXACT, bool APPLY>
+__device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int c, int wg) {
+    using S = VecShape<WP>;
+    // rows requested ahead (beside the products, their registers allow fewer)
+    constexpr int D = WP == 128 ? (APPLY ? 2 : 1) : WP == 64 ? 3 : 5;
+    constexpr int NB = D + 1, NR = S::NR;
+    const int t = threadIdx.x, v = t >> 6, lane = t & 63;
+    const int sub = v / S::WPG, wv = v % S::WPG;
+    const int n = lane & 15, g = lane >> 4;
+    const int w = EXACT ? WP : a.w, L = a.L;
+    const int base = wv * 16 * S::MTW, r0 = base + NR * g;
+    const int bb = (wg * S::GPW + sub) * 16 + n;
+    const bool live = bb < a.B;
+    const int b = live ? bb : a.B - 1;
+    const int m0 = c * a.Lc, m1 = min(a.rows, m0 + a.Lc);
+    char* const panel = lds + sub * 2 * S::BUF;
+    const unsigned bL = (unsigned)b * L, nv = (unsigned)a.B * L * w;
+    const Src<EXACT> sd(a.d, nv), sr(a.r, BWD ? (unsigned)a.B * w : nv), sz(a.Z, nv);
+
+    if constexpr (BWD && !APPLY) {
+        // only row 0 has a right-hand side
+        if (c > 0) {
+            if (live) {
+                const float zero[NR] = {};
+                store_row<NR, true>(a.q + ((long long)b * (a.C - 1) + c) * WP, r0, WP, zero);
+            }
+            return;
+        }
+    }
+    unsigned mx = 0u, mz = 0u;
+    float raw[NB][S::MTW][S::KT][8];
+    float ad[NB][NR], ar[NB][NR], az[NB][NR];
+    // row m's weights, and the vectors its result meets: d and r (forward),
+    // d of the next row's layer (backward), the iterate
+    auto aux = [&](int m, float (&d)[NR], float (&r)[NR], float (&z)[NR]) {
+        if constexpr (!BWD) {
+            load_row<NR>(sd, (bL + m) * w, r0, w, d);
+            load_row<NR>(sr, (bL + m) * w, r0, w, r);
+            if constexpr (APPLY) load_row<NR>(sz, (bL + m) * w, r0, w, z);
+        } else {
+            load_row<NR>(sd, (bL + max(L - m - 1, 0)) * w, r0, w, d);
+        }
+    };
+    auto emit = [&](int m, const float (&x)[NR], const float (&z)[NR]) {
+        if constexpr (!APPLY) {
+            if (m == m1 - 1 && live)
+                store_row<NR, true>(a.q + ((long long)b * (a.C - 1) + c) * WP, r0, WP, x);
+        } else if constexpr (!BWD) {
+            float y[NR];
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                y[j] = z[j] + x[j];
+                mx = max(mx, __float_as_uint(fabsf(x[j])));
+                mz = max(mz, __float_as_uint(fabsf(y[j])));
+            }
+            if (live) store_row<NR, EXACT>(a.Z + (long long)(bL + m) * w, r0, w, y);
+        } else if (live) {
+            store_row<NR, EXACT>(m < L ? a.Lambda + (long long)(bL + L - 1 - m) * w : a.dz0 + (long long)b * w,
+                                 r0, w, x);
+        }
+    };
+    auto request = [&](int m, float (&rw)[S::MTW][S::KT][8], float (&d)[NR], float (&r)[NR],
+                       float (&z)[NR]) {
+        const int mm = min(m, m1 - 1);
+        const int op = BWD ? min(L - mm, L - 1) : mm;
+        load_strip<WP, BWD, EXACT>(Src<EXACT>(a.W + (long long)op * w * w, w * w), w, base, n, g,
+                                   rw);
+        aux(mm, d, r, z);
+    };
+    float x[NR];
+    int m = m0;
+    // the B operand of row m: x, scaled by row m's own d when transposed
+    auto put = [&](int buf, const float (&d)[NR]) {
+        if constexpr (BWD) {
+            float y[NR];
+#pragma unroll
+            for (int j = 0; j < NR; ++j) y[j] = d[j] * x[j];
+            put_panel<WP>(panel + buf * S::BUF, r0, n, y);
+        } else {
+            put_panel<WP>(panel + buf * S::BUF, r0, n, x);
+        }
+    };
+    {
+        float d0[NR] = {}, rr[NR], z0[NR];
+        if (APPLY && c > 0) {
+            const Src<true> sx(a.xe + ((long long)b * (a.C - 1) + c - 1) * WP, WP);
+            load_row<NR>(sx, 0, r0, WP, x);
+            if constexpr (BWD) load_row<NR>(sd, (bL + L - m) * w, r0, w, d0);
+        } else {
+            if constexpr (BWD)
+                load_row<NR>(sr, (unsigned)b * w, r0, w, x);  // G
+            else
+                load_row<NR>(sr, (bL + m) * w, r0, w, x);
+            aux(m, d0, rr, z0);
+            emit(m, x, z0);
+            ++m;
+        }
+        if (m < m1) put(0, d0);
+    }
+    if (m < m1) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) request(m + s, raw[s], ad[s], ar[s], az[s]);
+        for (int mb = m, buf = 0; mb < m1; mb += NB) {
+#pragma unroll
+            for (int s = 0; s < NB; ++s) {
+                const int row = mb + s;
+                if (row >= m1) break;
+                Parts8 A[S::MTW][S::KT];
+#pragma unroll
+                for (int q = 0; q < S::MTW; ++q)
+#pragma unroll
+                    for (int k = 0; k < S::KT; ++k) A[q][k] = split8(raw[s][q][k]);
+                __syncthreads();  // the panel of row - 1 is complete
+                    request(row + D, raw[(s + D) % NB], ad[(s + D) % NB], ar[(s + D) % NB],
+                        az[(s + D) % NB]);
+                const char* in = panel + buf * S::BUF + lane * 16;
+                Acc<f4> acc[S::MTW] = {};
+#pragma unroll
+                for (int k = 0; k < S::KT; ++k) {
+                    Parts8 p;
+                    p.h = *reinterpret_cast<const b8*>(in + k * 1024);
+                    p.m = *reinterpret_cast<const b8*>(in + (S::KT + k) * 1024);
+                    p.l = *reinterpret_cast<const b8*>(in + (2 * S::KT + k) * 1024);
+#pragma unroll
+                    for (int q = 0; q < S::MTW; ++q) mac(acc[q], A[q][k], p);
+                }
+#pragma unroll
+                for (int q = 0; q < S::MTW; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int j = S::MTW * e + q;
+                        float y = acc[q].x[e] + acc[q].s[e];
+                        if constexpr (!BWD) y *= ad[s][j];
+                        if (a.residual) y += x[j];
+                        if constexpr (!BWD) y += ar[s][j];
+                        x[j] = EXACT || r0 + j < w ? y : 0.f;
+                    }
+                buf ^= 1;
+                put(buf, ad[s]);
+                emit(row, x, az[s]);
+            }
+        }
+    }
+    if constexpr (APPLY && !BWD) {
+        if (!live) mx = mz = 0u;
+        for (int off = 32; off > 0; off >>= 1) {
+            mx = max(mx, (unsigned)__shfl_xor((int)mx, off, 64));
+            mz = max(mz, (unsigned)__shfl_xor((int)mz, off, 64));
+        }
+        if (lane == 0) {
+            const int slot = (blockIdx.x * 4 + v) % kRedShards;
+            atomicMax(a.red + kRedDZ + slot, mx);
+            atomicMax(a.red + kRedZ + slot, mz);
+        }
+    }
+}
+
+// ----------------------------------------------------------- product panels
+// P of chunk c for SYS systems: wave (system, 32 columns) keeps its columns
+// of the running product in registers, as the float32 results of a 32 x 32
+// tile per 32 rows and as the operand parts of the next product, whose lanes
+// hold exactly those rows (the k order of an operand is free, and the
+// weights are laid out to match).  So the waves of a workgroup share only
+// the weights: 4096 of them per stage are loaded into registers one stage
+// ahead, split, and put into one of two LDS buffers in operand order; one
+// barrier per stage.
+template <int WP, bool BWD, bool EXACT>
+__device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int c, int wg) {
+    using S = ProdShape<WP>;
+    const int t = threadIdx.x, v = t >> 6, lane = t & 63;
+    const int n = lane & 31, h = lane >> 5;
+    const int w = EXACT ? WP : a.w, L = a.L;
+    const int panel = v % S::MT;
+    const int bb = wg * S::SYS + v / S::MT;
+    const bool live = bb < a.B;
+    const int b = live ? bb : a.B - 1;
+    const int m0 = c * a.Lc, m1 = min(a.rows, m0 + a.Lc);
+    const Src<EXACT> sd(a.d, (unsigned)a.B * L * w);
+
+    // this thread's 4 x 4 weights of a stage: rows 4 rg .., columns 4 cg .. of
+    // the stage's 32-row block blk
+    const int rg = t & 7, cg = (t >> 3) % (WP / 4), blk = __builtin_amdgcn_readfirstlane(t / (2 * WP));
+    constexpr int LPS = S::LPS;
+    constexpr int SPL = WP == 128 ? 4 : 1;  // stages per layer
+    f4 raw[4];
+    // d of the layers a stage starts: SYS systems x WP rows per layer, thread
+    // t's element e is layer (t + 256 e) / 128's t % 128
+    constexpr int ND = (LPS + 1) / 2;
+    float rd[ND];
+    const int dsys = min(a.B - 1, wg * S::SYS + (t & 127) / WP), drow = (t & 127) % WP;
+    auto request = [&](int st) {
+#pragma unroll
+        for (int e = 0; e < ND; ++e) {
+            // (transposed: of the operator of the row after, which scales
+            // the columns that the product of this row leaves)
+            const int j = (t + 256 * e) >> 7;
+            const int m = min(m1 - 1, m0 + (WP == 128 ? st / 4 : st * LPS) + (LPS > 1 ? j : 0));
+            const int l = BWD ? max(L - m - 1, 0) : m;
+            const unsigned o = ((unsigned)dsys * L + l) * w + drow;
+            rd[e] = EXACT || drow < w ? sd.one(o) : 0.f;
+        }
+        const int m = min(m1 - 1, m0 + (WP == 128 ? st / 4 : WP == 64 ? st : 4 * st + blk));
+        const int mt = WP == 128 ? st % 4 : WP == 64 ? blk : 0;
+        const int i = 32 * mt + 4 * rg, k = 4 * cg;
+        // (as in load_strip, elements beyond a row's end meet zeros, or give
+        // rows that meet zeros)
+        const Src<EXACT> Wl(a.W + (long long)(BWD ? L - m : m) * w * w, w * w);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) raw[e] = Wl.at(((BWD ? k : i) + e) * w + (BWD ? i : k));
+    };
+    char* const dst = lds + (blk * S::KT + cg / 4) * 1024 + (4 * rg + 32 * (cg & 1)) * 16 +
+                      8 * ((cg >> 1) & 1);
+    auto put = [&](int buf) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const f4 x = BWD ? f4{raw[0][e], raw[1][e], raw[2][e], raw[3][e]} : raw[e];
+            const Parts2 p = split2(x[0], x[1]), q = split2(x[2], x[3]);
+            char* o = dst + buf * S::STAGE + e * 16;
+            *reinterpret_cast<u2*>(o) = u2{p.h, q.h};
+            *reinterpret_cast<u2*>(o + S::WB / 3) = u2{p.m, q.m};
+            *reinterpret_cast<u2*>(o + 2 * (S::WB / 3)) = u2{p.l, q.l};
+        }
+        float* const dd = reinterpret_cast<float*>(lds + buf * S::STAGE + S::WB);
+#pragma unroll
+        for (int e = 0; e < ND; ++e)
+            dd[LPS > 1 ? t + 256 * e : t & 127] = rd[e];
+    };
+
+    f16v P[S::MT];
+    Parts8 B[S::KT];
+    const int col = 32 * panel + n;
+#pragma unroll
+    for (int mt = 0; mt < S::MT; ++mt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            P[mt][e] = 32 * mt + 8 * (e / 4) + 4 * h + e % 4 == col ? 1.f : 0.f;
+    // d of rows 32 mt + 8 q + 4 h + 0..3, q = 0..3, from a stage
+    auto scale = [&](const float* dd, int mt, float (&d)[16]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f4 x = *reinterpret_cast<const f4*>(dd + 32 * mt + 8 * q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) d[4 * q + e] = x[e];
+        }
+    };
+    // the operand parts of P (transposed system: of diag(d) P, d of the next
+    // row; before the first row P = I, scaled by the first row's d)
+    auto operands = [&](const float* dd, bool first) {
+#pragma unroll
+        for (int mt = 0; mt < S::MT; ++mt) {
+            float d[16];
+            if constexpr (BWD) {
+                if (first)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        float x[4];
+                        load_row<4>(sd, ((unsigned)b * L + L - m0) * w, 32 * mt + 8 * q + 4 * h, w,
+                                    x);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) d[4 * q + e] = x[e];
+                    }
+                else
+                    scale(dd, mt, d);
+            }
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                float x[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    x[j] = P[mt][8 * half + j];
+                    if constexpr (BWD) x[j] *= d[8 * half + j];
+                }
+                B[2 * mt + half] = split8(x);
+            }
+        }
+    };
+    const float* const dbase =
+        reinterpret_cast<const float*>(lds + S::WB) + v / S::MT * WP + 4 * h;
+    request(0);
+    put(0);
+    request(1);
+    operands(nullptr, true);
+    for (int m = m0; m < m1; ++m) {
+        const int st0 = WP == 128 ? 4 * (m - m0) : (m - m0) / LPS;
+#pragma unroll
+        for (int mt = 0; mt < S::MT; ++mt) {
+            const int st = st0 + (SPL == 4 ? mt : 0);
+            if (SPL == 4 || (mt == 0 && (m - m0) % LPS == 0)) {
+                __syncthreads();  // stage st is in LDS, stage st - 1 is consumed
+            }
+            const int tile = WP == 128 ? 0 : WP == 64 ? 4 * mt : 2 * ((m - m0) % LPS);
+            const char* in = lds + (st & 1) * S::STAGE + tile * 1024 + lane * 16;
+            const float* dd = dbase + (st & 1) * (S::STAGE / 4) + 128 * ((m - m0) % LPS);
+            Acc<f16v> acc = {};
+            // a part of the weights is read for the next k tile as soon as its
+            // last product of this one is issued; the scheduling barriers
+            // keep that order and let everything else move
+            Parts8 A;
+            A.l = *reinterpret_cast<const b8*>(in + 2 * (S::WB / 3));
+            A.m = *reinterpret_cast<const b8*>(in + S::WB / 3);
+            A.h = *reinterpret_cast<const b8*>(in);
+            if (SPL == 4 || (mt == 0 && (m - m0) % LPS == 0)) {
+                // (past the last stage: its weights again, never read)
+                put((st + 1) & 1);
+                request(st + 2);
+            }
+            constexpr int kMove = 0x2 | 0x4 | 0x10 | 0x200;
+#pragma unroll
+            for (int k = 0; k < S::KT; ++k) {
+                const char* const next = in + (k + 1) * 1024;
+                const bool more = k + 1 < S::KT;
+                acc.s = mfma32(A.l, B[k].h, acc.s);
+                if (more) A.l = *reinterpret_cast<const b8*>(next + 2 * (S::WB / 3));
+                __builtin_amdgcn_sched_barrier(kMove);
+                acc.s = mfma32(A.m, B[k].m, acc.s);
+                acc.s = mfma32(A.m, B[k].h, acc.s);
+                if (more) A.m = *reinterpret_cast<const b8*>(next + S::WB / 3);
+                __builtin_amdgcn_sched_barrier(kMove);
+                acc.x = mfma32(A.h, B[k].h, acc.x);
+                acc.s = mfma32(A.h, B[k].l, acc.s);
+                acc.s = mfma32(A.h, B[k].m, acc.s);
+                if (more) A.h = *reinterpret_cast<const b8*>(next);
+                __builtin_amdgcn_sched_barrier(kMove);
+            }
+            float d[16];
+            if constexpr (!BWD) scale(dd, mt, d);
+            if (a.residual) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    P[mt][e] = BWD ? P[mt][e] + (acc.x[e] + acc.s[e])
+                                   : fmaf(d[e], acc.x[e] + acc.s[e], P[mt][e]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    P[mt][e] = BWD ? acc.x[e] + acc.s[e] : d[e] * (acc.x[e] + acc.s[e]);
+            }
+        }
+        const int last = st0 + SPL - 1;
+        if (m + 1 < m1)
+            operands(dbase + (last & 1) * (S::STAGE / 4) + 128 * ((m - m0) % LPS), false);
+    }
+    if (!live) return;
+    float* out = a.P + ((long long)b * (a.C - 1) + c) * WP * WP + col;
+#pragma unroll
+    for (int mt = 0; mt < S::MT; ++mt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            out[(long long)(32 * mt + 8 * (e / 4) + 4 * h + e % 4) * WP] = P[mt][e];
+}
+
+// The vectors of chunks 0 .. C-2 first (the longer chain per row and few
+// workgroups), then the products of chunks 1 .. C-2.
+template <int WP, bool BWD, bool EXACT>
+__global__ __launch_bounds__(kThr, WP == 128 ? 2 : 3) void chunk_pass(PanelArgs a) {
+    __shared__ __attribute__((aligned(16))) char
+        lds[ProdShape<WP>::LDS > VecShape<WP>::LDS ? ProdShape<WP>::LDS : VecShape<WP>::LDS];
+    const int vg = (a.B + 16 * VecShape<WP>::GPW - 1) / (16 * VecShape<WP>::GPW);
+    const int nv = vg * (a.C - 1);
+    if ((int)blockIdx.x < nv) {
+        vector_panel<WP, BWD, EXACT, false>(a, lds, blockIdx.x / vg, blockIdx.x % vg);
+        return;
+    }
+    const int pg = (a.B + ProdShape<WP>::SYS - 1) / ProdShape<WP>::SYS;
+    const int total = pg * (a.C - 2);
+    // workgroups go round-robin to the 8 XCDs: consecutive items, which share
+    // a chunk's weights, stay on one XCD and its L2
+    const int id = (int)blockIdx.x - nv, per = (total + 7) / 8;
+    const int item = (id & 7) * per + (id >> 3);
+    if (item >= total || (id >> 3) >= per) return;
+    product_panel<WP, BWD, EXACT>(a, lds, 1 + item / pg, item % pg);
+}
+
+template <int WP, bool BWD, bool EXACT>
+__global__ __launch_bounds__(kThr) void apply_pass(PanelArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[VecShape<WP>::LDS];
+    const int vg = (a.B + 16 * VecShape<WP>::GPW - 1) / (16 * VecShape<WP>::GPW);
+    vector_panel<WP, BWD, EXACT, true>(a, lds, blockIdx.x / vg, blockIdx.x % vg);
+}
+
+// ------------------------------------------------------------ layer vectors
+// d = c sigma'(a) and, forward, r = f(Z_{l-1}) - Z_l with its maximum, for
+// a = W_l Z_{l-1} + b_l: one layer per workgroup (a part of the batch where
+// there are few layers), the split weights in registers for all systems.
+// Bound by one read of W and of the states and the write of d and r.
+template <int WP, bool BWD, bool EXACT>
+__global__ __launch_bounds__(kThr) void layer_vectors(
+    const float* __restrict__ W, const float* __restrict__ bias, const float* __restrict__ z0,
+    const float* __restrict__ Z, float* __restrict__ d_out, float* __restrict__ r_out,
+    unsigned* __restrict__ red, int B, int L, int w_, int layer, float alpha, int parts) {
+    using S = VecShape<WP>;
+    constexpr int NR = S::NR;
+    const int t = threadIdx.x, v = t >> 6, lane = t & 63;
+    const int sub = v / S::WPG, wv = v % S::WPG;
+    const int n = lane & 15, g = lane >> 4;
+    const int w = EXACT ? WP : w_;
+    const int base = wv * 16 * S::MTW, r0 = base + NR * g;
+    const int l = blockIdx.x / parts, part = blockIdx.x % parts;
+    if constexpr (!BWD)
+        if (blockIdx.x == 0)
+            for (int k = t; k < 2 * kRedShards; k += kThr) red[k] = 0u;
+    const float* Wl = W + (long long)l * w * w;
+    Parts8 A[S::MTW][S::KT];
+    {
+        float raw[S::MTW][S::KT][8];
+        load_strip<WP, false, EXACT>(Src<EXACT>(Wl, w * w), w, base, n, g, raw);
+#pragma unroll
+        for (int q = 0; q < S::MTW; ++q)
+#pragma unroll
+            for (int k = 0; k < S::KT; ++k) A[q][k] = split8(raw[q][k]);
+    }
+    float bi[NR];
+    load_row<NR>(Src<EXACT>(bias + (long long)l * w, w), 0, r0, w, bi);
+    const bool res = layer_residual(layer);
+    unsigned mr = 0u;
+    const int ng = (B + 15) / 16;
+    const unsigned nv = (unsigned)B * L * w;
+    const Src<EXACT> sz(Z, nv), sp(l == 0 ? z0 : Z, l == 0 ? (unsigned)B * w : nv);
+    for (int gr = part * S::GPW + sub; gr < ng; gr += parts * S::GPW) {
+        const int bb = gr * 16 + n;
+        const bool live = bb < B;
+        const int b = live ? bb : B - 1;
+        const unsigned op = l == 0 ? b * w : ((unsigned)b * L + l - 1) * w;
+        const unsigned o = ((unsigned)b * L + l) * w;
+        float zl[NR], zr[NR];
+        if constexpr (!BWD) load_row<NR>(sz, o, r0, w, zl);
+        if (!BWD && res) load_row<NR>(sp, op, r0, w, zr);
+        Acc<f4> acc[S::MTW] = {};
+#pragma unroll
+        for (int k = 0; k < S::KT; ++k) {
+            float x[8];
+            load_row<8>(sp, op, 32 * k + 8 * g, w, x);
+            const Parts8 p = split8(x);
+#pragma unroll
+            for (int q = 0; q < S::MTW; ++q) mac(acc[q], A[q][k], p);
+        }
+        float dv[NR], rv[NR];
+#pragma unroll
+        for (int q = 0; q < S::MTW; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int j = S::MTW * e + q;
+                float y = acc[q].x[e] + acc[q].s[e] + bi[j];
+                // an infinity has no split, and a value that rounds up to one
+                // none either: such a row is summed as it stands
+                if (__builtin_expect(!(fabsf(y) <= 3.0e38f), 0)) {
+                    y = bi[j];
+                    if (EXACT || r0 + j < w)
+                        for (int k = 0; k < w; ++k)
+                            y = fmaf(Wl[(long long)(r0 + j) * w + k], sp.one(op + k), y);
+                }
+                float dd;
+                const float f = activate(layer, y, &dd);
+                dv[j] = res ? alpha * dd : dd;
+                if constexpr (!BWD) {
+                    rv[j] = (res ? fmaf(alpha, f, zr[j]) : f) - zl[j];
+                    if (live && (EXACT || r0 + j < w))
+                        mr = max(mr, __float_as_uint(fabsf(rv[j])));
+                }
+            }
+        if (live) {
+            store_row<NR, EXACT>(d_out + o, r0, w, dv);
+            if constexpr (!BWD) store_row<NR, EXACT>(r_out + o, r0, w, rv);
+        }
+    }
+    if constexpr (!BWD) {
+        for (int off = 32; off > 0; off >>= 1) mr = max(mr, (unsigned)__shfl_xor((int)mr, off, 64));
+        if (lane == 0) atomicMax(red + kRedF + (int)((blockIdx.x * 4 + v) % kRedShards), mr);
+    }
+}
+
+int padded(int w) { return w <= 32 ? 32 : w <= 64 ? 64 : 128; }
+
+#define DEEPPCR_PANEL(K, BW, GRID, ...)                                                         \
+    do {                                                                                        \
+        const dim3 grid_((unsigned)(GRID)), thr_(kThr);                                         \
+        switch (a_w) {                                                                          \
+            case 32: hipLaunchKernelGGL((K<32, BW, true>), grid_, thr_, 0, st, __VA_ARGS__); break;   \
+            case 64: hipLaunchKernelGGL((K<64, BW, true>), grid_, thr_, 0, st, __VA_ARGS__); break;   \
+            case 128: hipLaunchKernelGGL((K<128, BW, true>), grid_, thr_, 0, st, __VA_ARGS__); break; \
+            default:                                                                            \
+                if (a_w < 32) hipLaunchKernelGGL((K<32, BW, false>), grid_, thr_, 0, st, __VA_ARGS__); \
+                else if (a_w < 64) hipLaunchKernelGGL((K<64, BW, false>), grid_, thr_, 0, st, __VA_ARGS__); \
+                else hipLaunchKernelGGL((K<128, BW, false>), grid_, thr_, 0, st, __VA_ARGS__);  \
+        }                                                                                       \
+    } while (0)
+
+int vector_groups(int B, int WP) {
+    const int per = WP == 32 ? 32 : 16;
+    return (B + per - 1) / per;
+}
+int product_groups(int B, int WP) {
+    const int per = 128 / WP;
+    return (B + per - 1) / per;
+}
+
+}  // namespace
+
+// (w = 16 has PCR kernels of its own, 0.7-1.2 times as fast over B and L)
+bool panel_width(int w) { return w > 8 && w <= kMaxWidth && w != 16; }
+int panel_pad(int w) { return padded(w); }
+
+// Chunks of a solve.  The products run in parallel over chunks and cost the
+// same in total, so there are as many chunks as keep one round of workgroups
+// on the chip (two per CU at a padded width of 128, three below; at 32, whose
+// rows are short, one and a half rounds were faster: 600 us against 680 per
+// mlp_fwd call), unless the substitution over the chunk ends, one row after
+// the other, would then cost more than the rows of a chunk: C^2 = 4 rows.
+int panel_chunks(int B, int rows, int w) {
+    const int WP = padded(w);
+    const int slots = 256 * (WP == 128 ? 4 : WP == 64 ? 6 : 9) / 2;
+    int C = 1 + slots / (product_groups(B, WP) + vector_groups(B, WP));
+    int root = 1;
+    while ((long long)root * root < 4LL * rows) ++root;
+    // a long chain of few systems: the PCR levels have the parallelism
+    if (w == WP && root > 100 && C > root) return 0;
+    if (C > root) C = root;
+    if (C > rows) C = rows;
+    return C;
+}
+
+hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, const float* z0,
+                                const float* Z, float* d, float* r, unsigned* red, int B, int L,
+                                int w, int layer, float alpha, hipStream_t st) {
+    // enough workgroups for the chip, one part of the batch each
+    const int WP = padded(w), groups = vector_groups(B, WP);
+    int parts = 2048 / L;
+    if (parts > groups) parts = groups;
+    if (parts < 1) parts = 1;
+    const int a_w = w;
+    if (bwd)
+        DEEPPCR_PANEL(layer_vectors, true, (long long)L * parts, W, bias, z0, Z, d, r, red, B, L, w,
+                      layer, alpha, parts);
+    else
+        DEEPPCR_PANEL(layer_vectors, false, (long long)L * parts, W, bias, z0, Z, d, r, red, B, L,
+                      w, layer, alpha, parts);
+    return hipGetLastError();
+}
+
+hipError_t launch_chunk_pass(bool bwd, const PanelArgs& a, hipStream_t st) {
+    const int WP = padded(a.w), a_w = a.w;
+    const long long nv = (long long)vector_groups(a.B, WP) * (a.C - 1);
+    const long long np = (long long)product_groups(a.B, WP) * (a.C - 2);
+    const long long grid = nv + (np + 7) / 8 * 8;
+    if (bwd)
+        DEEPPCR_PANEL(chunk_pass, true, grid, a);
+    else
+        DEEPPCR_PANEL(chunk_pass, false, grid, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_apply_pass(bool bwd, const PanelArgs& a, hipStream_t st) {
+    const int a_w = a.w;
+    const long long grid = (long long)vector_groups(a.B, padded(a.w)) * a.C;
+    if (bwd)
+        DEEPPCR_PANEL(apply_pass, true, grid, a);
+    else
+        DEEPPCR_PANEL(apply_pass, false, grid, a);
+    return hipGetLastError();
+}
+
+}  // namespace deeppcr

@@ -1,0 +1,83 @@
+"""GPU parity of the chunked MLP solve (widths 9 to 128) where its tiles and
+chunks end: widths on both sides of the padded ones and odd ones whose rows
+start on any 4-byte boundary, batches on both sides of a group of systems,
+depths giving one, two, three and many chunks, a short last chunk.  Against
+the CPU oracle on the same seeded float32 inputs.
+
+Tolerance: a float32 dot product of w terms is within w 2^-24 of its terms'
+norm whatever its order, and in these contracting networks a perturbation of
+one row fades within a few rows; 4 rows of it are allowed for, relative to
+the largest entry of the system (as normwise_rel_err measures)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2309_16318_amd import deeppcr, synth
+from tests._util import normwise_rel_err
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# (w, B, L)
+SHAPES = [(9, 1, 40), (9, 33, 70), (15, 17, 100), (17, 3, 129), (24, 16, 64), (31, 5, 63),
+          (32, 1, 1), (32, 4, 2), (32, 33, 3), (32, 129, 200), (33, 3, 65), (47, 2, 257),
+          (48, 31, 90), (63, 16, 33), (64, 1, 64), (64, 17, 300), (65, 3, 50), (97, 2, 130),
+          (100, 7, 200), (127, 1, 65), (128, 1, 5), (128, 15, 100), (128, 16, 257)]
+
+
+@pytest.fixture(scope="module")
+def dev():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return torch.device("cuda:0")
+
+
+def g(a, dev):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(dev)
+
+
+def h(t):
+    torch.cuda.synchronize()
+    return t.detach().cpu().numpy()
+
+
+@pytest.mark.parametrize("w,B,L", SHAPES)
+@pytest.mark.parametrize("layer,alpha", [(0, 1.0), (1, 0.1)])
+def test_forward_backward(dev, w, B, L, layer, alpha):
+    print(f"panels w={w} B={B} L={L} layer={layer}", flush=True)
+    tol = 4 * w * 2.0 ** -24
+    if layer == 1:
+        tol *= 1 + alpha * L / 8  # a residual network carries a perturbation on
+    d = synth.mlp_inputs(B, L, w, seed=4200 + w + B + L)
+    W, bias, z0 = g(d["W"], dev), g(d["bias"], dev), g(d["z0"], dev)
+    res = deeppcr.deeppcr_mlp_forward(W, bias, z0, layer=layer, alpha=alpha)
+    ref = oracle.seq_forward(layer, alpha, d["W"], d["bias"], d["z0"])
+    assert res.status == deeppcr.OK
+    err = normwise_rel_err(h(res.Z), ref)
+    Z32 = ref.astype(np.float32)
+    lam, dz0, dW, db = deeppcr.deeppcr_mlp_backward(W, bias, z0, g(Z32, dev), g(d["G"], dev),
+                                                    layer=layer, alpha=alpha)
+    rl, rz, rW, rb = oracle.seq_backward(layer, alpha, d["W"], d["bias"], d["z0"], Z32, d["G"])
+    eb = normwise_rel_err(np.concatenate([h(dz0)[:, None], h(lam)], 1),
+                          np.concatenate([rz[:, None], rl], 1))
+    eW, eb2 = (normwise_rel_err(h(a), b, axes="all") for a, b in ((dW, rW), (db, rb)))
+    print(f"  Z {err:.1e} adjoints {eb:.1e} dW {eW:.1e} db {eb2:.1e} tol {tol:.1e}", flush=True)
+    assert max(err, eb, eW, eb2) <= tol
+
+
+def test_infinite_input_saturates(dev):
+    """An infinite input has no split into parts: the saturating activation
+    still maps it to 1, as a plain sum does."""
+    d = synth.mlp_inputs(3, 40, 64, seed=5)
+    z0 = d["z0"].copy()
+    z0[1, 7] = np.inf
+    z0[2, 3] = 3.39e38
+    W = d["W"].copy()
+    W[0, :, 7] = np.abs(W[0, :, 7]) + 0.1
+    W[0, :, 3] = np.abs(W[0, :, 3]) + 0.1
+    res = deeppcr.deeppcr_mlp_forward(g(W, dev), g(d["bias"], dev), g(z0, dev))
+    assert res.status == deeppcr.OK
+    Z = h(res.Z)
+    assert np.all(Z[1:, 0] == 1.0)
+    ref = oracle.seq_forward(0, 1.0, W[1:], d["bias"][1:], np.ones((1, 64), np.float32))
+    assert np.max(np.abs(Z[1:, 1:] - ref)) <= 4 * 64 * 2.0 ** -24
