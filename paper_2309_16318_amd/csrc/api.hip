@@ -721,6 +721,7 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
     const long long n = (long long)B * L * w;
     const VecDst xd{ws.r[(num_passes(B, L, w) + 1) & 1], (long long)L * w, (long long)w};
     const PanelPlan pl = panel_plan(B, L, w, false);
+    const bool wide_sub = wide_width(w) && wide_substitution(B, L, w);
     const bool fused = layer_first_level(w);
     const NewtonArgs na{W, bias, z0, Z, ws.red, layer, alpha};
     unsigned* fslots = ws.red + kRedF;
@@ -739,6 +740,11 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
             e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 4.0 * n), 2.0 * B * L * w2, st, [&] {
                 return launch_layer_vectors(false, W, bias, z0, Z, ws.r[1], ws.r[0], ws.red, B, L,
                                             w, layer, alpha, st);
+            });
+        } else if (wide_sub) {
+            e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 4.0 * n), 2.0 * B * L * w2, st, [&] {
+                return launch_wide_vectors(false, W, bias, z0, Z, ws.r[1], ws.r[0], ws.red, B, L,
+                                           w, layer, alpha, st);
             });
         } else if (fused) {
             e = fused_first_level(na, B, L, w, ws, xd, st);
@@ -778,6 +784,16 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
             pa.residual = layer_residual(layer);
             e = panel_solve(false, pa, pl, workspace, st);
             if (e != hipSuccess) return hip_fail(e, "chunked solve");
+        } else if (wide_sub) {
+            for (int l = 1; l < L && e == hipSuccess; ++l)
+                e = timed(DEEPPCR_KCLASS_PCR_TAIL, 4.0 * (w2 + 3.0 * B * w), 2.0 * B * w2, st, [&] {
+                    return launch_wide_step(W, ws.r[1], ws.r[0], B, L, w, layer_residual(layer), l,
+                                            st);
+                });
+            if (e != hipSuccess) return hip_fail(e, "wide_step");
+            e = timed(DEEPPCR_KCLASS_UPDATE, 12.0 * n, 2.0 * n, st,
+                      [&] { return launch_update_reduce(Z, ws.r[0], n, ws.red, st); });
+            if (e != hipSuccess) return hip_fail(e, "update_reduce");
         } else if (fused) {
             e = fused_rest_levels(na, B, L, w, ws, xd, st);
             if (e != hipSuccess) return hip_fail(e, "newton levels");
@@ -1201,6 +1217,28 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
         pa.residual = layer_residual(layer);
         e = panel_solve(true, pa, pl, workspace, st);
         if (e != hipSuccess) return hip_fail(e, "chunked solve");
+        e = timed(DEEPPCR_KCLASS_WGRAD, 4.0 * (3.0 * B * L * w + L * (w2 + w)), 2.0 * B * L * w2,
+                  st, [&] { return launch_wgrad(z0, Z, ws.dscale, Lambda, dW, db, B, L, w, st); });
+        if (e != hipSuccess) return hip_fail(e, "wgrad");
+        return DEEPPCR_OK;
+    }
+    if (wide_width(w) && wide_substitution(B, L + 1, w)) {
+        const long long ld = (long long)L * w;
+        hipError_t e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 2.0 * B * L * w),
+                             2.0 * B * L * w2, st, [&] {
+            return launch_wide_vectors(true, W, bias, z0, Z, ws.dscale, nullptr, nullptr, B, L, w,
+                                       layer, alpha, st);
+        });
+        if (e != hipSuccess) return hip_fail(e, "wide_vectors");
+        e = timed(DEEPPCR_KCLASS_OTHER, 8.0 * B * w, 0.0, st, [&] {
+            return launch_copy_rows(VecSrc{G, w, w}, VecDst{Lambda + ld - w, ld, w}, B, 1, w, st);
+        });
+        for (int l = L - 1; l >= 0 && e == hipSuccess; --l)
+            e = timed(DEEPPCR_KCLASS_PCR_TAIL, 4.0 * (w2 + 3.0 * B * w), 2.0 * B * w2, st, [&] {
+                return launch_wide_step_t(W, ws.dscale, G, Lambda, dz0, B, L, w,
+                                          layer_residual(layer), l, st);
+            });
+        if (e != hipSuccess) return hip_fail(e, "wide_step_t");
         e = timed(DEEPPCR_KCLASS_WGRAD, 4.0 * (3.0 * B * L * w + L * (w2 + w)), 2.0 * B * L * w2,
                   st, [&] { return launch_wgrad(z0, Z, ws.dscale, Lambda, dW, db, B, L, w, st); });
         if (e != hipSuccess) return hip_fail(e, "wgrad");

@@ -392,6 +392,19 @@ hipError_t launch_backward_assemble_wide(const float* W, const float* bias, cons
                                          const float* Z, const float* G, float* A, float* rrev,
                                          float* dscale, int B, int L, int w, int layer,
                                          float alpha, hipStream_t stream);
+// Whether a solve of `rows` rows goes row by row instead of by PCR levels;
+// the layers' d and r (as launch_layer_vectors); one row of the forward solve
+// in place (r_l becomes the solution), l >= 1; one row of the transposed solve
+// (Lambda_{l-1}, or dz0 at l = 0, from Lambda_l, or G at l = L - 1).
+bool wide_substitution(int B, int rows, int w);
+hipError_t launch_wide_vectors(bool bwd, const float* W, const float* bias, const float* z0,
+                               const float* Z, float* d, float* r, unsigned* red, int B, int L,
+                               int w, int layer, float alpha, hipStream_t stream);
+hipError_t launch_wide_step(const float* W, const float* d, float* r, int B, int L, int w,
+                            int residual, int l, hipStream_t stream);
+hipError_t launch_wide_step_t(const float* W, const float* d, const float* G, float* Lambda,
+                              float* dz0, int B, int L, int w, int residual, int l,
+                              hipStream_t stream);
 hipError_t launch_dz0_wide(const float* W, const float* dscale, const float* Lambda, float* dz0,
                            int B, int L, int w, int layer, hipStream_t stream);
 hipError_t launch_wgrad_wide(const float* z0, const float* Z, const float* dscale,

@@ -529,6 +529,145 @@ __global__ __launch_bounds__(kThreads) void wgrad_wide(
     if (t < kWgRows && i0 + t < w) db[(long long)l * w + i0 + t] = dbacc;
 }
 
+// ----------------------------------------------- solves by substitution
+// At these widths a block product costs w mat-vecs, and one mat-vec already
+// fills the chip, so the linear solves of a Newton iteration and of the
+// backward pass go row by row where that is cheaper than the PCR levels
+// (wide_substitution): one launch per row, every block W_l read once for a
+// tile of systems, no block stored.  B = 1, L = 256, w = 1024, forward and
+// backward: 212 ms by PCR levels, 10.0 ms by rows.  What bounds a row is the
+// launch and the latency of its two dependent reads (3.6 us at w = 256, 4.5
+// at 1024, where reading W_l at the copy rate would take 0.8).
+constexpr int kSubB = 8;      // systems per workgroup
+constexpr int kEvalRows = 4;  // rows per wave of the layer evaluation
+
+// d = c sigma'(a) and, forward, r = f(Z_{l-1}) - Z_l with its maximum.
+// Grid (row groups, L, system tiles).
+template <bool VEC, bool BWD>
+__global__ __launch_bounds__(kThreads) void wide_vectors(
+    const float* __restrict__ W, const float* __restrict__ bias, const float* __restrict__ z0,
+    const float* __restrict__ Z, float* __restrict__ d_out, float* __restrict__ r_out,
+    unsigned* __restrict__ red, int B, int L, int w, int layer, float alpha) {
+    __shared__ float zs[kSubB][kWide];
+    const int l = blockIdx.y, b0 = kSubB * blockIdx.z;
+    const int nb = min(kSubB, B - b0);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if constexpr (!BWD)
+        if (blockIdx.x + blockIdx.y + blockIdx.z == 0)
+            for (int k = threadIdx.x; k < 2 * kRedShards; k += kThreads) red[k] = 0u;
+    for (int bb = 0; bb < nb; ++bb)
+        stage_vec(zs[bb], l == 0 ? z0 + (long long)(b0 + bb) * w
+                                 : Z + ((long long)(b0 + bb) * L + l - 1) * w, w);
+    __syncthreads();
+    const bool res = layer_residual(layer);
+    unsigned mr = 0u;
+    for (int q = 0; q < kEvalRows; ++q) {
+        const int i = (kWaves * blockIdx.x + wave) * kEvalRows + q;
+        if (i >= w) break;
+        float v[16];
+        row_load<VEC>(W + ((long long)l * w + i) * w, w, v, lane);
+        const float bi = bias[(long long)l * w + i];
+        for (int bb = 0; bb < nb; ++bb) {
+            const float a = row_dot<VEC>(v, zs[bb], lane) + bi;
+            if (lane != 0) continue;
+            float d;
+            const float y = activate(layer, a, &d);
+            const long long o = ((long long)(b0 + bb) * L + l) * w + i;
+            d_out[o] = res ? alpha * d : d;
+            if constexpr (!BWD) {
+                const float rv = (res ? fmaf(alpha, y, zs[bb][i]) : y) - Z[o];
+                r_out[o] = rv;
+                mr = max(mr, __float_as_uint(fabsf(rv)));
+            }
+        }
+    }
+    if constexpr (!BWD)
+        if (lane == 0)
+            atomicMax(red + kRedF + (int)((blockIdx.x + 64 * blockIdx.y + wave) % kRedShards), mr);
+}
+
+// Row l >= 1 of the forward solve, in place: r_l += d_l (W_l r_{l-1}) (+ r_{l-1}).
+template <bool VEC>
+__global__ __launch_bounds__(kThreads) void wide_step(const float* __restrict__ W,
+                                                      const float* __restrict__ d, float* r, int B,
+                                                      int L, int w, int residual, int l,
+                                                      int tile) {
+    __shared__ float xs[kSubB][kWide];
+    const int b0 = tile * blockIdx.y;
+    const int nb = min(tile, B - b0);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i = kWaves * blockIdx.x + wave;
+    float v[16];
+    if (i < w) row_load<VEC>(W + ((long long)l * w + i) * w, w, v, lane);
+    for (int bb = 0; bb < nb; ++bb)
+        stage_vec(xs[bb], r + ((long long)(b0 + bb) * L + l - 1) * w, w);
+    __syncthreads();
+    if (i >= w) return;
+    for (int bb = 0; bb < nb; ++bb) {
+        const float a = row_dot<VEC>(v, xs[bb], lane);
+        if (lane != 0) continue;
+        const long long o = ((long long)(b0 + bb) * L + l) * w + i;
+        const float x = fmaf(d[o], a, r[o]);
+        r[o] = residual ? x + xs[bb][i] : x;
+    }
+}
+
+// One row of the transposed solve: out = W_l^T (d_l lam) (+ lam).  Sixteen
+// columns per workgroup (one 64-byte piece of every row of W_l), the rows over
+// 128 groups of four threads, eight rows of a group in flight at once; the
+// groups meet through lane exchanges and LDS in a fixed order.
+constexpr int kStepT = 512, kStepTB = 4;
+template <bool VEC>
+__global__ __launch_bounds__(kStepT) void wide_step_t(
+    const float* __restrict__ Wl, const float* __restrict__ d, long long d_bstride,
+    const float* __restrict__ lam, long long lam_bstride, float* __restrict__ out,
+    long long out_bstride, int B, int w, int residual, int tile) {
+    __shared__ float gs[kStepTB][kWide];
+    __shared__ float part[kStepT / 64][kStepTB][16];
+    const int b0 = tile * blockIdx.y;
+    const int nb = min(tile, B - b0);
+    const int t = threadIdx.x, c = 16 * blockIdx.x + 4 * (t & 3), rg = t >> 2;
+    v4f v[kWide / 128];
+#pragma unroll
+    for (int u = 0; u < kWide / 128; ++u) {
+        const int i = rg + 128 * u;
+        const float* row = Wl + (long long)i * w + c;
+        if constexpr (VEC) {
+            v[u] = i < w && c < w ? *reinterpret_cast<const v4f*>(row) : v4f{0.f, 0.f, 0.f, 0.f};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[u][e] = i < w && c + e < w ? row[e] : 0.f;
+        }
+    }
+    for (int bb = 0; bb < nb; ++bb)
+        for (int i = t; i < kWide; i += kStepT)
+            gs[bb][i] = i < w ? d[(b0 + bb) * d_bstride + i] * lam[(b0 + bb) * lam_bstride + i]
+                              : 0.f;
+    __syncthreads();
+    for (int bb = 0; bb < nb; ++bb) {
+        v4f a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < kWide / 128; ++u) {
+            const float x = gs[bb][rg + 128 * u];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = fmaf(v[u][e], x, a[e]);
+        }
+        for (int off = 4; off < 64; off *= 2)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] += __shfl_xor(a[e], off, 64);
+        if ((t & 63) < 4) *reinterpret_cast<v4f*>(&part[t >> 6][bb][4 * (t & 3)]) = a;
+    }
+    __syncthreads();
+    const int bb = t >> 4, col = 16 * blockIdx.x + (t & 15);
+    if (bb < nb && col < w) {
+        float sum = 0.f;
+#pragma unroll
+        for (int q = 0; q < kStepT / 64; ++q) sum += part[q][bb][t & 15];
+        if (residual) sum += lam[(b0 + bb) * lam_bstride + col];
+        out[(b0 + bb) * out_bstride + col] = sum;
+    }
+}
+
 // ------------------------------------------------------ sequential passes
 // One layer l of the sequential passes for a tile of up to 8 systems:
 // workgroup (row group, system tile), a wave per row i of W_l, the row held
@@ -626,6 +765,81 @@ hipError_t launch_forward_eval_wide(const float* W, const float* bias, const flo
     else
         hipLaunchKernelGGL((forward_eval_wide<false>), grid, dim3(kThreads), 0, stream, W, bias,
                            z0, Z, A, r, red, L, w, layer, alpha);
+    return hipGetLastError();
+}
+
+// Systems per workgroup of a forward row: as few as leave eight workgroups
+// per CU, since each system of a tile costs its waves a sum (0.8 us).
+static int step_tile(int B, int w) {
+    const long long wgs = (long long)B * ((w + kWaves - 1) / kWaves);
+    const int n = (int)((wgs + 2047) / 2048);
+    return n < 1 ? 1 : n > kSubB ? kSubB : n;
+}
+
+bool wide_substitution(int B, int rows, int w) {
+    // Measured (B 1-64, L 16-1024): a row by substitution 3-4 us and 0.8 us
+    // per system of a tile (w = 1024: 4.5 and 6); a PCR level 15 us + 0.15
+    // w at the least, its products 15, 29, 36, 60 and 110 TFLOP/s at w = 129,
+    // 160, 200, 256, 1024 (tiles of 128 x 128).
+    const double fill = (double)w / ((w + kTile - 1) / kTile * kTile);
+    double flops = 0.0, us = 0.0;
+    for (long long s = 1; s < rows; s *= 2) {
+        if (rows > 2 * s) flops += (double)B * (rows - 2 * s) * 2.0 * w * w * w;
+        us += 15.0 + 0.15 * w;
+    }
+    us += flops / (1e6 * (45.0 + 0.065 * w) * fill * fill);
+    return rows * (4.4 + 0.8 * step_tile(B, w)) < us;
+}
+
+hipError_t launch_wide_vectors(bool bwd, const float* W, const float* bias, const float* z0,
+                               const float* Z, float* d, float* r, unsigned* red, int B, int L,
+                               int w, int layer, float alpha, hipStream_t stream) {
+    const int rows = kWaves * kEvalRows;
+    const dim3 grid((unsigned)((w + rows - 1) / rows), (unsigned)L,
+                    (unsigned)((B + kSubB - 1) / kSubB));
+#define DEEPPCR_WIDE_VEC(V, T)                                                              \
+    hipLaunchKernelGGL((wide_vectors<V, T>), grid, dim3(kThreads), 0, stream, W, bias, z0, Z, d, \
+                       r, red, B, L, w, layer, alpha)
+    if (w % 4 == 0 && bwd) DEEPPCR_WIDE_VEC(true, true);
+    else if (w % 4 == 0) DEEPPCR_WIDE_VEC(true, false);
+    else if (bwd) DEEPPCR_WIDE_VEC(false, true);
+    else DEEPPCR_WIDE_VEC(false, false);
+#undef DEEPPCR_WIDE_VEC
+    return hipGetLastError();
+}
+
+hipError_t launch_wide_step(const float* W, const float* d, float* r, int B, int L, int w,
+                            int residual, int l, hipStream_t stream) {
+    const int tile = step_tile(B, w);
+    const dim3 grid((unsigned)((w + kWaves - 1) / kWaves), (unsigned)((B + tile - 1) / tile));
+    if (w % 4 == 0)
+        hipLaunchKernelGGL((wide_step<true>), grid, dim3(kThreads), 0, stream, W, d, r, B, L, w,
+                           residual, l, tile);
+    else
+        hipLaunchKernelGGL((wide_step<false>), grid, dim3(kThreads), 0, stream, W, d, r, B, L, w,
+                           residual, l, tile);
+    return hipGetLastError();
+}
+
+hipError_t launch_wide_step_t(const float* W, const float* d, const float* G, float* Lambda,
+                              float* dz0, int B, int L, int w, int residual, int l,
+                              hipStream_t stream) {
+    const int fit = (int)(((long long)B * ((w + 15) / 16) + 1023) / 1024);
+    const int tile = fit < kStepTB ? fit : kStepTB;
+    const dim3 grid((unsigned)((w + 15) / 16), (unsigned)((B + tile - 1) / tile));
+    const long long ld = (long long)L * w;
+    const float* Wl = W + (long long)l * w * w;
+    const float* dl = d + (long long)l * w;
+    const float* lam = l == L - 1 ? G : Lambda + (long long)l * w;
+    const long long lam_ld = l == L - 1 ? w : ld;
+    float* out = l > 0 ? Lambda + (long long)(l - 1) * w : dz0;
+    const long long out_ld = l > 0 ? ld : w;
+    if (w % 4 == 0)
+        hipLaunchKernelGGL((wide_step_t<true>), grid, dim3(kStepT), 0, stream, Wl, dl, ld, lam,
+                           lam_ld, out, out_ld, B, w, residual, tile);
+    else
+        hipLaunchKernelGGL((wide_step_t<false>), grid, dim3(kStepT), 0, stream, Wl, dl, ld, lam,
+                           lam_ld, out, out_ld, B, w, residual, tile);
     return hipGetLastError();
 }
 
