@@ -295,6 +295,51 @@ void tail_work(int B, int L, int w, int kt, double* bytes, double* flops) {
 // Stride of the rows the last kt levels start from.
 int tail_stride(int L, int kt) { return 1 << (num_levels(L) - kt); }
 
+// Whether a solve on stored blocks goes by chunks (blocks.hip): widths up to
+// kMaxWidth, but not many rows of the smallest blocks, which fill a sixteenth
+// or less of a padded one (w = 2, B = 64, L = 1024: PCR levels 38 us, chunks
+// 44; B = 1, L = 4096 the other way round, 52 and 42).
+bool by_chunks(int B, int L, int w) {
+    return w <= kMaxWidth && !(w <= 3 && (double)B * L >= 16384);
+}
+
+// The solve on stored blocks, widths up to kMaxWidth, by chunks (blocks.hip).
+// `space`: B L w^2 floats at least.  With upd_red the solution is added to x
+// (the Newton iterate) and its maxima go to the slots of upd_red.
+hipError_t block_solve(const BlockSrc& A, const VecSrc& r, const VecDst& x, int B, int L, int w,
+                       float* space, hipStream_t st, unsigned* upd_red,
+                       const LayerScale* y = nullptr) {
+    BlockPlan pl;
+    block_plan(B, L, w, &pl);
+    const int Lc = pl.m ? pl.m : L, C = (L + Lc - 1) / Lc;
+    const double w2 = (double)w * w, rows = (double)B * L;
+    const float *xe = nullptr, *walk = nullptr;
+    if (C > 1) {
+        const size_t Ce = (size_t)B * (C - 1);
+        const auto up4 = [](size_t n) { return (n + 3) / 4 * 4; };
+        float* P = space;
+        float* q = P + up4(Ce * w * w);
+        float* e = q + up4(Ce * w);
+        hipError_t err = timed(DEEPPCR_KCLASS_PCR_LEVEL, 4.0 * (rows * (w2 + w) + Ce * (w2 + w)),
+                               rows * 2.0 * w2 * (w + 1), st,
+                               [&] { return launch_block_up(A, y, r, P, q, B, L, w, Lc, C, st); });
+        if (err != hipSuccess) return err;
+        xe = q;
+        if (pl.walk) {
+            walk = P;
+        } else if (C > 2) {
+            const long long nv = (long long)(C - 1) * w;
+            err = block_solve(BlockSrc{P, nv * w, (long long)w * w, 0}, VecSrc{q, nv, w},
+                              VecDst{e, nv, w}, B, C - 1, w, e + up4(Ce * w), st, nullptr);
+            if (err != hipSuccess) return err;
+            xe = e;
+        }
+    }
+    return timed(DEEPPCR_KCLASS_PCR_TAIL, 4.0 * rows * (w2 + (upd_red ? 3.0 : 2.0) * w),
+                 rows * 2.0 * w2, st,
+                 [&] { return launch_block_down(A, y, r, x, xe, walk, upd_red, B, L, w, Lc, C, st); });
+}
+
 // Runs all PCR levels.  Level 0 reads (A0, r0); level k writes operators to
 // ws A buffer (k + a_first) % 2 and vectors to ws r buffer (k + r_first) % 2,
 // except the last level, which writes the solution to `x`.
@@ -303,6 +348,7 @@ int tail_stride(int L, int kt) { return 1 << (num_levels(L) - kt); }
 hipError_t pcr_sweep(const BlockSrc& A0, const VecSrc& r0, const VecDst& x, int B, int L, int w,
                      float* wsA[2], float* wsr[2], int a_first, int r_first, hipStream_t st,
                      const BwdArgs* bwd = nullptr, unsigned* upd_red = nullptr) {
+    if (by_chunks(B, L, w) && !bwd) return block_solve(A0, r0, x, B, L, w, wsA[0], st, upd_red);
     const int K = num_levels(L);
     if (K == 0) {
         const double bytes = 8.0 * B * L * w;
@@ -564,12 +610,11 @@ hipError_t fused_rest_levels(const NewtonArgs& na, int B, int L, int w, const Ws
 
 // ------------------------------------------------- chunked MLP solve
 // Chunks and workspace of the chunked solve (panels.hip): P, q and the
-// solution at the chunk ends, and the buffers of a PCR sweep over them, all
-// in the space of the operator buffers A, which this path does not store.
+// solution at the chunk ends, and the space of their own solve, all in the
+// operator buffers A, which this path does not store.
 struct PanelPlan {
-    int C = 0, Lc = 0;      // C = 0: not for this shape
-    bool sweep = false;     // chunk ends by PCR levels, else by substitution
-    size_t P, q, xe, A[2], r[2];
+    int C = 0, Lc = 0;  // C = 0: not for this shape
+    size_t P, q, xe, space;
 };
 
 PanelPlan panel_plan(int B, int L, int w, bool bwd) {
@@ -584,17 +629,13 @@ PanelPlan panel_plan(int B, int L, int w, bool bwd) {
         pl.Lc = (rows + C - 1) / C;
         pl.C = (rows + pl.Lc - 1) / pl.Lc;
         const size_t Ce = pl.C > 1 ? pl.C - 1 : 0;
-        pl.sweep = Ce > 64;
         const size_t nP = align_up((size_t)B * Ce * WP * WP * 4),
                      nq = align_up((size_t)B * Ce * WP * 4);
         size_t off = 0;
         pl.P = off; off += nP;
         pl.q = off; off += nq;
         pl.xe = off; off += nq;
-        for (int i = 0; i < 2; ++i) {
-            pl.A[i] = off; off += pl.sweep ? nP : 0;
-            pl.r[i] = off; off += pl.sweep ? nq : 0;
-        }
+        pl.space = off; off += Ce > 1 ? nP / 2 : 0;
         // (one chunk needs no space)
         if (off <= lo.r[0]) return pl;
     }
@@ -628,22 +669,19 @@ hipError_t panel_solve(bool bwd, PanelArgs a, const PanelPlan& pl, void* ws_base
             const BlockSrc P{a.P, nv * WP, (long long)WP * WP, 0};
             const VecSrc q{a.q, nv, WP};
             const VecDst x{xe, nv, WP};
-            if (pl.sweep) {
-                float* A[2] = {(float*)(base + pl.A[0]), (float*)(base + pl.A[1])};
-                float* r[2] = {(float*)(base + pl.r[0]), (float*)(base + pl.r[1])};
-                e = pcr_sweep(P, q, x, a.B, Ce, WP, A, r, 0, 0, st);
-            } else {
-                e = timed(DEEPPCR_KCLASS_PCR_TAIL, 4.0 * a.B * Ce * ((double)WP * WP + 2.0 * WP),
-                          2.0 * a.B * Ce * (double)WP * WP, st, [&] {
-                    return launch_pcr_chain_subst(P, q, x, a.B, Ce, WP, 1, st);
-                });
-            }
+            e = block_solve(P, q, x, a.B, Ce, WP, (float*)(base + pl.space), st, nullptr);
             if (e != hipSuccess) return e;
         }
     }
     a.xe = xe;
     return timed(DEEPPCR_KCLASS_PCR_TAIL, 4.0 * (a.L * w2 + 4.0 * n), 2.0 * a.B * a.L * w2, st,
                  [&] { return launch_apply_pass(bwd, a, st); });
+}
+
+// MLP layers of widths up to 16 whose blocks the chunked solve forms from the
+// weights as it goes.
+bool layer_blocks(int B, int L, int w) {
+    return w > 8 && w <= 16 && (double)B * L * w < (double)(1 << 30);
 }
 
 // Argument checks shared by the two forward entry points.
@@ -721,8 +759,9 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
     const long long n = (long long)B * L * w;
     const VecDst xd{ws.r[(num_passes(B, L, w) + 1) & 1], (long long)L * w, (long long)w};
     const PanelPlan pl = panel_plan(B, L, w, false);
+    const bool layers16 = layer_blocks(B, L, w);
     const bool wide_sub = wide_width(w) && wide_substitution(B, L, w);
-    const bool fused = layer_first_level(w);
+    const bool fused = false;
     const NewtonArgs na{W, bias, z0, Z, ws.red, layer, alpha};
     unsigned* fslots = ws.red + kRedF;
     if (rule.residual) {
@@ -736,10 +775,10 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
         // Layers, Jacobian blocks (forward order) and residuals at the iterate:
         // fused into the first PCR level, or evaluated into ws A[1], r[1].
         hipError_t e;
-        if (pl.C > 0) {
+        if (pl.C > 0 || layers16) {
             e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 4.0 * n), 2.0 * B * L * w2, st, [&] {
-                return launch_layer_vectors(false, W, bias, z0, Z, ws.r[1], ws.r[0], ws.red, B, L,
-                                            w, layer, alpha, st);
+                return launch_layer_vectors(false, W, bias, z0, Z, ws.r[1], ws.r[0], ws.red,
+                                            rule.residual, B, L, w, layer, alpha, st);
             });
         } else if (wide_sub) {
             e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 4.0 * n), 2.0 * B * L * w2, st, [&] {
@@ -784,6 +823,11 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
             pa.residual = layer_residual(layer);
             e = panel_solve(false, pa, pl, workspace, st);
             if (e != hipSuccess) return hip_fail(e, "chunked solve");
+        } else if (layers16) {
+            const LayerScale y{ws.r[1], (long long)L * w, w, layer_residual(layer)};
+            e = block_solve(BlockSrc{W, 0, (long long)w * w, 0}, VecSrc{ws.r[0], (long long)L * w, w},
+                            VecDst{Z, (long long)L * w, w}, B, L, w, ws.A[0], st, ws.red, &y);
+            if (e != hipSuccess) return hip_fail(e, "block_solve");
         } else if (wide_sub) {
             for (int l = 1; l < L && e == hipSuccess; ++l)
                 e = timed(DEEPPCR_KCLASS_PCR_TAIL, 4.0 * (w2 + 3.0 * B * w), 2.0 * B * w2, st, [&] {
@@ -797,6 +841,12 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
         } else if (fused) {
             e = fused_rest_levels(na, B, L, w, ws, xd, st);
             if (e != hipSuccess) return hip_fail(e, "newton levels");
+        } else if (by_chunks(B, L, w)) {
+            e = block_solve(BlockSrc{ws.A[1], (long long)L * w * w, (long long)w * w, 0},
+                            VecSrc{ws.r[1], (long long)L * w, (long long)w},
+                            VecDst{Z, (long long)L * w, (long long)w}, B, L, w, ws.A[0], st,
+                            ws.red);
+            if (e != hipSuccess) return hip_fail(e, "block_solve");
         } else {
             e = pcr_sweep(BlockSrc{ws.A[1], (long long)L * w * w, (long long)w * w, 0},
                           VecSrc{ws.r[1], (long long)L * w, (long long)w}, xd, B, L, w, ws.A,
@@ -1107,7 +1157,7 @@ int deeppcr_newton_step(const float* J, const float* F, float* Z, int B, int L, 
     // ends in one, else by the update kernel
     const BlockSrc J0{J, (long long)L * w * w, (long long)w * w, 0};
     const VecSrc r0{ws.r[1], (long long)L * w, (long long)w};
-    if (tail_levels(B, L, w, 0) > 0) {
+    if (by_chunks(B, L, w)) {
         e = pcr_sweep(J0, r0, VecDst{Z, (long long)L * w, (long long)w}, B, L, w, ws.A, ws.r, 0,
                       0, st, nullptr, ws.red);
         if (e != hipSuccess) return hip_fail(e, "pcr_sweep");
@@ -1201,8 +1251,8 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
     if (pl.C > 0) {
         hipError_t e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 2.0 * B * L * w),
                              2.0 * B * L * w2, st, [&] {
-            return launch_layer_vectors(true, W, bias, z0, Z, ws.dscale, nullptr, nullptr, B, L, w,
-                                        layer, alpha, st);
+            return launch_layer_vectors(true, W, bias, z0, Z, ws.dscale, nullptr, nullptr, false,
+                                        B, L, w, layer, alpha, st);
         });
         if (e != hipSuccess) return hip_fail(e, "layer_vectors");
         PanelArgs pa{};
@@ -1217,6 +1267,29 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
         pa.residual = layer_residual(layer);
         e = panel_solve(true, pa, pl, workspace, st);
         if (e != hipSuccess) return hip_fail(e, "chunked solve");
+        e = timed(DEEPPCR_KCLASS_WGRAD, 4.0 * (3.0 * B * L * w + L * (w2 + w)), 2.0 * B * L * w2,
+                  st, [&] { return launch_wgrad(z0, Z, ws.dscale, Lambda, dW, db, B, L, w, st); });
+        if (e != hipSuccess) return hip_fail(e, "wgrad");
+        return DEEPPCR_OK;
+    }
+    if (layer_blocks(B, L, w)) {
+        hipError_t e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 2.0 * B * L * w),
+                             2.0 * B * L * w2, st, [&] {
+            return launch_layer_vectors(true, W, bias, z0, Z, ws.dscale, nullptr, nullptr, false,
+                                        B, L, w, layer, alpha, st);
+        });
+        if (e != hipSuccess) return hip_fail(e, "layer_vectors");
+        // row m of the transposed system: W_{L-m}^T, d_{L-m}; G at row 0
+        const long long ld = (long long)L * w, wl = w;
+        const LayerScale y{ws.dscale + ld, ld, -wl, layer_residual(layer)};
+        e = block_solve(BlockSrc{W + (long long)L * w * w, 0, -(long long)w * w, 1},
+                        VecSrc{G, wl, 0}, VecDst{Lambda + ld - w, ld, -wl}, B, L, w, ws.A[0], st,
+                        nullptr, &y);
+        if (e != hipSuccess) return hip_fail(e, "block_solve");
+        e = timed(DEEPPCR_KCLASS_OTHER, 4.0 * (w2 + 3.0 * B * w), 2.0 * B * w2, st, [&] {
+            return launch_dz0(W, ws.dscale, Lambda, dz0, B, L, w, layer, st);
+        });
+        if (e != hipSuccess) return hip_fail(e, "dz0");
         e = timed(DEEPPCR_KCLASS_WGRAD, 4.0 * (3.0 * B * L * w + L * (w2 + w)), 2.0 * B * L * w2,
                   st, [&] { return launch_wgrad(z0, Z, ws.dscale, Lambda, dW, db, B, L, w, st); });
         if (e != hipSuccess) return hip_fail(e, "wgrad");
@@ -1244,7 +1317,7 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
         if (e != hipSuccess) return hip_fail(e, "wgrad");
         return DEEPPCR_OK;
     }
-    const bool from_weights = first_level_count(B, L, w) == 2;
+    const bool from_weights = false;
     const BwdArgs bw{W, ws.dscale, layer_residual(layer) ? 1 : 0};
     const double jbytes = from_weights ? 0.0 : 4.0 * B * L * w2;
     hipError_t e = timed(DEEPPCR_KCLASS_LAYER, jbytes + 4.0 * B * L * 3.0 * w,
@@ -1324,7 +1397,7 @@ int deeppcr_resnet_forward(const float* W, const float* bias, const float* z0, f
     const double eval_bytes = 4.0 * ((double)L * w2 + (double)B * G * (w2 + 3.0 * w));
     const double eval_flops = (double)B * G * ((skip - 1) * 2.0 * w2 * w + skip * 2.0 * w2);
     int status = tol > 0.f ? DEEPPCR_ENOCONV : DEEPPCR_OK;
-    const bool upd_in_tail = tail_levels(B, G, w, 0) > 0;
+    const bool upd_in_tail = by_chunks(B, G, w);
     for (int k = 1; k <= max_iter; ++k) {
         hipError_t e = timed(DEEPPCR_KCLASS_LAYER, eval_bytes, eval_flops, st, [&] {
             return launch_resnet_block_eval(W, bias, z0, X, ws.A[1], ws.r[1], ws.red, B, G, w,
@@ -1411,7 +1484,9 @@ int deeppcr_resnet_backward(const float* W, const float* z0, const float* Z, con
                          });
     if (e != hipSuccess) return hip_fail(e, "resnet_block_jac");
     // block-output adjoints mu (natural order) from the transposed solve
-    float* mu = ws.r[(num_passes(B, G, w) + 1) & 1];
+    // (not the right-hand side's buffer: the solution's rows are written in the
+    // opposite order; the PCR levels end in either)
+    float* mu = ws.r[by_chunks(B, G, w) ? 0 : (num_passes(B, G, w) + 1) & 1];
     const VecDst xd{mu + (long long)(G - 1) * w, (long long)G * w, -(long long)w};
     e = pcr_sweep(BlockSrc{ws.A[1], (long long)G * w * w, (long long)w * w, 1},
                   VecSrc{ws.r[1], (long long)G * w, (long long)w}, xd, B, G, w, ws.A, ws.r, 0, 0,

@@ -261,6 +261,33 @@ hipError_t launch_eval_small(bool bwd, const float* W, const float* bias, const 
                              unsigned* red, int B, int L, int w, int layer, float alpha,
                              hipStream_t stream);
 
+// -------------------------------------------- solve on stored blocks, chunks
+// How a solve (widths up to kMaxWidth) is cut, with its estimated time in us:
+// chunks of m rows (0: substitution of all rows); walk: block_down finds every
+// chunk's x_in itself from the chunk ends' P and q.
+struct BlockPlan {
+    int m;
+    bool walk;
+};
+double block_plan(int B, int L, int w, BlockPlan* plan);
+// The maps x_end = P x_in + q of chunks 0 .. C-2 of Lc rows (P [B, C-1, w, w],
+// chunk 0 not written; q [B, C-1, w]).
+// With y (w <= 16) A holds layer weights, not blocks: J = diag(d) W (+ I),
+// d = y.d + b bstride + m rstride at row m; transposed, r is read at row 0 only.
+struct LayerScale {
+    const float* d;
+    long long bstride, rstride;
+    int residual;
+};
+hipError_t launch_block_up(const BlockSrc& A, const LayerScale* y, const VecSrc& r, float* P,
+                           float* q, int B, int L, int w, int Lc, int C, hipStream_t st);
+// The substitution inside every chunk, from xe [B, C-1, w], the solution at
+// the chunk ends (P null), or from P and xe = q (unused for C = 1).  With red
+// the solution is added to x (the Newton iterate), its maxima reduced into red.
+hipError_t launch_block_down(const BlockSrc& A, const LayerScale* y, const VecSrc& r,
+                             const VecDst& x, const float* xe, const float* P, unsigned* red,
+                             int B, int L, int w, int Lc, int C, hipStream_t st);
+
 // ------------------------------------------------------- chunked MLP solve
 // The Newton solve (rows l = 0 .. L-1, operator of row l from layer l) and
 // the transposed solve (rows m = 0 .. L, operator of row m from layer L - m,
@@ -284,11 +311,12 @@ struct PanelArgs {
 };
 bool panel_width(int w);
 int panel_pad(int w);
-int panel_chunks(int B, int rows, int w);  // 0: leave the shape to the PCR levels
-// d (and, forward, r with its maximum; clears the max|dZ|, max|Z| slots).
+int panel_chunks(int B, int rows, int w);
+// d (and, forward, r and, if want_max, its maximum; clears the max|dZ|, max|Z|
+// slots of red).
 hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, const float* z0,
-                                const float* Z, float* d, float* r, unsigned* red, int B, int L,
-                                int w, int layer, float alpha, hipStream_t st);
+                                const float* Z, float* d, float* r, unsigned* red, bool want_max,
+                                int B, int L, int w, int layer, float alpha, hipStream_t st);
 // P of chunks 1 .. C-2 and q of chunks 0 .. C-2 (C >= 2).
 hipError_t launch_chunk_pass(bool bwd, const PanelArgs& a, hipStream_t st);
 // Every row from its chunk's x_in (xe of the chunk before; 0 in the first).

@@ -23,6 +23,7 @@
 // each per 32 x 32 x 16 tile against 8 x 64 cycles of float32 instructions:
 // 2.7 times the rate, with fewer roundings (one per 16 terms and part).
 #include "internal.h"
+#include "rows.h"
 
 namespace deeppcr {
 namespace {
@@ -30,7 +31,6 @@ namespace {
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef __bf16 b2 __attribute__((ext_vector_type(2)));
 typedef float f2 __attribute__((ext_vector_type(2)));
-typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef unsigned u2 __attribute__((ext_vector_type(2)));
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
@@ -97,57 +97,6 @@ __device__ __forceinline__ void mac(Acc<f4>& c, const Parts8& a, const Parts8& b
     c.s = mfma16(a.h, b.l, c.s);
     c.s = mfma16(a.m, b.h, c.s);
     c.s = mfma16(a.h, b.m, c.s);
-}
-
-// Rows of w floats read four at a time.  EXACT (w = the padded width): plain
-// 16-byte loads.  Otherwise rows start on any 4-byte boundary: buffer loads,
-// which the hardware bounds-checks per element against the tensor's (for
-// weights the layer's) end and fills with zeros beyond it.
-template <bool EXACT>
-struct Src {
-    const float* p;
-    __device__ __forceinline__ Src(const float* q, unsigned) : p(q) {}
-    __device__ __forceinline__ f4 at(unsigned off) const {
-        return *reinterpret_cast<const f4*>(p + off);
-    }
-    __device__ __forceinline__ float one(unsigned off) const { return p[off]; }
-};
-template <>
-struct Src<false> {
-    __amdgpu_buffer_rsrc_t r;
-    __device__ __forceinline__ Src(const float* q, unsigned floats)
-        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(q), 0, floats * 4u, 0x00027000)) {}
-    __device__ __forceinline__ f4 at(unsigned off) const {
-        return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, off * 4u, 0, 0));
-    }
-    __device__ __forceinline__ float one(unsigned off) const {
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off * 4u, 0, 0));
-    }
-};
-
-// Elements i .. i + N - 1 of the row of w starting at float `row` of src;
-// zeros beyond the row's end.
-template <int N, bool EXACT>
-__device__ __forceinline__ void load_row(const Src<EXACT>& src, unsigned row, int i, int w,
-                                         float (&v)[N]) {
-#pragma unroll
-    for (int q = 0; q < N; q += 4) {
-        const f4 x = src.at(row + i + q);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[q + e] = EXACT || i + q + e < w ? x[e] : 0.f;
-    }
-}
-template <int N, bool EXACT>
-__device__ __forceinline__ void store_row(float* p, int i, int w, const float (&v)[N]) {
-    if constexpr (EXACT) {
-#pragma unroll
-        for (int q = 0; q < N; q += 4)
-            *reinterpret_cast<f4*>(p + i + q) = f4{v[q], v[q + 1], v[q + 2], v[q + 3]};
-    } else {
-#pragma unroll
-        for (int q = 0; q < N; ++q)
-            if (i + q < w) p[i + q] = v[q];
-    }
 }
 
 // ------------------------------------------------------------ shapes
@@ -618,15 +567,19 @@ __global__ __launch_bounds__(kThr) void apply_pass(PanelArgs a) {
 }
 
 // ------------------------------------------------------------ layer vectors
-// d = c sigma'(a) and, forward, r = f(Z_{l-1}) - Z_l with its maximum, for
-// a = W_l Z_{l-1} + b_l: one layer per workgroup (a part of the batch where
-// there are few layers), the split weights in registers for all systems.
-// Bound by one read of W and of the states and the write of d and r.
+// d = c sigma'(a) and, forward, r = f(Z_{l-1}) - Z_l with its maximum (where
+// red is given), for a = W_l Z_{l-1} + b_l.  Items (layer, 16 systems), a
+// contiguous range of them per group of waves, which keeps a layer's split
+// weights in registers for all its systems.  Bound by one read of W and of the
+// states and the write of d and r.  One atomic per workgroup, at most 2048 of
+// them (L = 8192, w = 32, B = 1: 42 us with one per wave and a workgroup per
+// layer).
 template <int WP, bool BWD, bool EXACT>
 __global__ __launch_bounds__(kThr) void layer_vectors(
     const float* __restrict__ W, const float* __restrict__ bias, const float* __restrict__ z0,
     const float* __restrict__ Z, float* __restrict__ d_out, float* __restrict__ r_out,
-    unsigned* __restrict__ red, int B, int L, int w_, int layer, float alpha, int parts) {
+    unsigned* __restrict__ clear, unsigned* __restrict__ red, int B, int L, int w_, int layer,
+    float alpha, int per) {
     using S = VecShape<WP>;
     constexpr int NR = S::NR;
     const int t = threadIdx.x, v = t >> 6, lane = t & 63;
@@ -634,42 +587,52 @@ __global__ __launch_bounds__(kThr) void layer_vectors(
     const int n = lane & 15, g = lane >> 4;
     const int w = EXACT ? WP : w_;
     const int base = wv * 16 * S::MTW, r0 = base + NR * g;
-    const int l = blockIdx.x / parts, part = blockIdx.x % parts;
     if constexpr (!BWD)
         if (blockIdx.x == 0)
-            for (int k = t; k < 2 * kRedShards; k += kThr) red[k] = 0u;
-    const float* Wl = W + (long long)l * w * w;
-    Parts8 A[S::MTW][S::KT];
-    {
-        float raw[S::MTW][S::KT][8];
-        load_strip<WP, false, EXACT>(Src<EXACT>(Wl, w * w), w, base, n, g, raw);
-#pragma unroll
-        for (int q = 0; q < S::MTW; ++q)
-#pragma unroll
-            for (int k = 0; k < S::KT; ++k) A[q][k] = split8(raw[q][k]);
-    }
-    float bi[NR];
-    load_row<NR>(Src<EXACT>(bias + (long long)l * w, w), 0, r0, w, bi);
-    const bool res = layer_residual(layer);
-    unsigned mr = 0u;
+            for (int k = t; k < 2 * kRedShards; k += kThr) clear[k] = 0u;
     const int ng = (B + 15) / 16;
     const unsigned nv = (unsigned)B * L * w;
-    const Src<EXACT> sz(Z, nv), sp(l == 0 ? z0 : Z, l == 0 ? (unsigned)B * w : nv);
-    for (int gr = part * S::GPW + sub; gr < ng; gr += parts * S::GPW) {
+    const Src<EXACT> sz(Z, nv), s0(z0, (unsigned)B * w);
+    const bool res = layer_residual(layer);
+    const int it0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * S::GPW + sub) * per);
+    const int it1 = min(it0 + per, L * ng);
+    Parts8 A[S::MTW][S::KT];
+    float bi[NR];
+    int have = -1;
+    unsigned mr = 0u;
+    for (int it = it0; it < it1; ++it) {
+        const int l = it / ng, gr = it - l * ng;
+        const float* Wl = W + (long long)l * w * w;
+        if (l != have) {
+            float raw[S::MTW][S::KT][8];
+            load_strip<WP, false, EXACT>(Src<EXACT>(Wl, w * w), w, base, n, g, raw);
+            load_row<NR>(Src<EXACT>(bias + (long long)l * w, w), 0, r0, w, bi);
+#pragma unroll
+            for (int q = 0; q < S::MTW; ++q)
+#pragma unroll
+                for (int k = 0; k < S::KT; ++k) A[q][k] = split8(raw[q][k]);
+            have = l;
+        }
         const int bb = gr * 16 + n;
         const bool live = bb < B;
         const int b = live ? bb : B - 1;
         const unsigned op = l == 0 ? b * w : ((unsigned)b * L + l - 1) * w;
         const unsigned o = ((unsigned)b * L + l) * w;
-        float zl[NR], zr[NR];
+        float zl[NR], zr[NR], x[S::KT][8];
+        if (l == 0) {
+#pragma unroll
+            for (int k = 0; k < S::KT; ++k) load_row<8>(s0, op, 32 * k + 8 * g, w, x[k]);
+            if (!BWD && res) load_row<NR>(s0, op, r0, w, zr);
+        } else {
+#pragma unroll
+            for (int k = 0; k < S::KT; ++k) load_row<8>(sz, op, 32 * k + 8 * g, w, x[k]);
+            if (!BWD && res) load_row<NR>(sz, op, r0, w, zr);
+        }
         if constexpr (!BWD) load_row<NR>(sz, o, r0, w, zl);
-        if (!BWD && res) load_row<NR>(sp, op, r0, w, zr);
         Acc<f4> acc[S::MTW] = {};
 #pragma unroll
         for (int k = 0; k < S::KT; ++k) {
-            float x[8];
-            load_row<8>(sp, op, 32 * k + 8 * g, w, x);
-            const Parts8 p = split8(x);
+            const Parts8 p = split8(x[k]);
 #pragma unroll
             for (int q = 0; q < S::MTW; ++q) mac(acc[q], A[q][k], p);
         }
@@ -683,10 +646,11 @@ __global__ __launch_bounds__(kThr) void layer_vectors(
                 // an infinity has no split, and a value that rounds up to one
                 // none either: such a row is summed as it stands
                 if (__builtin_expect(!(fabsf(y) <= 3.0e38f), 0)) {
+                    const float* zp = l == 0 ? z0 : Z;
                     y = bi[j];
                     if (EXACT || r0 + j < w)
                         for (int k = 0; k < w; ++k)
-                            y = fmaf(Wl[(long long)(r0 + j) * w + k], sp.one(op + k), y);
+                            y = fmaf(Wl[(long long)(r0 + j) * w + k], zp[(long long)op + k], y);
                 }
                 float dd;
                 const float f = activate(layer, y, &dd);
@@ -703,8 +667,15 @@ __global__ __launch_bounds__(kThr) void layer_vectors(
         }
     }
     if constexpr (!BWD) {
+        if (!red) return;
+        __shared__ unsigned part[4];
         for (int off = 32; off > 0; off >>= 1) mr = max(mr, (unsigned)__shfl_xor((int)mr, off, 64));
-        if (lane == 0) atomicMax(red + kRedF + (int)((blockIdx.x * 4 + v) % kRedShards), mr);
+        if (lane == 0) part[v] = mr;
+        __syncthreads();
+        if (t == 0) {
+            for (int i = 1; i < 4; ++i) mr = max(mr, part[i]);
+            atomicMax(red + kRedF + (int)(blockIdx.x % kRedShards), mr);
+        }
     }
 }
 
@@ -735,44 +706,59 @@ int product_groups(int B, int WP) {
 
 }  // namespace
 
-// (w = 16 has PCR kernels of its own, 0.7-1.2 times as fast over B and L)
-bool panel_width(int w) { return w > 8 && w <= kMaxWidth && w != 16; }
+bool panel_width(int w) { return w > 16 && w <= kMaxWidth; }
 int panel_pad(int w) { return padded(w); }
 
-// Chunks of a solve.  The products run in parallel over chunks and cost the
-// same in total, so there are as many chunks as keep one round of workgroups
-// on the chip (two per CU at a padded width of 128, three below; at 32, whose
-// rows are short, one and a half rounds were faster: 600 us against 680 per
-// mlp_fwd call), unless the substitution over the chunk ends, one row after
-// the other, would then cost more than the rows of a chunk: C^2 = 4 rows.
+// Chunks of a solve, by the estimated time of its parts: a row of the
+// products and of the apply pass, measured on one MI355X, one round of
+// workgroups (two per CU at a padded width of 128, three below) or more, and
+// the solve over the chunk ends.
 int panel_chunks(int B, int rows, int w) {
-    const int WP = padded(w);
-    const int slots = 256 * (WP == 128 ? 4 : WP == 64 ? 6 : 9) / 2;
-    int C = 1 + slots / (product_groups(B, WP) + vector_groups(B, WP));
-    int root = 1;
-    while ((long long)root * root < 4LL * rows) ++root;
-    // a long chain of few systems: the PCR levels have the parallelism
-    if (w == WP && root > 100 && C > root) return 0;
-    if (C > root) C = root;
-    if (C > rows) C = rows;
-    return C;
+    const int WP = padded(w), k = WP == 32 ? 0 : WP == 64 ? 1 : 2;
+    static const double prod[] = {1.0, 2.0, 7.0}, apply[] = {0.55, 0.75, 2.6};
+    // a full round of products takes longer than a lone workgroup
+    static const double full[] = {1.6, 4.0, 12.5};
+    const double slots = 256.0 * (WP == 128 ? 2 : 3);
+    const int pg = product_groups(B, WP), vg = vector_groups(B, WP);
+    int best = 1;
+    double t_best = 4.5 + rows * apply[k];
+    for (int j = 3; j <= 40; ++j) {
+        // C = 2, 3, 4, 5, 6, 8, 10, 12, ...: quarter powers of two
+        const int C = ((4 + j % 4) << (j / 4)) >> 2;
+        if (C < 2 || C > rows) continue;
+        const int Lc = (rows + C - 1) / C;
+        const double wgs = (double)pg * (C - 2) + (double)vg * (C - 1);
+        double row = prod[k];
+        if (wgs > 256) row += (full[k] - prod[k]) * (wgs > slots ? 1.0 : (wgs - 256) / (slots - 256));
+        if (wgs > slots) row *= wgs > 4 * slots ? wgs / slots : (double)(int)(wgs / slots + 0.999);
+        if (C == 2) row = 1.2 * apply[k];
+        const double va = (double)vg * C > 1024 ? vg * C / 1024.0 : 1.0;
+        double t = 9.0 + Lc * (row + apply[k] * va);
+        if (t < t_best && C > 2) t += block_plan(B, C - 1, WP, nullptr);
+        if (t < t_best) {
+            t_best = t;
+            best = C;
+        }
+    }
+    return best;
 }
 
 hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, const float* z0,
-                                const float* Z, float* d, float* r, unsigned* red, int B, int L,
-                                int w, int layer, float alpha, hipStream_t st) {
-    // enough workgroups for the chip, one part of the batch each
-    const int WP = padded(w), groups = vector_groups(B, WP);
-    int parts = 2048 / L;
-    if (parts > groups) parts = groups;
-    if (parts < 1) parts = 1;
+                                const float* Z, float* d, float* r, unsigned* red, bool want_max,
+                                int B, int L, int w, int layer, float alpha, hipStream_t st) {
+    // one item per group of waves, or up to 2048 workgroups
+    const int WP = padded(w), groups = WP == 32 ? 2 : 1;
+    const int items = L * ((B + 15) / 16);
+    const int per = (items + 2048 * groups - 1) / (2048 * groups);
+    const int grid = (items + per * groups - 1) / (per * groups);
+    unsigned* const mx = want_max ? red : nullptr;
     const int a_w = w;
     if (bwd)
-        DEEPPCR_PANEL(layer_vectors, true, (long long)L * parts, W, bias, z0, Z, d, r, red, B, L, w,
-                      layer, alpha, parts);
+        DEEPPCR_PANEL(layer_vectors, true, grid, W, bias, z0, Z, d, r, red, mx, B, L, w, layer,
+                      alpha, per);
     else
-        DEEPPCR_PANEL(layer_vectors, false, (long long)L * parts, W, bias, z0, Z, d, r, red, B, L,
-                      w, layer, alpha, parts);
+        DEEPPCR_PANEL(layer_vectors, false, grid, W, bias, z0, Z, d, r, red, mx, B, L, w, layer,
+                      alpha, per);
     return hipGetLastError();
 }
 

@@ -1,0 +1,92 @@
+"""GPU parity of the chunked solve on stored blocks (widths 1 to 128) at the
+shapes where it is cut differently: one substitution, chunks whose ends are
+walked or solved on their own, a short last chunk, more chunks than one
+workgroup's; widths on both sides of the padded ones; both orientations; x
+aliasing r; NaN in the first block, which must not enter.  Against forward and
+back substitution in float64.
+
+Tolerance: a row's dot product of w terms is within w 2^-24 of its terms'
+norm whatever its order, and in these systems (|J| about 0.9) a perturbation
+of one row fades within about ten; relative to the largest entry."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2309_16318_amd import deeppcr, synth
+from tests._util import normwise_rel_err
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = [(1, 3, 100), (2, 2, 700), (3, 5, 33), (5, 1, 4097), (8, 1, 300), (9, 7, 65), (15, 2, 130),
+          (16, 1, 1), (16, 1, 9), (16, 3, 513), (17, 2, 70), (24, 33, 64), (32, 1, 2), (32, 3, 129),
+          (33, 2, 65), (48, 3, 200), (64, 1, 17), (64, 5, 257), (65, 1, 40), (100, 2, 90),
+          (127, 1, 33), (128, 1, 13), (128, 2, 100)]
+
+
+@pytest.fixture(scope="module")
+def dev():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return torch.device("cuda:0")
+
+
+@pytest.mark.parametrize("w,B,L", SHAPES)
+@pytest.mark.parametrize("transpose", [0, 1])
+def test_solve(dev, w, B, L, transpose):
+    print(f"blocks w={w} B={B} L={L} transpose={transpose}", flush=True)
+    d = synth.random_system(B, L, w, seed=900 + w + B + L, scale=0.9)
+    ref = oracle.seq_solve(d["J"], d["r"], bool(transpose))
+    J = d["J"].copy()
+    J[:, 0] = np.nan
+    x = torch.from_numpy(d["r"]).to(dev)
+    deeppcr.pcr_solve_block_bidiag(torch.from_numpy(J).to(dev), x, x=x, transpose=transpose)
+    torch.cuda.synchronize()
+    err = normwise_rel_err(x.cpu().numpy(), ref)
+    print(f"  err {err:.1e}", flush=True)
+    assert err <= 10 * max(w, 4) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("w,B,L", SHAPES)
+def test_newton_step(dev, w, B, L):
+    """The substitution also adds the solution to the iterate and reduces the
+    three measures."""
+    print(f"blocks step w={w} B={B} L={L}", flush=True)
+    d = synth.random_system(B, L, w, seed=700 + w + B + L, scale=0.9)
+    rng = np.random.default_rng(1)
+    Z = rng.standard_normal((B, L, w)).astype(np.float32)
+    F = Z + d["r"]
+    r = (F - Z).astype(np.float64)
+    dz = oracle.seq_solve(d["J"], r.astype(np.float32), False)
+    Zt = torch.from_numpy(Z.copy()).to(dev)
+    res = deeppcr.deeppcr_newton_step(torch.from_numpy(d["J"]).to(dev),
+                                      torch.from_numpy(F).to(dev), Zt)
+    tol = 10 * max(w, 4) * 2.0 ** -24
+    got = Zt.cpu().numpy()
+    assert normwise_rel_err(got, Z + dz) <= tol
+    for a, b in ((res.residual, np.max(np.abs(r))), (res.max_update, np.max(np.abs(dz))),
+                 (res.max_abs, np.max(np.abs(Z + dz)))):
+        assert abs(a - b) <= tol * max(1.0, abs(b))
+
+
+@pytest.mark.parametrize("w,B,L", [(9, 3, 70), (12, 17, 40), (16, 5, 33), (16, 1, 300), (16, 64, 100)])
+@pytest.mark.parametrize("layer,alpha", [(0, 1.0), (3, 0.1)])
+def test_layer_blocks(dev, w, B, L, layer, alpha):
+    """Widths 9 to 16: the blocks of MLP layers formed from the weights."""
+    print(f"layer blocks w={w} B={B} L={L} layer={layer}", flush=True)
+    d = synth.mlp_inputs(B, L, w, seed=w + B + L)
+    t = {k: torch.from_numpy(v).to(dev) for k, v in d.items()}
+    ref = oracle.seq_forward(layer, alpha, d["W"], d["bias"], d["z0"])
+    res = deeppcr.deeppcr_mlp_forward(t["W"], t["bias"], t["z0"], layer=layer, alpha=alpha)
+    assert res.status == deeppcr.OK
+    tol = 40 * w * 2.0 ** -24 * (1 + alpha * L / 8 if layer == 3 else 1)
+    assert normwise_rel_err(res.Z.cpu().numpy(), ref) <= tol
+    Z32 = ref.astype(np.float32)
+    lam, dz0, dW, db = deeppcr.deeppcr_mlp_backward(t["W"], t["bias"], t["z0"],
+                                                    torch.from_numpy(Z32).to(dev), t["G"],
+                                                    layer=layer, alpha=alpha)
+    rl, rz, rW, rb = oracle.seq_backward(layer, alpha, d["W"], d["bias"], d["z0"], Z32, d["G"])
+    got = np.concatenate([dz0.cpu().numpy()[:, None], lam.cpu().numpy()], 1)
+    assert normwise_rel_err(got, np.concatenate([rz[:, None], rl], 1)) <= tol
+    assert normwise_rel_err(dW.cpu().numpy(), rW, axes="all") <= tol
+    assert normwise_rel_err(db.cpu().numpy(), rb, axes="all") <= tol
