@@ -295,13 +295,12 @@ void tail_work(int B, int L, int w, int kt, double* bytes, double* flops) {
 // Stride of the rows the last kt levels start from.
 int tail_stride(int L, int kt) { return 1 << (num_levels(L) - kt); }
 
-// Whether a solve on stored blocks goes by chunks (blocks.hip): widths up to
-// kMaxWidth, but not many rows of the smallest blocks, which fill a sixteenth
-// or less of a padded one (w = 2, B = 64, L = 1024: PCR levels 38 us, chunks
-// 44; B = 1, L = 4096 the other way round, 52 and 42).
-bool by_chunks(int B, int L, int w) {
-    return w <= kMaxWidth && !(w <= 3 && (double)B * L >= 16384);
-}
+// Whether a solve on stored blocks goes by chunks (blocks.hip): widths 4 to
+// kMaxWidth.  Smaller blocks fill a sixteenth or less of a padded one, so
+// many rows are faster by PCR levels (w = 2, B = 64, L = 1024: 38 us against
+// 44) and few gain little, and the levels' error is the smaller (long chains
+// of 2 x 2 blocks: 1.2 times).
+bool by_chunks(int w) { return w >= 4 && w <= kMaxWidth; }
 
 // The solve on stored blocks, widths up to kMaxWidth, by chunks (blocks.hip).
 // `space`: B L w^2 floats at least.  With upd_red the solution is added to x
@@ -348,7 +347,7 @@ hipError_t block_solve(const BlockSrc& A, const VecSrc& r, const VecDst& x, int 
 hipError_t pcr_sweep(const BlockSrc& A0, const VecSrc& r0, const VecDst& x, int B, int L, int w,
                      float* wsA[2], float* wsr[2], int a_first, int r_first, hipStream_t st,
                      const BwdArgs* bwd = nullptr, unsigned* upd_red = nullptr) {
-    if (by_chunks(B, L, w) && !bwd) return block_solve(A0, r0, x, B, L, w, wsA[0], st, upd_red);
+    if (by_chunks(w) && !bwd) return block_solve(A0, r0, x, B, L, w, wsA[0], st, upd_red);
     const int K = num_levels(L);
     if (K == 0) {
         const double bytes = 8.0 * B * L * w;
@@ -841,7 +840,7 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
         } else if (fused) {
             e = fused_rest_levels(na, B, L, w, ws, xd, st);
             if (e != hipSuccess) return hip_fail(e, "newton levels");
-        } else if (by_chunks(B, L, w)) {
+        } else if (by_chunks(w)) {
             e = block_solve(BlockSrc{ws.A[1], (long long)L * w * w, (long long)w * w, 0},
                             VecSrc{ws.r[1], (long long)L * w, (long long)w},
                             VecDst{Z, (long long)L * w, (long long)w}, B, L, w, ws.A[0], st,
@@ -1157,7 +1156,7 @@ int deeppcr_newton_step(const float* J, const float* F, float* Z, int B, int L, 
     // ends in one, else by the update kernel
     const BlockSrc J0{J, (long long)L * w * w, (long long)w * w, 0};
     const VecSrc r0{ws.r[1], (long long)L * w, (long long)w};
-    if (by_chunks(B, L, w)) {
+    if (by_chunks(w)) {
         e = pcr_sweep(J0, r0, VecDst{Z, (long long)L * w, (long long)w}, B, L, w, ws.A, ws.r, 0,
                       0, st, nullptr, ws.red);
         if (e != hipSuccess) return hip_fail(e, "pcr_sweep");
@@ -1397,7 +1396,7 @@ int deeppcr_resnet_forward(const float* W, const float* bias, const float* z0, f
     const double eval_bytes = 4.0 * ((double)L * w2 + (double)B * G * (w2 + 3.0 * w));
     const double eval_flops = (double)B * G * ((skip - 1) * 2.0 * w2 * w + skip * 2.0 * w2);
     int status = tol > 0.f ? DEEPPCR_ENOCONV : DEEPPCR_OK;
-    const bool upd_in_tail = by_chunks(B, G, w);
+    const bool upd_in_tail = by_chunks(w);
     for (int k = 1; k <= max_iter; ++k) {
         hipError_t e = timed(DEEPPCR_KCLASS_LAYER, eval_bytes, eval_flops, st, [&] {
             return launch_resnet_block_eval(W, bias, z0, X, ws.A[1], ws.r[1], ws.red, B, G, w,
@@ -1486,7 +1485,7 @@ int deeppcr_resnet_backward(const float* W, const float* z0, const float* Z, con
     // block-output adjoints mu (natural order) from the transposed solve
     // (not the right-hand side's buffer: the solution's rows are written in the
     // opposite order; the PCR levels end in either)
-    float* mu = ws.r[by_chunks(B, G, w) ? 0 : (num_passes(B, G, w) + 1) & 1];
+    float* mu = ws.r[by_chunks(w) ? 0 : (num_passes(B, G, w) + 1) & 1];
     const VecDst xd{mu + (long long)(G - 1) * w, (long long)G * w, -(long long)w};
     e = pcr_sweep(BlockSrc{ws.A[1], (long long)G * w * w, (long long)w * w, 1},
                   VecSrc{ws.r[1], (long long)G * w, (long long)w}, xd, B, G, w, ws.A, ws.r, 0, 0,

@@ -125,59 +125,72 @@ struct ProdShape {
 };
 
 // The rows of W_l (TRANS: of W_l^T) a lane multiplies with, for the vector
-// panels.  Where w is not the padded width, elements beyond a row's end hold
+// panels, in put_panel's k order.  Where w is not the padded width, elements beyond a row's end hold
 // the next row's weights: they meet zeros of the panel, or (TRANS) give rows
 // that the caller drops.
 template <int WP, bool TRANS, bool EXACT>
 __device__ __forceinline__ void load_strip(const Src<EXACT>& Wl, int w, int base, int idx, int g,
                                            float (&raw)[VecShape<WP>::MTW][VecShape<WP>::KT][8]) {
     using S = VecShape<WP>;
+    const int k0 = 16 * (g / 2) + 4 * (g % 2);  // and k0 + 8
     if constexpr (!TRANS) {
 #pragma unroll
         for (int t = 0; t < S::MTW; ++t) {
-            const unsigned row = (base + S::MTW * idx + t) * w + 8 * g;
+            const unsigned row = (base + S::MTW * idx + t) * w + k0;
 #pragma unroll
             for (int k = 0; k < S::KT; ++k)
 #pragma unroll
                 for (int q = 0; q < 8; q += 4) {
-                    const f4 x = Wl.at(row + 32 * k + q);
+                    const f4 x = Wl.at(row + 32 * k + 2 * q);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) raw[t][k][q + e] = x[e];
                 }
         }
     } else {
-        const unsigned col = base + S::MTW * idx + 8 * g * w;
+        const unsigned col = base + S::MTW * idx + k0 * w;
 #pragma unroll
         for (int k = 0; k < S::KT; ++k)
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
+                const int kk = 32 * k + j + (j & 4);
                 if constexpr (EXACT && S::MTW == 2) {
-                    const f2 x = *reinterpret_cast<const f2*>(Wl.p + col + (32 * k + j) * w);
+                    const f2 x = *reinterpret_cast<const f2*>(Wl.p + col + kk * w);
                     raw[0][k][j] = x[0];
                     raw[1][k][j] = x[1];
                 } else {
 #pragma unroll
-                    for (int t = 0; t < S::MTW; ++t)
-                        raw[t][k][j] = Wl.one(col + (32 * k + j) * w + t);
+                    for (int t = 0; t < S::MTW; ++t) raw[t][k][j] = Wl.one(col + kk * w + t);
                 }
             }
     }
 }
 
-// A lane's NR rows of a vector panel as operand parts in LDS.
+// Elements i .. i + 3 and i + 8 .. i + 11 of a row.
+template <bool EXACT>
+__device__ __forceinline__ void load_operand(const Src<EXACT>& src, unsigned row, int i, int w,
+                                             float (&v)[8]) {
+    float a[4], b[4];
+    load_row<4>(src, row, i, w, a);
+    load_row<4>(src, row, i + 8, w, b);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        v[e] = a[e];
+        v[4 + e] = b[e];
+    }
+}
+
+// A lane's NR rows of a vector panel as operand parts in LDS, for the k order
+// of the split weights: a lane (n, g) of k tile K multiplies rows 16 T + 4 h ..
+// + 3 and 16 T + 8 + 4 h .. + 3, T = 2 K + g / 2, h = g % 2.
 template <int WP>
 __device__ __forceinline__ void put_panel(char* buf, int r0, int n,
                                           const float (&x)[VecShape<WP>::NR]) {
     using S = VecShape<WP>;
-    const int kt = r0 / 32, lane = n + 16 * ((r0 % 32) / 8);
-    char* p = buf + kt * 1024 + lane * 16 + (r0 % 8) * 2;
-    if constexpr (S::NR == 8) {
-        const Parts8 q = split8(x);
-        *reinterpret_cast<b8*>(p) = q.h;
-        *reinterpret_cast<b8*>(p + S::KT * 1024) = q.m;
-        *reinterpret_cast<b8*>(p + 2 * S::KT * 1024) = q.l;
-    } else {
-        const Parts2 a = split2(x[0], x[1]), b = split2(x[2], x[3]);
+#pragma unroll
+    for (int j = 0; j < S::NR; j += 4) {
+        const int u = (r0 % 16 + j) / 4;  // the quarter of its 16 rows
+        char* p = buf + r0 / 32 * 1024 + (n + 16 * (2 * (r0 / 16 % 2) + u % 2)) * 16 + 8 * (u / 2);
+        const Parts2 a = split2(x[j], x[j + 1]), b = split2(x[j + 2], x[j + 3]);
         *reinterpret_cast<u2*>(p) = u2{a.h, b.h};
         *reinterpret_cast<u2*>(p + S::KT * 1024) = u2{a.m, b.m};
         *reinterpret_cast<u2*>(p + 2 * S::KT * 1024) = u2{a.l, b.l};
@@ -594,6 +607,7 @@ __global__ __launch_bounds__(kThr) void layer_vectors(
     const unsigned nv = (unsigned)B * L * w;
     const Src<EXACT> sz(Z, nv), s0(z0, (unsigned)B * w);
     const bool res = layer_residual(layer);
+    const int k0 = 16 * (g / 2) + 4 * (g % 2);
     const int it0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * S::GPW + sub) * per);
     const int it1 = min(it0 + per, L * ng);
     Parts8 A[S::MTW][S::KT];
@@ -621,11 +635,11 @@ __global__ __launch_bounds__(kThr) void layer_vectors(
         float zl[NR], zr[NR], x[S::KT][8];
         if (l == 0) {
 #pragma unroll
-            for (int k = 0; k < S::KT; ++k) load_row<8>(s0, op, 32 * k + 8 * g, w, x[k]);
+            for (int k = 0; k < S::KT; ++k) load_operand(s0, op, 32 * k + k0, w, x[k]);
             if (!BWD && res) load_row<NR>(s0, op, r0, w, zr);
         } else {
 #pragma unroll
-            for (int k = 0; k < S::KT; ++k) load_row<8>(sz, op, 32 * k + 8 * g, w, x[k]);
+            for (int k = 0; k < S::KT; ++k) load_operand(sz, op, 32 * k + k0, w, x[k]);
             if (!BWD && res) load_row<NR>(sz, op, r0, w, zr);
         }
         if constexpr (!BWD) load_row<NR>(sz, o, r0, w, zl);
