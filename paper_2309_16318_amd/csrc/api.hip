@@ -614,6 +614,8 @@ hipError_t fused_rest_levels(const NewtonArgs& na, int B, int L, int w, const Ws
 struct PanelPlan {
     int C = 0, Lc = 0;  // C = 0: not for this shape
     size_t P, q, xe, space;
+    bool split = false;  // the weights are split once, at S
+    size_t S;
 };
 
 PanelPlan panel_plan(int B, int L, int w, bool bwd) {
@@ -635,11 +637,22 @@ PanelPlan panel_plan(int B, int L, int w, bool bwd) {
         pl.q = off; off += nq;
         pl.xe = off; off += nq;
         pl.space = off; off += Ce > 1 ? nP / 2 : 0;
-        // (one chunk needs no space)
-        if (off <= lo.r[0]) return pl;
+        if (off > lo.r[0]) continue;
+        pl.S = off;
+        pl.split = off + split_bytes(L, w) <= lo.r[0];
+        return pl;
     }
     pl.C = 0;
     return pl;
+}
+
+// Splits the weights if the plan says so, once per call.
+hipError_t panel_split(bool bwd, const float* W, int L, int w, const PanelPlan& pl, void* ws_base,
+                       hipStream_t st) {
+    if (pl.C == 0 || !pl.split) return hipSuccess;
+    return timed(DEEPPCR_KCLASS_OTHER, 4.0 * L * w * w + (double)split_bytes(L, w), 0.0, st, [&] {
+        return launch_split_weights(bwd, W, (char*)ws_base + pl.S, L, w, st);
+    });
 }
 
 // The solve of Eq. 3 (Eq. 12) for the layers described by `a`, whose d and r
@@ -650,6 +663,7 @@ hipError_t panel_solve(bool bwd, PanelArgs a, const PanelPlan& pl, void* ws_base
     a.rows = a.L + (bwd ? 1 : 0);
     a.Lc = pl.Lc;
     a.C = pl.C;
+    if (pl.split) a.S = base + pl.S;
     a.P = (float*)(base + pl.P);
     a.q = (float*)(base + pl.q);
     float* xe = (float*)(base + pl.xe);
@@ -758,6 +772,7 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
     const long long n = (long long)B * L * w;
     const VecDst xd{ws.r[(num_passes(B, L, w) + 1) & 1], (long long)L * w, (long long)w};
     const PanelPlan pl = panel_plan(B, L, w, false);
+    DEEPPCR_HIP(panel_split(false, W, L, w, pl, workspace, st));
     const bool layers16 = layer_blocks(B, L, w);
     const bool wide_sub = wide_width(w) && wide_substitution(B, L, w);
     const bool fused = false;
@@ -1254,6 +1269,7 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
                                         B, L, w, layer, alpha, st);
         });
         if (e != hipSuccess) return hip_fail(e, "layer_vectors");
+        DEEPPCR_HIP(panel_split(true, W, L, w, pl, workspace, st));
         PanelArgs pa{};
         pa.W = W;
         pa.d = ws.dscale;

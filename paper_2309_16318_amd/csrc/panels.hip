@@ -25,6 +25,8 @@
 #include "internal.h"
 #include "rows.h"
 
+#include <type_traits>
+
 namespace deeppcr {
 namespace {
 
@@ -36,6 +38,14 @@ typedef unsigned u2 __attribute__((ext_vector_type(2)));
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThr = 256;
+
+template <int I, int N, class F>
+__device__ __forceinline__ void unrolled(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        unrolled<I + 1, N>(f);
+    }
+}
 
 // The three bf16 parts of two values, packed.
 struct Parts2 {
@@ -124,6 +134,17 @@ struct ProdShape {
     static constexpr int LDS = 2 * STAGE;
 };
 
+// Weights split once for all passes of a call: per layer and part (h, m, l)
+// the 1 KiB operand tiles of the product panels, 32 rows x 16 columns each,
+// rows padded with zeros; at WP = 128 per 32 rows [part][tile], below
+// [part][all tiles].
+template <int WP>
+struct SplitShape {
+    static constexpr int LAYER = WP * WP * 6;                       // bytes of a layer
+    static constexpr int PART = WP == 32 ? 2048 : 8192;             // bytes of a part
+    static constexpr int SLICE = WP == 128 ? 3 * PART : LAYER;      // bytes of 32 rows (128)
+};
+
 // The rows of W_l (TRANS: of W_l^T) a lane multiplies with, for the vector
 // panels, in put_panel's k order.  Where w is not the padded width, elements beyond a row's end hold
 // the next row's weights: they meet zeros of the panel, or (TRANS) give rows
@@ -200,7 +221,7 @@ __device__ __forceinline__ void put_panel(char* buf, int r0, int n,
 // ------------------------------------------------------------ vector panels
 // One chunk of the recurrence for 16 systems per group.  APPLY: from x_in to
 // every row; otherwise from zero to the chunk's last row, q.
-template <int WP, bool BWD, bool EXACT, bool APPLY>
+template <int WP, bool BWD, bool EXACT, bool APPLY, bool PRE>
 __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int c, int wg) {
     using S = VecShape<WP>;
     // rows requested ahead (beside the products, their registers allow fewer)
@@ -230,7 +251,8 @@ __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int 
         }
     }
     unsigned mx = 0u, mz = 0u;
-    float raw[NB][S::MTW][S::KT][8];
+    float raw[PRE ? 1 : NB][S::MTW][S::KT][8];
+    Parts8 pre[PRE ? NB : 1][S::MTW][S::KT];
     float ad[NB][NR], ar[NB][NR], az[NB][NR];
     // row m's weights, and the vectors its result meets: d and r (forward),
     // d of the next row's layer (backward), the iterate
@@ -261,13 +283,30 @@ __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int 
                                  r0, w, x);
         }
     };
-    auto request = [&](int m, float (&rw)[S::MTW][S::KT][8], float (&d)[NR], float (&r)[NR],
-                       float (&z)[NR]) {
+    // split weights of this lane's rows: tile row within 32 rows, and tile
+    const int trow = (base + S::MTW * n) % 32;
+    const unsigned off = base / 32 * (WP == 128 ? SplitShape<WP>::SLICE : WP / 16 * 1024) +
+                         g / 2 * 1024 + (trow + 32 * (g % 2)) * 16;
+    auto request = [&](int m, auto slot) {
+        constexpr int s = decltype(slot)::value;
         const int mm = min(m, m1 - 1);
         const int op = BWD ? min(L - mm, L - 1) : mm;
-        load_strip<WP, BWD, EXACT>(Src<EXACT>(a.W + (long long)op * w * w, w * w), w, base, n, g,
-                                   rw);
-        aux(mm, d, r, z);
+        if constexpr (PRE) {
+            const char* p = a.S + (long long)op * SplitShape<WP>::LAYER + off;
+#pragma unroll
+            for (int q = 0; q < S::MTW; ++q)
+#pragma unroll
+                for (int k = 0; k < S::KT; ++k) {
+                    const char* o = p + k * 2048 + q * 16;
+                    pre[s][q][k].h = *reinterpret_cast<const b8*>(o);
+                    pre[s][q][k].m = *reinterpret_cast<const b8*>(o + SplitShape<WP>::PART);
+                    pre[s][q][k].l = *reinterpret_cast<const b8*>(o + 2 * SplitShape<WP>::PART);
+                }
+        } else {
+            load_strip<WP, BWD, EXACT>(Src<EXACT>(a.W + (long long)op * w * w, w * w), w, base, n,
+                                       g, raw[s]);
+        }
+        aux(mm, ad[s], ar[s], az[s]);
     };
     float x[NR];
     int m = m0;
@@ -300,21 +339,25 @@ __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int 
         if (m < m1) put(0, d0);
     }
     if (m < m1) {
-#pragma unroll
-        for (int s = 0; s < D; ++s) request(m + s, raw[s], ad[s], ar[s], az[s]);
-        for (int mb = m, buf = 0; mb < m1; mb += NB) {
-#pragma unroll
-            for (int s = 0; s < NB; ++s) {
+        unrolled<0, D>([&](auto s) { request(m + decltype(s)::value, s); });
+        int buf = 0;
+        for (int mb = m; mb < m1; mb += NB) {
+            unrolled<0, NB>([&](auto sc) {
+                constexpr int s = decltype(sc)::value;
                 const int row = mb + s;
-                if (row >= m1) break;
+                if (row >= m1) return;  // uniform over the workgroup
                 Parts8 A[S::MTW][S::KT];
 #pragma unroll
                 for (int q = 0; q < S::MTW; ++q)
 #pragma unroll
-                    for (int k = 0; k < S::KT; ++k) A[q][k] = split8(raw[s][q][k]);
+                    for (int k = 0; k < S::KT; ++k) {
+                        if constexpr (PRE)
+                            A[q][k] = pre[s][q][k];
+                        else
+                            A[q][k] = split8(raw[s][q][k]);
+                    }
                 __syncthreads();  // the panel of row - 1 is complete
-                    request(row + D, raw[(s + D) % NB], ad[(s + D) % NB], ar[(s + D) % NB],
-                        az[(s + D) % NB]);
+                request(row + D, std::integral_constant<int, (s + D) % NB>{});
                 const char* in = panel + buf * S::BUF + lane * 16;
                 Acc<f4> acc[S::MTW] = {};
 #pragma unroll
@@ -340,7 +383,7 @@ __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int 
                 buf ^= 1;
                 put(buf, ad[s]);
                 emit(row, x, az[s]);
-            }
+            });
         }
     }
     if constexpr (APPLY && !BWD) {
@@ -366,7 +409,7 @@ __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int 
 // the weights: 4096 of them per stage are loaded into registers one stage
 // ahead, split, and put into one of two LDS buffers in operand order; one
 // barrier per stage.
-template <int WP, bool BWD, bool EXACT>
+template <int WP, bool BWD, bool EXACT, bool PRE>
 __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int c, int wg) {
     using S = ProdShape<WP>;
     const int t = threadIdx.x, v = t >> 6, lane = t & 63;
@@ -384,7 +427,8 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
     const int rg = t & 7, cg = (t >> 3) % (WP / 4), blk = __builtin_amdgcn_readfirstlane(t / (2 * WP));
     constexpr int LPS = S::LPS;
     constexpr int SPL = WP == 128 ? 4 : 1;  // stages per layer
-    f4 raw[4];
+    f4 raw[PRE ? 1 : 4];
+    u4 pre[PRE ? 6 : 1];
     // d of the layers a stage starts: SYS systems x WP rows per layer, thread
     // t's element e is layer (t + 256 e) / 128's t % 128
     constexpr int ND = (LPS + 1) / 2;
@@ -401,26 +445,47 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
             const unsigned o = ((unsigned)dsys * L + l) * w + drow;
             rd[e] = EXACT || drow < w ? sd.one(o) : 0.f;
         }
-        const int m = min(m1 - 1, m0 + (WP == 128 ? st / 4 : WP == 64 ? st : 4 * st + blk));
-        const int mt = WP == 128 ? st % 4 : WP == 64 ? blk : 0;
-        const int i = 32 * mt + 4 * rg, k = 4 * cg;
-        // (as in load_strip, elements beyond a row's end meet zeros, or give
-        // rows that meet zeros)
-        const Src<EXACT> Wl(a.W + (long long)(BWD ? L - m : m) * w * w, w * w);
+        if constexpr (PRE) {
+            // six 16-byte pieces of the stage per thread
 #pragma unroll
-        for (int e = 0; e < 4; ++e) raw[e] = Wl.at(((BWD ? k : i) + e) * w + (BWD ? i : k));
+            for (int j = 0; j < 6; ++j) {
+                const int u = t + 256 * j;
+                const int m = min(m1 - 1, m0 + (WP == 128 ? st / 4 : WP == 64 ? st : 4 * st + u / 384));
+                const char* p = a.S + (long long)(BWD ? L - m : m) * SplitShape<WP>::LAYER +
+                                (WP == 128 ? st % 4 * SplitShape<WP>::SLICE : 0);
+                pre[j] = *reinterpret_cast<const u4*>(p + (WP == 32 ? u % 384 : u) * 16);
+            }
+        } else {
+            const int m = min(m1 - 1, m0 + (WP == 128 ? st / 4 : WP == 64 ? st : 4 * st + blk));
+            const int mt = WP == 128 ? st % 4 : WP == 64 ? blk : 0;
+            const int i = 32 * mt + 4 * rg, k = 4 * cg;
+            // (as in load_strip, elements beyond a row's end meet zeros, or give
+            // rows that meet zeros)
+            const Src<EXACT> Wl(a.W + (long long)(BWD ? L - m : m) * w * w, w * w);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) raw[e] = Wl.at(((BWD ? k : i) + e) * w + (BWD ? i : k));
+        }
     };
     char* const dst = lds + (blk * S::KT + cg / 4) * 1024 + (4 * rg + 32 * (cg & 1)) * 16 +
                       8 * ((cg >> 1) & 1);
     auto put = [&](int buf) {
+        if constexpr (PRE) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const f4 x = BWD ? f4{raw[0][e], raw[1][e], raw[2][e], raw[3][e]} : raw[e];
-            const Parts2 p = split2(x[0], x[1]), q = split2(x[2], x[3]);
-            char* o = dst + buf * S::STAGE + e * 16;
-            *reinterpret_cast<u2*>(o) = u2{p.h, q.h};
-            *reinterpret_cast<u2*>(o + S::WB / 3) = u2{p.m, q.m};
-            *reinterpret_cast<u2*>(o + 2 * (S::WB / 3)) = u2{p.l, q.l};
+            for (int j = 0; j < 6; ++j) {
+                const int u = t + 256 * j;
+                const int o = WP == 32 ? u % 384 / 128 * 8192 + u / 384 * 2048 + u % 128 * 16 : u * 16;
+                *reinterpret_cast<u4*>(lds + buf * S::STAGE + o) = pre[j];
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const f4 x = BWD ? f4{raw[0][e], raw[1][e], raw[2][e], raw[3][e]} : raw[e];
+                const Parts2 p = split2(x[0], x[1]), q = split2(x[2], x[3]);
+                char* o = dst + buf * S::STAGE + e * 16;
+                *reinterpret_cast<u2*>(o) = u2{p.h, q.h};
+                *reinterpret_cast<u2*>(o + S::WB / 3) = u2{p.m, q.m};
+                *reinterpret_cast<u2*>(o + 2 * (S::WB / 3)) = u2{p.l, q.l};
+            }
         }
         float* const dd = reinterpret_cast<float*>(lds + buf * S::STAGE + S::WB);
 #pragma unroll
@@ -552,14 +617,14 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
 
 // The vectors of chunks 0 .. C-2 first (the longer chain per row and few
 // workgroups), then the products of chunks 1 .. C-2.
-template <int WP, bool BWD, bool EXACT>
+template <int WP, bool BWD, bool EXACT, bool PRE>
 __global__ __launch_bounds__(kThr, WP == 128 ? 2 : 3) void chunk_pass(PanelArgs a) {
     __shared__ __attribute__((aligned(16))) char
         lds[ProdShape<WP>::LDS > VecShape<WP>::LDS ? ProdShape<WP>::LDS : VecShape<WP>::LDS];
     const int vg = (a.B + 16 * VecShape<WP>::GPW - 1) / (16 * VecShape<WP>::GPW);
     const int nv = vg * (a.C - 1);
     if ((int)blockIdx.x < nv) {
-        vector_panel<WP, BWD, EXACT, false>(a, lds, blockIdx.x / vg, blockIdx.x % vg);
+        vector_panel<WP, BWD, EXACT, false, PRE>(a, lds, blockIdx.x / vg, blockIdx.x % vg);
         return;
     }
     const int pg = (a.B + ProdShape<WP>::SYS - 1) / ProdShape<WP>::SYS;
@@ -569,14 +634,47 @@ __global__ __launch_bounds__(kThr, WP == 128 ? 2 : 3) void chunk_pass(PanelArgs 
     const int id = (int)blockIdx.x - nv, per = (total + 7) / 8;
     const int item = (id & 7) * per + (id >> 3);
     if (item >= total || (id >> 3) >= per) return;
-    product_panel<WP, BWD, EXACT>(a, lds, 1 + item / pg, item % pg);
+    product_panel<WP, BWD, EXACT, PRE>(a, lds, 1 + item / pg, item % pg);
 }
 
-template <int WP, bool BWD, bool EXACT>
+template <int WP, bool BWD, bool EXACT, bool PRE>
 __global__ __launch_bounds__(kThr) void apply_pass(PanelArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[VecShape<WP>::LDS];
     const int vg = (a.B + 16 * VecShape<WP>::GPW - 1) / (16 * VecShape<WP>::GPW);
-    vector_panel<WP, BWD, EXACT, true>(a, lds, blockIdx.x / vg, blockIdx.x % vg);
+    vector_panel<WP, BWD, EXACT, true, PRE>(a, lds, blockIdx.x / vg, blockIdx.x % vg);
+}
+
+// ------------------------------------------------------------ split weights
+// The tiles of SplitShape from W (BWD: of W^T), 4 x 4 weights per thread.
+template <int WP, bool BWD, bool EXACT>
+__global__ __launch_bounds__(kThr) void split_weights(const float* __restrict__ W,
+                                                      char* __restrict__ out, int L, int w_) {
+    constexpr int UNITS = WP * WP / 16;
+    const int w = EXACT ? WP : w_;
+    const int id = blockIdx.x * kThr + threadIdx.x;
+    const int l = __builtin_amdgcn_readfirstlane(id / UNITS), u = id % UNITS;
+    if (l >= L) return;
+    const int rg = u & 7, cg = (u >> 3) % (WP / 4), mt = u / (2 * WP);
+    const int i = 32 * mt + 4 * rg, k = 4 * cg;
+    const Src<EXACT> Wl(W + (long long)l * w * w, w * w);
+    f4 raw[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float x[4];
+        load_row<4>(Wl, ((BWD ? k : i) + e) * w, BWD ? i : k, w, x);
+        raw[e] = f4{x[0], x[1], x[2], x[3]};
+    }
+    char* dst = out + (long long)l * SplitShape<WP>::LAYER +
+                (WP == 128 ? mt * SplitShape<WP>::SLICE : mt * (WP / 16) * 1024) + cg / 4 * 1024 +
+                (4 * rg + 32 * (cg & 1)) * 16 + 8 * ((cg >> 1) & 1);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const f4 x = BWD ? f4{raw[0][e], raw[1][e], raw[2][e], raw[3][e]} : raw[e];
+        const Parts2 p = split2(x[0], x[1]), q = split2(x[2], x[3]);
+        *reinterpret_cast<u2*>(dst + e * 16) = u2{p.h, q.h};
+        *reinterpret_cast<u2*>(dst + e * 16 + SplitShape<WP>::PART) = u2{p.m, q.m};
+        *reinterpret_cast<u2*>(dst + e * 16 + 2 * SplitShape<WP>::PART) = u2{p.l, q.l};
+    }
 }
 
 // ------------------------------------------------------------ layer vectors
@@ -695,19 +793,32 @@ __global__ __launch_bounds__(kThr) void layer_vectors(
 
 int padded(int w) { return w <= 32 ? 32 : w <= 64 ? 64 : 128; }
 
-#define DEEPPCR_PANEL(K, BW, GRID, ...)                                                         \
-    do {                                                                                        \
-        const dim3 grid_((unsigned)(GRID)), thr_(kThr);                                         \
-        switch (a_w) {                                                                          \
-            case 32: hipLaunchKernelGGL((K<32, BW, true>), grid_, thr_, 0, st, __VA_ARGS__); break;   \
-            case 64: hipLaunchKernelGGL((K<64, BW, true>), grid_, thr_, 0, st, __VA_ARGS__); break;   \
-            case 128: hipLaunchKernelGGL((K<128, BW, true>), grid_, thr_, 0, st, __VA_ARGS__); break; \
-            default:                                                                            \
-                if (a_w < 32) hipLaunchKernelGGL((K<32, BW, false>), grid_, thr_, 0, st, __VA_ARGS__); \
-                else if (a_w < 64) hipLaunchKernelGGL((K<64, BW, false>), grid_, thr_, 0, st, __VA_ARGS__); \
-                else hipLaunchKernelGGL((K<128, BW, false>), grid_, thr_, 0, st, __VA_ARGS__);  \
-        }                                                                                       \
+// K with the padded width, whether w is it, and the template arguments given
+#define DEEPPCR_PANEL(KERNEL, GRID, ...)                                                      \
+    do {                                                                                      \
+        const dim3 grid_((unsigned)(GRID)), thr_(kThr);                                       \
+        switch (a_w) {                                                                        \
+            case 32: hipLaunchKernelGGL(KERNEL(32, true), grid_, thr_, 0, st, __VA_ARGS__); break;   \
+            case 64: hipLaunchKernelGGL(KERNEL(64, true), grid_, thr_, 0, st, __VA_ARGS__); break;   \
+            case 128: hipLaunchKernelGGL(KERNEL(128, true), grid_, thr_, 0, st, __VA_ARGS__); break; \
+            default:                                                                          \
+                if (a_w < 32) hipLaunchKernelGGL(KERNEL(32, false), grid_, thr_, 0, st, __VA_ARGS__); \
+                else if (a_w < 64) hipLaunchKernelGGL(KERNEL(64, false), grid_, thr_, 0, st, __VA_ARGS__); \
+                else hipLaunchKernelGGL(KERNEL(128, false), grid_, thr_, 0, st, __VA_ARGS__); \
+        }                                                                                     \
     } while (0)
+#define LAYER_VECTORS_F(WP, EX) (layer_vectors<WP, false, EX>)
+#define LAYER_VECTORS_B(WP, EX) (layer_vectors<WP, true, EX>)
+#define SPLIT_F(WP, EX) (split_weights<WP, false, EX>)
+#define SPLIT_B(WP, EX) (split_weights<WP, true, EX>)
+#define CHUNK_F(WP, EX) (chunk_pass<WP, false, EX, false>)
+#define CHUNK_B(WP, EX) (chunk_pass<WP, true, EX, false>)
+#define CHUNK_FP(WP, EX) (chunk_pass<WP, false, EX, true>)
+#define CHUNK_BP(WP, EX) (chunk_pass<WP, true, EX, true>)
+#define APPLY_F(WP, EX) (apply_pass<WP, false, EX, false>)
+#define APPLY_B(WP, EX) (apply_pass<WP, true, EX, false>)
+#define APPLY_FP(WP, EX) (apply_pass<WP, false, EX, true>)
+#define APPLY_BP(WP, EX) (apply_pass<WP, true, EX, true>)
 
 int vector_groups(int B, int WP) {
     const int per = WP == 32 ? 32 : 16;
@@ -723,31 +834,26 @@ int product_groups(int B, int WP) {
 bool panel_width(int w) { return w > 16 && w <= kMaxWidth; }
 int panel_pad(int w) { return padded(w); }
 
-// Chunks of a solve, by the estimated time of its parts: a row of the
-// products and of the apply pass, measured on one MI355X, one round of
-// workgroups (two per CU at a padded width of 128, three below) or more, and
-// the solve over the chunk ends.
+// Chunks of a solve, by the estimated time of its parts (us), measured on one
+// MI355X over B 1-256 and L 128-8192: a row of the products while there is a
+// workgroup per CU at most (beyond, in proportion; at a padded width of 128,
+// where two share a CU, twice as much up to 512 workgroups), a row of the
+// apply pass, a launch, and the solve over the chunk ends.  B = 16, L = 1024,
+// w = 128: 946 us with 8 chunks, 521 with 16, 423 with 32, 447 with 96.
 int panel_chunks(int B, int rows, int w) {
     const int WP = padded(w), k = WP == 32 ? 0 : WP == 64 ? 1 : 2;
-    static const double prod[] = {1.0, 2.0, 7.0}, apply[] = {0.55, 0.75, 2.6};
-    // a full round of products takes longer than a lone workgroup
-    static const double full[] = {1.6, 4.0, 12.5};
-    const double slots = 256.0 * (WP == 128 ? 2 : 3);
+    static const double prod[] = {0.58, 1.48, 4.75}, apply[] = {0.5, 0.72, 2.6};
     const int pg = product_groups(B, WP), vg = vector_groups(B, WP);
     int best = 1;
-    double t_best = 4.5 + rows * apply[k];
-    for (int j = 3; j <= 40; ++j) {
-        // C = 2, 3, 4, 5, 6, 8, 10, 12, ...: quarter powers of two
-        const int C = ((4 + j % 4) << (j / 4)) >> 2;
-        if (C < 2 || C > rows) continue;
+    double t_best = 4.0 + rows * apply[k];
+    for (int j = 4; j <= 44; ++j) {
+        const int C = ((4 + j % 4) << (j / 4)) >> 2;  // 2, 2, 3, 3, 4, 5, 6, 7, 8, 10, ...
+        if (C > rows) break;
         const int Lc = (rows + C - 1) / C;
-        const double wgs = (double)pg * (C - 2) + (double)vg * (C - 1);
-        double row = prod[k];
-        if (wgs > 256) row += (full[k] - prod[k]) * (wgs > slots ? 1.0 : (wgs - 256) / (slots - 256));
-        if (wgs > slots) row *= wgs > 4 * slots ? wgs / slots : (double)(int)(wgs / slots + 0.999);
-        if (C == 2) row = 1.2 * apply[k];
-        const double va = (double)vg * C > 1024 ? vg * C / 1024.0 : 1.0;
-        double t = 9.0 + Lc * (row + apply[k] * va);
+        const double wgs = ((double)pg * (C - 2) + (double)vg * (C - 1)) / 256.0;
+        double row = C == 2 ? apply[k] : prod[k];
+        if (C > 2 && wgs > 1.0) row *= WP != 128 ? (wgs > 1.2 ? 0.85 * wgs : 1.0) : wgs > 2.0 ? wgs : 2.0;
+        double t = 8.0 + Lc * (row + apply[k] * ((double)vg * C > 512 ? vg * C / 512.0 : 1.0));
         if (t < t_best && C > 2) t += block_plan(B, C - 1, WP, nullptr);
         if (t < t_best) {
             t_best = t;
@@ -768,11 +874,22 @@ hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, con
     unsigned* const mx = want_max ? red : nullptr;
     const int a_w = w;
     if (bwd)
-        DEEPPCR_PANEL(layer_vectors, true, grid, W, bias, z0, Z, d, r, red, mx, B, L, w, layer,
+        DEEPPCR_PANEL(LAYER_VECTORS_B, grid, W, bias, z0, Z, d, r, red, mx, B, L, w, layer,
                       alpha, per);
     else
-        DEEPPCR_PANEL(layer_vectors, false, grid, W, bias, z0, Z, d, r, red, mx, B, L, w, layer,
+        DEEPPCR_PANEL(LAYER_VECTORS_F, grid, W, bias, z0, Z, d, r, red, mx, B, L, w, layer,
                       alpha, per);
+    return hipGetLastError();
+}
+
+size_t split_bytes(int L, int w) { return (size_t)L * padded(w) * padded(w) * 6; }
+
+hipError_t launch_split_weights(bool bwd, const float* W, char* out, int L, int w,
+                                hipStream_t st) {
+    const int WP = padded(w), a_w = w;
+    const long long grid = ((long long)L * WP * WP / 16 + kThr - 1) / kThr;
+    if (bwd) DEEPPCR_PANEL(SPLIT_B, grid, W, out, L, w);
+    else DEEPPCR_PANEL(SPLIT_F, grid, W, out, L, w);
     return hipGetLastError();
 }
 
@@ -781,20 +898,20 @@ hipError_t launch_chunk_pass(bool bwd, const PanelArgs& a, hipStream_t st) {
     const long long nv = (long long)vector_groups(a.B, WP) * (a.C - 1);
     const long long np = (long long)product_groups(a.B, WP) * (a.C - 2);
     const long long grid = nv + (np + 7) / 8 * 8;
-    if (bwd)
-        DEEPPCR_PANEL(chunk_pass, true, grid, a);
-    else
-        DEEPPCR_PANEL(chunk_pass, false, grid, a);
+    if (bwd && a.S) DEEPPCR_PANEL(CHUNK_BP, grid, a);
+    else if (bwd) DEEPPCR_PANEL(CHUNK_B, grid, a);
+    else if (a.S) DEEPPCR_PANEL(CHUNK_FP, grid, a);
+    else DEEPPCR_PANEL(CHUNK_F, grid, a);
     return hipGetLastError();
 }
 
 hipError_t launch_apply_pass(bool bwd, const PanelArgs& a, hipStream_t st) {
     const int a_w = a.w;
     const long long grid = (long long)vector_groups(a.B, padded(a.w)) * a.C;
-    if (bwd)
-        DEEPPCR_PANEL(apply_pass, true, grid, a);
-    else
-        DEEPPCR_PANEL(apply_pass, false, grid, a);
+    if (bwd && a.S) DEEPPCR_PANEL(APPLY_BP, grid, a);
+    else if (bwd) DEEPPCR_PANEL(APPLY_B, grid, a);
+    else if (a.S) DEEPPCR_PANEL(APPLY_FP, grid, a);
+    else DEEPPCR_PANEL(APPLY_F, grid, a);
     return hipGetLastError();
 }
 
