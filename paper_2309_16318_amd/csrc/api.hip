@@ -226,14 +226,6 @@ int num_levels(int L) {
     return k;
 }
 
-// Kernel launches of a PCR sweep: pairs of levels where the width has the
-// two-level kernel, plus a single last level when the level count is odd.
-int num_passes(int B, int L, int w) {
-    const int kt = tail_levels(B, L, w, 0);
-    const int K1 = num_levels(L) - kt;
-    return (two_level(B, L, w) ? (K1 + 1) / 2 : K1) + (kt > 0 ? 1 : 0);
-}
-
 // Every array argument must start on a 16-byte boundary (the kernels load
 // rows of blocks, states and weights as 16-byte vectors); NULL passes (the
 // null checks are separate).
@@ -258,42 +250,6 @@ void level_work(int B, int L, int w, int s, double* bytes, double* flops) {
     *bytes = 4.0 * B * (nr * w2 + na * w2 + 2.0 * L * w);
     *flops = (double)B * (nr * 2.0 * w2 + na * 2.0 * w2 * w);
 }
-
-// Algorithmic work of a fused pair of levels (strides s, 2s): the flops of
-// both levels; the bytes the fused pass must move: A_l read for l >= s, the
-// level-2s operators written for l >= 4s, r read and written once.
-void level2_work(int B, int L, int w, int s, double* bytes, double* flops) {
-    double b1, f1, b2, f2;
-    level_work(B, L, w, s, &b1, &f1);
-    level_work(B, L, w, 2 * s, &b2, &f2);
-    const double nr = (double)(L - s), na = (double)(L - 4 * s > 0 ? L - 4 * s : 0);
-    const double w2 = (double)w * w;
-    *bytes = 4.0 * B * (nr * w2 + na * w2 + 2.0 * L * w);
-    *flops = f1 + f2;
-}
-
-// Algorithmic work of the last two levels as mat-vecs only (strides s, 2s,
-// 4s >= L): A_l read once for l >= s; mat-vecs A_l r_{l-s} and
-// A_l r'_{l-s} for l >= s, A_l t_{l-s} for l >= 2s; r read and written once.
-void last2_work(int B, int L, int w, int s, double* bytes, double* flops) {
-    const double n1 = (double)(L - s), n2 = (double)(L - 2 * s > 0 ? L - 2 * s : 0);
-    const double w2 = (double)w * w;
-    *bytes = 4.0 * B * (n1 * w2 + 2.0 * L * w);
-    *flops = (double)B * 2.0 * w2 * (2.0 * n1 + n2);
-}
-
-// Algorithmic work of the last kt levels solved by substitution along the
-// chains (s = 2^(levels - kt)): A_l read once and one mat-vec for every row
-// l >= s; r read and the solution written.
-void tail_work(int B, int L, int w, int kt, double* bytes, double* flops) {
-    const int s = 1 << (num_levels(L) - kt);
-    const double w2 = (double)w * w;
-    *bytes = 4.0 * B * ((double)(L - s) * w2 + 2.0 * L * w);
-    *flops = (double)B * (L - s) * 2.0 * w2;
-}
-
-// Stride of the rows the last kt levels start from.
-int tail_stride(int L, int kt) { return 1 << (num_levels(L) - kt); }
 
 // Whether a solve on stored blocks goes by chunks (blocks.hip): widths 4 to
 // kMaxWidth.  Smaller blocks fill a sixteenth or less of a padded one, so
@@ -339,76 +295,37 @@ hipError_t block_solve(const BlockSrc& A, const VecSrc& r, const VecDst& x, int 
                  [&] { return launch_block_down(A, y, r, x, xe, walk, upd_red, B, L, w, Lc, C, st); });
 }
 
-// Runs all PCR levels.  Level 0 reads (A0, r0); level k writes operators to
-// ws A buffer (k + a_first) % 2 and vectors to ws r buffer (k + r_first) % 2,
-// except the last level, which writes the solution to `x`.
-// With bwd the first pass (levels 1 and 2) forms the backward's blocks from
-// the weights instead of reading A0 (w = 32, 64, 128 and L > 2 only).
+// The solve: by chunks, or by PCR levels (widths below 4 and above kMaxWidth),
+// one per launch.  Level 0 reads (A0, r0); level k writes operators to ws A
+// buffer k % 2 and vectors to ws r buffer k % 2, except the last level, which
+// writes the solution to x.  upd_red (by chunks only): as for block_solve.
 hipError_t pcr_sweep(const BlockSrc& A0, const VecSrc& r0, const VecDst& x, int B, int L, int w,
-                     float* wsA[2], float* wsr[2], int a_first, int r_first, hipStream_t st,
-                     const BwdArgs* bwd = nullptr, unsigned* upd_red = nullptr) {
-    if (by_chunks(w) && !bwd) return block_solve(A0, r0, x, B, L, w, wsA[0], st, upd_red);
+                     float* wsA[2], float* wsr[2], hipStream_t st, unsigned* upd_red = nullptr) {
+    if (by_chunks(w)) return block_solve(A0, r0, x, B, L, w, wsA[0], st, upd_red);
     const int K = num_levels(L);
     if (K == 0) {
         const double bytes = 8.0 * B * L * w;
         return timed(DEEPPCR_KCLASS_OTHER, bytes, 0.0, st,
                      [&] { return launch_copy_rows(r0, x, B, L, w, st); });
     }
-    const bool two = two_level(B, L, w);
-    const int kt = tail_levels(B, L, w, 0);
-    const int K1 = K - kt;  // levels before the tail
     BlockSrc Ain = A0;
     VecSrc rin = r0;
     int s = 1;
-    // pass p writes operators to ws A buffer (p + a_first) % 2 and vectors to
-    // ws r buffer (p + r_first) % 2; the last pass writes the solution to x
-    // (the tail pass, when there is one, after the levels below K1)
-    const int Kend = kt > 0 ? K1 : K;
-    for (int k = 0, p = 0; k < Kend; ++p) {
-        const bool pair = two && k + 1 < Kend;
-        const bool last = kt == 0 && (k + (pair ? 1 : 0)) == K - 1;
-        float* Aout = wsA[(p + a_first) & 1];
-        VecDst rout = last ? x
-                           : VecDst{wsr[(p + r_first) & 1], (long long)L * w, (long long)w};
+    for (int k = 0; k < K; ++k, s *= 2) {
+        float* Aout = wsA[k & 1];
+        const VecDst rout =
+            k == K - 1 ? x : VecDst{wsr[k & 1], (long long)L * w, (long long)w};
         double bytes, flops;
-        hipError_t e;
-        if (bwd && k == 0) {
-            // blocks from the weights (read from L2): the products and r
-            level2_work(B, L, w, s, &bytes, &flops);
-            bytes -= 4.0 * B * (L - 1) * (double)w * w;
-            e = timed(DEEPPCR_KCLASS_PCR_LEVEL, bytes, flops, st, [&] {
-                return launch_pcr_level2_bwd(*bwd, rin, Aout, rout, B, L, w, st);
-            });
-        } else if (pair && last && last_pair_width(w)) {
-            last2_work(B, L, w, s, &bytes, &flops);
-            e = timed(DEEPPCR_KCLASS_PCR_LEVEL, bytes, flops, st, [&] {
-                return launch_pcr_level2_last(Ain, rin, rout, B, L, w, s, st);
-            });
-        } else if (pair) {
-            level2_work(B, L, w, s, &bytes, &flops);
-            e = timed(DEEPPCR_KCLASS_PCR_LEVEL, bytes, flops, st, [&] {
-                return launch_pcr_level2(Ain, rin, Aout, rout, B, L, w, s, st);
-            });
-        } else {
-            level_work(B, L, w, s, &bytes, &flops);
-            e = timed(DEEPPCR_KCLASS_PCR_LEVEL, bytes, flops, st, [&] {
-                return wide_width(w) ? launch_pcr_level_wide(Ain, rin, Aout, rout, B, L, w, s, st)
-                                     : launch_pcr_level(Ain, rin, Aout, rout, B, L, w, s, st);
-            });
-        }
+        level_work(B, L, w, s, &bytes, &flops);
+        hipError_t e = timed(DEEPPCR_KCLASS_PCR_LEVEL, bytes, flops, st, [&] {
+            return wide_width(w) ? launch_pcr_level_wide(Ain, rin, Aout, rout, B, L, w, s, st)
+                                 : launch_pcr_level_small(Ain, rin, Aout, rout, B, L, w, s, st);
+        });
         if (e != hipSuccess) return e;
         Ain = BlockSrc{Aout, (long long)L * w * w, (long long)w * w, 0};
         rin = VecSrc{rout.base, rout.bstride, rout.rstride};
-        s *= pair ? 4 : 2;
-        k += pair ? 2 : 1;
     }
-    if (kt == 0) return hipSuccess;
-    double bytes, flops;
-    tail_work(B, L, w, kt, &bytes, &flops);
-    if (upd_red) bytes += 4.0 * B * L * w;  // the iterate is read as well
-    return timed(DEEPPCR_KCLASS_PCR_TAIL, bytes, flops, st, [&] {
-        return launch_pcr_chain_subst(Ain, rin, x, B, L, w, tail_stride(L, kt), st, upd_red);
-    });
+    return hipSuccess;
 }
 
 struct Ws {
@@ -498,113 +415,6 @@ hipError_t read_measures(const unsigned* red, unsigned* hw, hipStream_t st, unsi
     if (e != hipSuccess) return e;
     for (int j = 0; j < 3; ++j) m[j] = rec[j];
     return hipSuccess;
-}
-
-// The fused Newton linear solve (w = 16, 32, 64, 128): the layer evaluation
-// runs inside the first PCR pass (level 1, or levels 1 and 2 where
-// first_level_count says so); for w = 16, 32 without a tail pass the update
-// + reduction runs inside the last level, otherwise the last pass writes the
-// solution (as does the first for L <= 2, to `x`) and the separate update
-// kernel applies it.
-// Split in two so that a stopping test on the residual (reduced by the first
-// level) can sit between the halves.
-hipError_t fused_first_level(const NewtonArgs& na, int B, int L, int w, const Ws& ws,
-                             const VecDst& x, hipStream_t st) {
-    const int K = num_levels(L);
-    const double w2 = (double)w * w;
-    const long long ld = (long long)L * w;
-    // the first level (or two) with the layers: W once, Z read twice,
-    // products and r written
-    const int nl = first_level_count(B, L, w);
-    const double na2 = (double)(L - 2 * nl > 0 ? L - 2 * nl : 0);
-    const double bytes = 4.0 * ((double)L * w2 + B * (na2 * w2 + 3.0 * L * w));
-    double flops = (double)B * (L * 3.0 * w2 + (L - 1) * 2.0 * w2 +
-                                (L - 2 > 0 ? L - 2 : 0) * 2.0 * w2 * w);
-    if (nl == 2) {
-        double b2, f2;
-        level_work(B, L, w, 2, &b2, &f2);
-        flops += f2;
-    }
-    const VecDst out = (K <= 1) ? x : VecDst{ws.r[0], ld, (long long)w};
-    return timed(DEEPPCR_KCLASS_PCR_LEVEL, bytes, flops, st,
-                 [&] { return launch_first_level_fwd(na, ws.A[0], out, B, L, w, st); });
-}
-
-hipError_t fused_rest_levels(const NewtonArgs& na, int B, int L, int w, const Ws& ws,
-                             const VecDst& x, hipStream_t st) {
-    const int K = num_levels(L);
-    const long long ld = (long long)L * w;
-    if (K <= 1) {
-        const long long n = (long long)B * L * w;
-        return timed(DEEPPCR_KCLASS_UPDATE, 12.0 * n, 2.0 * n, st,
-                     [&] { return launch_update_reduce(na.Z, x.base, n, na.red, st); });
-    }
-    // the last levels go to one tail pass where tail_levels says so; else for
-    // w = 16, 32 the last level applies the update itself
-    const int k0 = first_level_count(B, L, w);
-    const int kt = tail_levels(B, L, w, k0);
-    const bool upd = fused_newton_levels(w) && kt == 0 && k0 < K;
-    const int Kp = upd ? K - 1 : K - kt;
-    BlockSrc Ain{ws.A[0], (long long)L * w * w, (long long)w * w, 0};
-    VecSrc rin{ws.r[0], ld, (long long)w};
-    // the levels after the first one (or two) up to Kp-1, two per pass where
-    // possible; pass p writes ws buffers p % 2 (the first pass wrote buffers 0)
-    int s = 1 << k0, p = 1;
-    for (int k = k0; k < Kp; ++p) {
-        const bool pair = two_level(B, L, w) && k + 1 < Kp;
-        float* Aout = ws.A[p & 1];
-        const VecDst rout{ws.r[p & 1], ld, (long long)w};
-        double bytes, flops;
-        hipError_t e;
-        if (pair && !upd && kt == 0 && k + 1 == K - 1 && last_pair_width(w)) {
-            last2_work(B, L, w, s, &bytes, &flops);
-            e = timed(DEEPPCR_KCLASS_PCR_LEVEL, bytes, flops, st, [&] {
-                return launch_pcr_level2_last(Ain, rin, rout, B, L, w, s, st);
-            });
-        } else if (pair) {
-            level2_work(B, L, w, s, &bytes, &flops);
-            e = timed(DEEPPCR_KCLASS_PCR_LEVEL, bytes, flops, st, [&] {
-                return launch_pcr_level2(Ain, rin, Aout, rout, B, L, w, s, st);
-            });
-        } else {
-            level_work(B, L, w, s, &bytes, &flops);
-            e = timed(DEEPPCR_KCLASS_PCR_LEVEL, bytes, flops, st, [&] {
-                return launch_pcr_level(Ain, rin, Aout, rout, B, L, w, s, st);
-            });
-        }
-        if (e != hipSuccess) return e;
-        Ain = BlockSrc{Aout, (long long)L * w * w, (long long)w * w, 0};
-        rin = VecSrc{rout.base, rout.bstride, rout.rstride};
-        s *= pair ? 4 : 2;
-        k += pair ? 2 : 1;
-    }
-    if (kt > 0) {
-        // the chains left for the last kt levels solved by substitution in
-        // one pass, which also applies the update Z += x and reduces the
-        // convergence maxima (the iterate is read and written instead of
-        // the solution being written)
-        double bytes, flops;
-        tail_work(B, L, w, kt, &bytes, &flops);
-        bytes += 4.0 * B * L * w;
-        const VecDst zo{na.Z, ld, (long long)w};
-        return timed(DEEPPCR_KCLASS_PCR_TAIL, bytes, flops, st, [&] {
-            return launch_pcr_chain_subst(Ain, rin, zo, B, L, w, tail_stride(L, kt), st,
-                                          na.red);
-        });
-    }
-    if (!upd) {
-        // the last pass wrote the solution to the ws r buffer rin reads
-        const long long n = (long long)B * L * w;
-        return timed(DEEPPCR_KCLASS_UPDATE, 12.0 * n, 2.0 * n, st,
-                     [&] { return launch_update_reduce(na.Z, rin.base, n, na.red, st); });
-    }
-    // the last level with the update Z += x and the convergence reduction
-    double bytes, flops;
-    level_work(B, L, w, s, &bytes, &flops);
-    bytes += 8.0 * B * L * w;  // the iterate is read and written
-    return timed(DEEPPCR_KCLASS_PCR_LEVEL, bytes, flops, st, [&] {
-        return launch_last_level_update(Ain, rin, na, B, L, w, s, st);
-    });
 }
 
 // ------------------------------------------------- chunked MLP solve
@@ -770,13 +580,12 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
         if (e != hipSuccess) return hip_fail(e, "initial_guess");
     }
     const long long n = (long long)B * L * w;
-    const VecDst xd{ws.r[(num_passes(B, L, w) + 1) & 1], (long long)L * w, (long long)w};
+    // the buffer that the last PCR level's vectors do not come from
+    const VecDst xd{ws.r[(num_levels(L) + 1) & 1], (long long)L * w, (long long)w};
     const PanelPlan pl = panel_plan(B, L, w, false);
     DEEPPCR_HIP(panel_split(false, W, L, w, pl, workspace, st));
     const bool layers16 = layer_blocks(B, L, w);
     const bool wide_sub = wide_width(w) && wide_substitution(B, L, w);
-    const bool fused = false;
-    const NewtonArgs na{W, bias, z0, Z, ws.red, layer, alpha};
     unsigned* fslots = ws.red + kRedF;
     if (rule.residual) {
         hipError_t e = timed(DEEPPCR_KCLASS_OTHER, 4.0 * kRedShards, 0.0, st,
@@ -786,8 +595,9 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
     float res0 = 0.f;
     for (int k = 0; k <= rule.max_iter; ++k) {
         if (!rule.residual && k == rule.max_iter) break;
-        // Layers, Jacobian blocks (forward order) and residuals at the iterate:
-        // fused into the first PCR level, or evaluated into ws A[1], r[1].
+        // The layers at the iterate: d and residuals into ws r[1], r[0] where
+        // the solve forms the blocks itself, else Jacobian blocks (forward
+        // order) and residuals into ws A[1], r[1].
         hipError_t e;
         if (pl.C > 0 || layers16) {
             e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 4.0 * n), 2.0 * B * L * w2, st, [&] {
@@ -799,8 +609,6 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
                 return launch_wide_vectors(false, W, bias, z0, Z, ws.r[1], ws.r[0], ws.red, B, L,
                                            w, layer, alpha, st);
             });
-        } else if (fused) {
-            e = fused_first_level(na, B, L, w, ws, xd, st);
         } else {
             e = timed(DEEPPCR_KCLASS_LAYER, eval_bytes, eval_flops, st, [&] {
                 return launch_forward_eval(W, bias, z0, Z, ws.A[1], ws.r[1], ws.red, B, L, w,
@@ -852,9 +660,6 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
             e = timed(DEEPPCR_KCLASS_UPDATE, 12.0 * n, 2.0 * n, st,
                       [&] { return launch_update_reduce(Z, ws.r[0], n, ws.red, st); });
             if (e != hipSuccess) return hip_fail(e, "update_reduce");
-        } else if (fused) {
-            e = fused_rest_levels(na, B, L, w, ws, xd, st);
-            if (e != hipSuccess) return hip_fail(e, "newton levels");
         } else if (by_chunks(w)) {
             e = block_solve(BlockSrc{ws.A[1], (long long)L * w * w, (long long)w * w, 0},
                             VecSrc{ws.r[1], (long long)L * w, (long long)w},
@@ -864,7 +669,7 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
         } else {
             e = pcr_sweep(BlockSrc{ws.A[1], (long long)L * w * w, (long long)w * w, 0},
                           VecSrc{ws.r[1], (long long)L * w, (long long)w}, xd, B, L, w, ws.A,
-                          ws.r, 0, 0, st);
+                          ws.r, st);
             if (e != hipSuccess) return hip_fail(e, "pcr_sweep");
             e = timed(DEEPPCR_KCLASS_UPDATE, 12.0 * n, 2.0 * n, st,
                       [&] { return launch_update_reduce(Z, xd.base, n, ws.red, st); });
@@ -952,7 +757,7 @@ int pcr_solve_run(const float* J, const float* r, float* x, int B, int L, int w,
         r0 = VecSrc{r + (long long)(L - 1) * w, (long long)L * w, -(long long)w};
         xd = VecDst{x + (long long)(L - 1) * w, (long long)L * w, -(long long)w};
     }
-    hipError_t e = pcr_sweep(A0, r0, xd, B, L, w, ws.A, ws.r, 0, 0, st);
+    hipError_t e = pcr_sweep(A0, r0, xd, B, L, w, ws.A, ws.r, st);
     if (e != hipSuccess) return hip_fail(e, "pcr_solve_block_bidiag");
     return DEEPPCR_OK;
 }
@@ -1172,12 +977,12 @@ int deeppcr_newton_step(const float* J, const float* F, float* Z, int B, int L, 
     const BlockSrc J0{J, (long long)L * w * w, (long long)w * w, 0};
     const VecSrc r0{ws.r[1], (long long)L * w, (long long)w};
     if (by_chunks(w)) {
-        e = pcr_sweep(J0, r0, VecDst{Z, (long long)L * w, (long long)w}, B, L, w, ws.A, ws.r, 0,
-                      0, st, nullptr, ws.red);
+        e = pcr_sweep(J0, r0, VecDst{Z, (long long)L * w, (long long)w}, B, L, w, ws.A, ws.r, st,
+                      ws.red);
         if (e != hipSuccess) return hip_fail(e, "pcr_sweep");
     } else {
-        const VecDst xd{ws.r[(num_passes(B, L, w) + 1) & 1], (long long)L * w, (long long)w};
-        e = pcr_sweep(J0, r0, xd, B, L, w, ws.A, ws.r, 0, 0, st);
+        const VecDst xd{ws.r[(num_levels(L) + 1) & 1], (long long)L * w, (long long)w};
+        e = pcr_sweep(J0, r0, xd, B, L, w, ws.A, ws.r, st);
         if (e != hipSuccess) return hip_fail(e, "pcr_sweep");
         e = timed(DEEPPCR_KCLASS_UPDATE, 12.0 * n, 2.0 * n, st,
                   [&] { return launch_update_reduce(Z, xd.base, n, ws.red, st); });
@@ -1258,9 +1063,6 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
     hipStream_t st = (hipStream_t)stream;
     Ws ws = carve(workspace, lo);
     const double w2 = (double)w * w;
-    // w = 32, 64, 128 with paired levels: the first PCR pass forms the blocks
-    // from the weights and c d, so the assembly writes only c d and the
-    // right-hand side
     const PanelPlan pl = panel_plan(B, L, w, true);
     if (pl.C > 0) {
         hipError_t e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 2.0 * B * L * w),
@@ -1332,20 +1134,16 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
         if (e != hipSuccess) return hip_fail(e, "wgrad");
         return DEEPPCR_OK;
     }
-    const bool from_weights = false;
-    const BwdArgs bw{W, ws.dscale, layer_residual(layer) ? 1 : 0};
-    const double jbytes = from_weights ? 0.0 : 4.0 * B * L * w2;
-    hipError_t e = timed(DEEPPCR_KCLASS_LAYER, jbytes + 4.0 * B * L * 3.0 * w,
-                         (double)B * L * (from_weights ? 2.0 : 3.0) * w2, st, [&] {
-        return launch_backward_assemble(W, bias, z0, Z, G, from_weights ? nullptr : ws.A[1],
-                                        ws.r[1], ws.dscale, B, L, w, layer, alpha, st);
+    hipError_t e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * B * L * (w2 + 3.0 * w), 3.0 * B * L * w2, st,
+                         [&] {
+        return launch_backward_assemble(W, bias, z0, Z, G, ws.A[1], ws.r[1], ws.dscale, B, L, w,
+                                        layer, alpha, st);
     });
     if (e != hipSuccess) return hip_fail(e, "backward_assemble");
     const VecDst lam{Lambda + (long long)(L - 1) * w, (long long)L * w, -(long long)w};
     e = pcr_sweep(BlockSrc{ws.A[1], (long long)L * w * w, (long long)w * w,
                            backward_blocks_transposed(w) ? 1 : 0},
-                  VecSrc{ws.r[1], (long long)L * w, (long long)w}, lam, B, L, w, ws.A, ws.r, 0, 0,
-                  st, from_weights ? &bw : nullptr);
+                  VecSrc{ws.r[1], (long long)L * w, (long long)w}, lam, B, L, w, ws.A, ws.r, st);
     if (e != hipSuccess) return hip_fail(e, "pcr_sweep");
     e = timed(DEEPPCR_KCLASS_OTHER, 4.0 * (w2 + 3.0 * B * w), 2.0 * B * w2, st, [&] {
         return launch_dz0(W, ws.dscale, Lambda, dz0, B, L, w, layer, st);
@@ -1406,7 +1204,7 @@ int deeppcr_resnet_forward(const float* W, const float* bias, const float* z0, f
         });
         if (e != hipSuccess) return hip_fail(e, "resnet_initial_guess");
     }
-    const VecDst xd{ws.r[(num_passes(B, G, w) + 1) & 1], (long long)G * w, (long long)w};
+    const VecDst xd{ws.r[(num_levels(G) + 1) & 1], (long long)G * w, (long long)w};
     // block evaluation: W once, X read twice, blocks and residuals written;
     // flops: the s - 1 block products and the s mat-vecs per block
     const double eval_bytes = 4.0 * ((double)L * w2 + (double)B * G * (w2 + 3.0 * w));
@@ -1425,13 +1223,13 @@ int deeppcr_resnet_forward(const float* W, const float* bias, const float* z0, f
             // block evaluation cleared their slots)
             e = pcr_sweep(BlockSrc{ws.A[1], (long long)G * w * w, (long long)w * w, 0},
                           VecSrc{ws.r[1], (long long)G * w, (long long)w},
-                          VecDst{X, (long long)G * w, (long long)w}, B, G, w, ws.A, ws.r, 0, 0,
-                          st, nullptr, ws.red);
+                          VecDst{X, (long long)G * w, (long long)w}, B, G, w, ws.A, ws.r, st,
+                          ws.red);
             if (e != hipSuccess) return hip_fail(e, "pcr_sweep");
         } else {
             e = pcr_sweep(BlockSrc{ws.A[1], (long long)G * w * w, (long long)w * w, 0},
                           VecSrc{ws.r[1], (long long)G * w, (long long)w}, xd, B, G, w, ws.A,
-                          ws.r, 0, 0, st);
+                          ws.r, st);
             if (e != hipSuccess) return hip_fail(e, "pcr_sweep");
             e = timed(DEEPPCR_KCLASS_UPDATE, 12.0 * n, 2.0 * n, st,
                       [&] { return launch_update_reduce(X, xd.base, n, ws.red, st); });
@@ -1501,11 +1299,10 @@ int deeppcr_resnet_backward(const float* W, const float* z0, const float* Z, con
     // block-output adjoints mu (natural order) from the transposed solve
     // (not the right-hand side's buffer: the solution's rows are written in the
     // opposite order; the PCR levels end in either)
-    float* mu = ws.r[by_chunks(w) ? 0 : (num_passes(B, G, w) + 1) & 1];
+    float* mu = ws.r[by_chunks(w) ? 0 : (num_levels(G) + 1) & 1];
     const VecDst xd{mu + (long long)(G - 1) * w, (long long)G * w, -(long long)w};
     e = pcr_sweep(BlockSrc{ws.A[1], (long long)G * w * w, (long long)w * w, 1},
-                  VecSrc{ws.r[1], (long long)G * w, (long long)w}, xd, B, G, w, ws.A, ws.r, 0, 0,
-                  st);
+                  VecSrc{ws.r[1], (long long)G * w, (long long)w}, xd, B, G, w, ws.A, ws.r, st);
     if (e != hipSuccess) return hip_fail(e, "pcr_sweep");
     e = timed(DEEPPCR_KCLASS_OTHER, 4.0 * ((double)L * w2 + 2.0 * B * L * w),
               2.0 * B * L * w2, st, [&] {

@@ -79,113 +79,6 @@ struct VecDst {
     long long rstride;
 };
 
-// ---------------------------------------------------------------- PCR level
-// Work decomposition of one level with stride s: the rows l >= s form s
-// chains (l mod s); each chain is cut into segments of at most n rows;
-// segs_per_class segments per chain, total = B * s * segs_per_class items.
-struct LevelPlan {
-    int s;
-    int n;
-    int segs_per_class;
-    long long total;
-};
-LevelPlan plan_level(int B, int L, int s, long long target_items, int n_max);
-
-// The blocks of the backward's reversed transposed system formed from the
-// weights instead of read from memory: row m >= 1 holds J_{L-m}^T with
-// J_l = diag(dscale_l) W_l (+ I for residual layers), dscale [B, L, w].
-struct BwdArgs {
-    const float* W;       // [L, w, w]
-    const float* dscale;  // [B, L, w]
-    int residual;
-};
-
-// Inputs of the layer evaluation fused into the first PCR level of a Newton
-// iteration, and of the Newton update fused into the last level.
-struct NewtonArgs {
-    const float* W;      // [L, w, w]
-    const float* bias;   // [L, w]
-    const float* z0;     // [B, w]
-    float* Z;            // [B, L, w] current iterate (read by the first level,
-                         // updated by the last level)
-    unsigned* red;       // reduction area (kRedDZ, kRedZ and kRedF slots)
-    int layer;
-    float alpha;
-};
-
-// Whether the first level with the layer evaluation (layer_first_level) and
-// the last level with the update (fused_newton_levels) exist for width w.
-bool fused_newton_levels(int w);
-bool layer_first_level(int w);
-
-// Number of PCR levels launch_first_level_fwd runs (1, or 2 for w = 64, 128
-// when the solve has two levels or more and two_level accepts the shape, and
-// for w = 32 from B L >= 2048 chain elements).
-int first_level_count(int B, int L, int w);
-
-// First level (s = 1) of the Newton linear solve with the layers, Jacobian
-// blocks and residuals evaluated on the fly (never stored):
-//   r_l = f_l(Z_{l-1}) - Z_l, J_l = df_l at Z_{l-1};
-//   rout[l] = r_l + J_l r_{l-1} (rout[0] = r_0), Aout[l] = J_l J_{l-1} (l >= 2);
-// or, when first_level_count says 2, the first two levels: rout and Aout
-// then hold what the level s = 2 writes.
-// Also clears the max|dZ| and max|Z| slots and reduces max|r| into the
-// kRedF slots.
-hipError_t launch_first_level_fwd(const NewtonArgs& na, float* Aout, const VecDst& rout, int B,
-                                  int L, int w, hipStream_t stream);
-
-// Last level of the Newton linear solve (stride s, reading the previous
-// level's blocks and vectors) fused with the update: Z[l] += x_l for every
-// row, and atomic max of |x| and |Z| into na.red.
-hipError_t launch_last_level_update(const BlockSrc& Ain, const VecSrc& rin, const NewtonArgs& na,
-                                    int B, int L, int w, int s, hipStream_t stream);
-
-// One level (stride s) of Parallel Cyclic Reduction over B systems of L rows:
-//   rows l <  s : rout[l] = rin[l]                     (already final)
-//   rows l >= s : rout[l] = rin[l] + Ain[l] rin[l-s]
-//   rows l >= 2s: Aout[l] = Ain[l] Ain[l-s]
-// Aout is contiguous [B, L, w, w] in internal row order.
-hipError_t launch_pcr_level(const BlockSrc& Ain, const VecSrc& rin, float* Aout,
-                            const VecDst& rout, int B, int L, int w, int s,
-                            hipStream_t stream);
-
-// Two levels (strides s and 2s) in one pass, where two_level accepts the
-// shape: rout[l] and Aout[l] hold what level 2s would have written
-// (operators for rows l >= 4s).  Aout must not be the buffer Ain reads.
-bool two_level(int B, int L, int w);
-
-// The first two levels (s = 1, 2) of the backward solve with the blocks
-// formed from the weights (w = 32, 64, 128, L > 2); rout and Aout as for
-// launch_pcr_level2.
-hipError_t launch_pcr_level2_bwd(const BwdArgs& bw, const VecSrc& rin, float* Aout,
-                                 const VecDst& rout, int B, int L, int w, hipStream_t stream);
-
-// The number of last levels (0: none) solved instead by substitution along
-// the chains they act on (launch_pcr_chain_subst), for the problem shape and
-// the number of levels `first` the solve's first pass does (then pairs up to
-// them): 3 to 6 levels at w = 32, 64, 128.
-int tail_levels(int B, int L, int w, int first);
-// After the levels with strides below s = 2^(levels - kt) every row l >= s
-// satisfies x_l = A_l x_{l-s} + r_l: B s independent chains
-// (l = c, c + s, ...), each solved by substitution, one mat-vec per row.
-// Ain holds the operators of the level before (rows l >= s), not
-// transposed; the solution goes to rout.  With red, rout is the Newton
-// iterate instead: the solution is added to it and max |x|, max |Z + x| are
-// reduced into the kRedDZ, kRedZ slots of red.
-hipError_t launch_pcr_chain_subst(const BlockSrc& Ain, const VecSrc& rin, const VecDst& rout,
-                                  int B, int L, int w, int s, hipStream_t stream,
-                                  unsigned* red = nullptr);
-
-// The last two levels of a solve (strides s, 2s with 4s >= L) in one pass
-// without operator products (mat-vecs only), for the widths last_pair_width
-// accepts; rout gets the solution.
-bool last_pair_width(int w);
-hipError_t launch_pcr_level2_last(const BlockSrc& Ain, const VecSrc& rin, const VecDst& rout,
-                                  int B, int L, int w, int s, hipStream_t stream);
-hipError_t launch_pcr_level2(const BlockSrc& Ain, const VecSrc& rin, float* Aout,
-                             const VecDst& rout, int B, int L, int w, int s,
-                             hipStream_t stream);
-
 // ------------------------------------------------------------ layer kernels
 // Forward Newton step: for every (b, l) evaluate the layer at Zprev = Z[b,l-1]
 // (z0[b] for l = 0), write r[b,l] = f_l(Zprev) - Z[b,l] and, for l >= 1,

@@ -70,20 +70,6 @@ __device__ __forceinline__ float half_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Sum over the lanes l, l ^ W, l ^ 2W, ... of the wave (W = 16 or 32) in
-// every lane: the row swap of v_permlane16_swap (16-lane rows 2r and 2r + 1)
-// and then that of v_permlane32_swap, no LDS round trip.
-template <int W>
-__device__ __forceinline__ float group_sum(float v) {
-    static_assert(W == 16 || W == 32, "lane groups of 16 or 32");
-    if constexpr (W == 16) {
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v),
-                                                        false, false);
-        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    return half_sum(v);
-}
-
 // (strip of M) x for x in LDS; every lane of the row gets the sum.
 template <int W, class M>
 __device__ __forceinline__ float strip_matvec(const M& a, const float* x, int h) {
@@ -191,31 +177,6 @@ __device__ __forceinline__ void strip_store(float* dst, const M& a, int R, int h
 #pragma unroll
     for (int q = 0; q < Tile2Shape<W>::NQ; ++q)
         *reinterpret_cast<v4f*>(dst + R * W + 8 * q + 4 * h) = strip_quad<W>(a, q);
-}
-
-// Quad q (columns 8q + 4h .. +3) of a strip from a block in global memory.
-template <int W, bool TRANS>
-__device__ __forceinline__ void strip_load_quad(const float* blk, StripA<W>& a, int R, int h,
-                                                int q) {
-    if constexpr (!TRANS) {
-        a[q] = *reinterpret_cast<const v4f*>(blk + R * W + 8 * q + 4 * h);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) a[q][e] = blk[(8 * q + 4 * h + e) * W + R];
-    }
-}
-
-// Quad q of a strip to a transposed block in LDS (see strip_put_T).
-template <int W, class M>
-__device__ __forceinline__ void strip_put_T_quad(float* XT, const M& a, int R, int h, int q) {
-    using S = Tile2Shape<W>;
-    float* xb = XT + 4 * h * S::PITCH + R;
-    const v4f x = strip_quad<W>(a, q);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        xb[(8 * q + e) * S::PITCH] = x[e];
-        asm volatile("" ::: "memory");
-    }
 }
 
 // A strip to a transposed block in LDS (XT[col][row], pitch PITCH).  The

@@ -28,13 +28,13 @@ import hashlib
 import json
 import os
 
-# the PCR level kernels, the register-strip helpers they are built from and
-# the substitution pass of the last levels
+# the kernels of the linear solves: chunk products and substitutions, on layers
+# and on stored blocks, and the row accesses they share
 KERNEL_SOURCES = [os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", f)
-                  for f in ("pcr_level.hip", "strip.h", "chain.hip")]
+                  for f in ("panels.hip", "blocks.hip", "rows.h")]
 
-# kernels of the last levels' pass (timed as a class of their own)
-TAIL_PREFIXES = ("pcr_chain_subst", "pcr_level_tail")
+# kernels of the substitutions (timed as a class of their own)
+TAIL_PREFIXES = ("pcr_chain_subst", "pcr_level_tail", "block_down", "apply_pass")
 
 
 def is_tail(name: str) -> bool:
@@ -42,8 +42,8 @@ def is_tail(name: str) -> bool:
 
 
 def is_pcr(name: str) -> bool:
-    """A kernel of the PCR sweep: a level pass or the last levels' pass."""
-    return "pcr_level" in name or is_tail(name)
+    """A kernel of a linear solve: a level, products or a substitution."""
+    return "pcr_level" in name or name.startswith(("chunk_pass", "block_up")) or is_tail(name)
 
 
 def code_digest(text: str) -> str:
