@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kThreads) void resnet_intra_adjoint_kernel(
 
 size_t block_lds_bytes(int w) { return (4 * (size_t)w + 2 * (size_t)w * w) * sizeof(float); }
 
-// ---- one wave per (system, block), w = 16 or 32 ----------------------------
+// ---- one wave per (system, block), w = 32 ----------------------------------
 // Lane l owns row i = l / LPR of the running product P and its NC columns
 // c0 = (l % LPR) * NC ..; the next factor's row, W_j[i, :] scaled by
 // sigma'(z), comes from global memory (L2-resident, shared by every system)
@@ -395,6 +395,101 @@ __global__ __launch_bounds__(256) void resnet_block_wave(
                 if (c0 + 4 * q + e == i) x[e] += 1.f;
             *reinterpret_cast<v4f*>(Ab + 4 * q) = x;
         }
+    }
+}
+
+// ---- one wave per (system, block), w = 16 ----------------------------------
+// The running product and the state stay in registers: a lane (i, g) of
+// v_mfma_f32_16x16x4_f32 holds rows 4 g + e of column i of a result and, as
+// the next right operand, gives instruction e the rows k = 4 g + e, which the
+// 16-byte load of W_j's row i matches as the left operand.  sigma' scales that
+// operand's k = 4 g + e, the rows of the state the lane holds.  Each lane
+// evaluates one activation and takes its quad's others by lane permutation.
+// Roles of BWD and the arguments as resnet_block_wave, which went through LDS
+// and vector FMAs: 25.7 us per launch (B = 64, 256 blocks of 4 layers, tanh).
+template <int E>
+__device__ __forceinline__ float quad_lane(float v) {
+    return dpp<E * 0x55>(v);
+}
+
+template <bool BWD>
+__global__ __launch_bounds__(256) void resnet_block_wave16(
+    const float* __restrict__ Wt, const float* __restrict__ bias, const float* __restrict__ z0,
+    const float* __restrict__ S, const float* __restrict__ Gv, float* __restrict__ A,
+    float* __restrict__ r, unsigned* __restrict__ red, int B, int G, int skip, int act) {
+    const int lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
+    if (!BWD && blockIdx.x == 0)
+        for (int k = threadIdx.x; k < 2 * kRedShards; k += 256) red[k] = 0u;
+    // b * G + g, the same in every lane: addresses stay scalar
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const long long item = (long long)blockIdx.x * 4 + wave;
+    if (item >= (long long)B * G) return;
+    const int b = (int)((unsigned)item / (unsigned)G);
+    const int g = (int)((unsigned)item - (unsigned)b * (unsigned)G);
+    const float* Zb = S + (long long)b * G * skip * 16;
+    auto vec = [&](const float* p) { return *reinterpret_cast<const v4f*>(p + 4 * q); };
+    auto row = [&](const float* p) { return *reinterpret_cast<const v4f*>(p + (16 * i + 4 * q)); };
+    if constexpr (BWD) {
+        const int m = G - 1 - g;
+        if (i == 0) {
+            const v4f zero = {0.f, 0.f, 0.f, 0.f};
+            *reinterpret_cast<v4f*>(r + ((long long)b * G + m) * 16 + 4 * q) =
+                m == 0 ? vec(Gv + (long long)b * 16) : zero;
+        }
+        if (g == 0) return;
+    }
+    const float* Wj = Wt + (long long)g * skip * 256;
+    v4f a = row(Wj), bi = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (!BWD) bi = vec(bias + (long long)g * skip * 16);
+    const v4f xin = vec(BWD ? Zb + ((long long)g * skip - 1) * 16
+                            : g == 0 ? z0 + (long long)b * 16 : S + (item - 1) * 16);
+    v4f z = xin, P;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) P[e] = 4 * q + e == i ? 1.f : 0.f;
+    const int own = lane & 3;
+    for (int tt = 0; tt < skip; ++tt) {
+        const v4f w = a, bt = bi;
+        const long long next = (long long)g * skip + min(tt + 1, skip - 1);
+        v4f zn = z;
+        a = row(Wt + next * 256);
+        if constexpr (!BWD)
+            bi = vec(bias + next * 16);
+        else
+            zn = vec(Zb + (next - 1) * 16);  // the next layer's input
+        const float x = own == 0 ? z[0] : own == 1 ? z[1] : own == 2 ? z[2] : z[3];
+        float d;
+        const float s = act_fn(act, x, &d);
+        if (g > 0) {
+            const v4f f = {w[0] * quad_lane<0>(d), w[1] * quad_lane<1>(d), w[2] * quad_lane<2>(d),
+                           w[3] * quad_lane<3>(d)};
+            v4f pn = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                pn = __builtin_amdgcn_mfma_f32_16x16x4f32(f[e], P[e], pn, 0, 0, 0);
+            P = pn;
+        }
+        if constexpr (!BWD) {
+            const v4f y = {quad_lane<0>(s), quad_lane<1>(s), quad_lane<2>(s), quad_lane<3>(s)};
+            v4f t0 = {0.f, 0.f, 0.f, 0.f}, t1 = t0;
+            t0 = __builtin_amdgcn_mfma_f32_16x16x4f32(w[0], y[0], t0, 0, 0, 0);
+            t1 = __builtin_amdgcn_mfma_f32_16x16x4f32(w[2], y[2], t1, 0, 0, 0);
+            t0 = __builtin_amdgcn_mfma_f32_16x16x4f32(w[1], y[1], t0, 0, 0, 0);
+            t1 = __builtin_amdgcn_mfma_f32_16x16x4f32(w[3], y[3], t1, 0, 0, 0);
+            z = t0 + t1 + bt;
+        } else {
+            z = zn;
+        }
+    }
+    if constexpr (!BWD)
+        if (i == 0) {
+            const v4f x = vec(S + item * 16);
+            *reinterpret_cast<v4f*>(r + item * 16 + 4 * q) = (z + xin) - x;
+        }
+    if (g > 0) {
+        float* Ab = A + (BWD ? (long long)b * G + (G - g) : item) * 256;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            Ab[64 * q + i + 16 * e] = P[e] + (4 * q + e == i ? 1.f : 0.f);
     }
 }
 
@@ -593,7 +688,11 @@ hipError_t launch_block_wave(const float* Wt, const float* bias, const float* z0
                              const float* Gv, float* A, float* r, unsigned* red, int B, int G,
                              int skip, int act, hipStream_t stream) {
     const long long items = (long long)B * G;
-    hipLaunchKernelGGL((resnet_block_wave<W, BWD>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0,
+    if constexpr (W == 16)
+        hipLaunchKernelGGL((resnet_block_wave16<BWD>), dim3((unsigned)((items + 3) / 4)), dim3(256),
+                           0, stream, Wt, bias, z0, S, Gv, A, r, red, B, G, skip, act);
+    else
+        hipLaunchKernelGGL((resnet_block_wave<W, BWD>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0,
                        stream, Wt, bias, z0, S, Gv, A, r, red, B, G, skip, act);
     return hipGetLastError();
 }
