@@ -411,8 +411,26 @@ size_t tiny_lds_bytes(int B, int L, int w) {
     return (3 * nz + 2 * na + nz + nw) * sizeof(float) + 2 * (kThreads / 64) * sizeof(unsigned);
 }
 
+// One workgroup against one launch per pass: its products (B L w^3 on each
+// PCR level but the last) run on one CU, and where the width is not a
+// template's their index arithmetic costs as much again, while the launches
+// of the chunked solve cost 17 us an iteration whatever they hold.  At 6
+// iterations, one workgroup against launches, us: w 9 L 16 B 1 (35k products)
+// 102 : 130, w 6 L 32 B 1 (28k) 101 : 155, w 5 L 64 B 1 (40k) 170 : 164,
+// w 9 L 8 B 4 (47k) 135 : 115, w 16 L 8 B 1 (65k) 108 : 89, w 12 L 16 B 2
+// (166k) 281 : 130, w 16 L 16 B 1 (197k) 285 : 119.  Widths 1, 2, 4 and 8
+// win or tie up to the LDS they can hold (w 8 L 32 B 2 115 : 165).  At w 3
+// the launches are those of the PCR levels, 2 more per level: L 256 B 1 (6.9k
+// a level) 241 : 259, L 8 B 64 (13.8k) 206 : 170.
 bool tiny_eligible(int B, int L, int w) {
-    return (double)B * L * w * (w + 4.0) * 4.0 <= 60000.0 && tiny_lds_bytes(B, L, w) <= 65536;
+    if ((double)B * L * w * (w + 4.0) * 4.0 > 60000.0 || tiny_lds_bytes(B, L, w) > 65536)
+        return false;
+    if (w == 1 || w == 2 || w == 4 || w == 8) return true;
+    const double products = (double)B * L * w * w * w;
+    if (w == 3) return products <= 8192.0;
+    int levels = 0;
+    while ((1 << levels) < L) ++levels;
+    return products * (levels - 1) <= 40000.0;
 }
 
 hipError_t launch_newton_tiny(const float* W, const float* bias, const float* z0, float* Z,

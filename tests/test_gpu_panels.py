@@ -40,8 +40,13 @@ def h(t):
     torch.cuda.synchronize()
     return t.detach().cpu().numpy()
 
+# sizes on both sides of the line between one workgroup and launches
+SMALL = [(3, 37, 8), (3, 38, 8), (5, 4, 16), (5, 16, 8), (6, 1, 32), (6, 1, 64), (9, 1, 17),
+         (9, 2, 16), (12, 2, 8), (16, 2, 4), (16, 4, 4), (17, 1, 16), (32, 1, 2), (32, 1, 4),
+         (48, 1, 1)]
 
-@pytest.mark.parametrize("w,B,L", SHAPES)
+
+@pytest.mark.parametrize("w,B,L", SHAPES + SMALL)
 @pytest.mark.parametrize("layer,alpha", [(0, 1.0), (1, 0.1)])
 def test_forward_backward(dev, w, B, L, layer, alpha):
     print(f"panels w={w} B={B} L={L} layer={layer}", flush=True)
