@@ -26,6 +26,9 @@ if ROOT not in sys.path:
 
 PEAK_HBM_GBS = 8000.0        # MI355X HBM3E, GB/s
 PEAK_FP32_TFLOPS = 157.3     # MI355X dense fp32 (matrix and vector), TFLOP/s
+# products of split weights: six bf16 products each, of the 2516.6 TFLOP/s
+# dense bf16 peak
+PEAK_SPLIT_TFLOPS = 2516.6 / 6
 RIDGE = PEAK_FP32_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)
 
 
@@ -316,7 +319,15 @@ def measured_mfma_util(workload):
             "pcr_tail_pct": t.get("pcr_tail_mfma_util_pct")}
 
 
-def roofline(cls, w, by_intensity=False):
+def products_peak(wl):
+    """Peak rate of the block products of a workload's solves: the MLP solves
+    of widths 17 to 128 take theirs as split bf16 products, all others as
+    fp32 ones."""
+    split = wl.kind == "mlp" and 17 <= wl.w <= 128
+    return PEAK_SPLIT_TFLOPS if split else PEAK_FP32_TFLOPS
+
+
+def roofline(cls, w, by_intensity=False, peak=PEAK_FP32_TFLOPS):
     """Roofline position of one kernel class from the library's counts:
     algorithmic flops and bytes of its launches over their summed event
     time; MFMA-bound at an intensity above the ridge (or, for the PCR level
@@ -326,11 +337,11 @@ def roofline(cls, w, by_intensity=False):
     gbs = cls["bytes"] / (cls["ms"] * 1e-3) / 1e9
     # both positions, so that a w <= 32 class placed on the MFMA side still
     # shows its fraction of the HBM peak (and the other way round)
-    both = {"frac_of_mfma_peak": round(tflops / PEAK_FP32_TFLOPS, 4),
+    both = {"frac_of_mfma_peak": round(tflops / peak, 4),
             "frac_of_hbm_peak": round(gbs / PEAK_HBM_GBS, 4)}
     if intensity >= RIDGE or (w >= 64 and not by_intensity):
-        return {"bound": "mfma", "achieved": round(tflops, 3), "peak": PEAK_FP32_TFLOPS,
-                "unit": "TFLOP/s", "frac": round(tflops / PEAK_FP32_TFLOPS, 4), **both}
+        return {"bound": "mfma", "achieved": round(tflops, 3), "peak": round(peak, 1),
+                "unit": "TFLOP/s", "frac": round(tflops / peak, 4), **both}
     return {"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS,
             "unit": "GB/s", "frac": round(gbs / PEAK_HBM_GBS, 4), **both}
 
@@ -370,15 +381,16 @@ def main():
 
     ms_step = el * 1e3 / args.steps
     value = wl.B * wl.L / (el / args.steps)
-    roof = roofline(prof["pcr_level"], wl.w)
+    # a solve that forms no products (one row per launch) has only substitutions
+    cls = "pcr_level" if prof["pcr_level"]["launches"] else "pcr_tail"
+    solve = prof[cls]
+    roof = roofline(solve, wl.w, by_intensity=cls == "pcr_tail", peak=products_peak(wl))
     roof["traffic"] = measured_traffic(wl.name)
     roof["mfma_util"] = measured_mfma_util(wl.name)
-    roof["alg_bytes_per_launch"] = round(prof["pcr_level"]["bytes"] /
-                                         max(prof["pcr_level"]["launches"], 1))
-    roof["kernel"] = "pcr_level"
-    roof["avg_launch_us"] = round(prof["pcr_level"]["ms"] * 1e3 /
-                                  max(prof["pcr_level"]["launches"], 1), 3)
-    roof["launches"] = prof["pcr_level"]["launches"]
+    roof["alg_bytes_per_launch"] = round(solve["bytes"] / max(solve["launches"], 1))
+    roof["kernel"] = cls
+    roof["avg_launch_us"] = round(solve["ms"] * 1e3 / max(solve["launches"], 1), 3)
+    roof["launches"] = solve["launches"]
 
     layer_names = ["tanh_mlp", "tanh_residual", "sigmoid_mlp", "sigmoid_residual", "relu_mlp",
                    "relu_residual"]
@@ -408,9 +420,11 @@ def main():
     }
     tail = prof["pcr_tail"]
     if tail["launches"] > 0:
-        # the last levels' pass (substitution along the chains), timed as a
-        # class of its own
-        out["roofline_tail"] = {"kernel": "chunk_chain" if wl.chunks > 1 else "pcr_chain_subst",
+        # the substitutions inside the chunks, timed as a class of their own
+        tail_kernel = ("chunk_chain" if wl.chunks > 1 else
+                       "apply_pass" if products_peak(wl) == PEAK_SPLIT_TFLOPS else
+                       "wide_step" if wl.w > 128 else "block_down")
+        out["roofline_tail"] = {"kernel": tail_kernel,
                                 **roofline(tail, wl.w, by_intensity=True),
                                 "avg_launch_us": round(tail["ms"] * 1e3 / tail["launches"], 3),
                                 "launches": tail["launches"]}

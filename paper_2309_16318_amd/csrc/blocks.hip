@@ -1,4 +1,4 @@
-// The block-bidiagonal solve of Eq. 3 on stored blocks, widths 1 to 128, by
+// The block-bidiagonal solve of Eq. 3 on stored blocks, widths 4 to 128, by
 // reduction over row chunks: the cyclic reduction of Sec. 3 with chunks of m
 // rows in the place of pairs.
 //

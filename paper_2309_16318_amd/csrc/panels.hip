@@ -1,5 +1,5 @@
 // The Newton solve and the backward solve of MLP layers by row chunks, for
-// widths 9 to 128: the operators J_l = diag(d_l) W_l (+ I) (App. A.1) are
+// widths 17 to 128: the operators J_l = diag(d_l) W_l (+ I) (App. A.1) are
 // never stored.
 //
 // The rows of every system are cut into C consecutive chunks.  Inside a chunk
@@ -8,7 +8,7 @@
 //      product P of its operators, one block product per row (Alg. 1 forms
 //      one per row and level), and, beside it, every chunk's q;
 //   2. the chunk ends are a block-bidiagonal system of C - 1 rows with the
-//      operators P, solved by the PCR sweep or by substitution;
+//      operators P, solved as stored blocks (blocks.hip);
 //   3. apply_pass substitutes inside every chunk from its x_in, which also
 //      applies the Newton update, or writes the adjoints.
 // In exact arithmetic this is the solution of Eq. 3 (Eq. 12 for the

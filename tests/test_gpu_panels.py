@@ -1,4 +1,4 @@
-"""GPU parity of the chunked MLP solve (widths 9 to 128) where its tiles and
+"""GPU parity of the chunked MLP solve (and of the small sizes beside it) where its tiles and
 chunks end: widths on both sides of the padded ones and odd ones whose rows
 start on any 4-byte boundary, batches on both sides of a group of systems,
 depths giving one, two, three and many chunks, a short last chunk.  Against
