@@ -16,6 +16,8 @@
 #include "internal.h"
 #include "strip.h"
 
+#include <type_traits>
+
 namespace deeppcr {
 namespace {
 
@@ -406,7 +408,8 @@ __global__ __launch_bounds__(256) void resnet_block_wave(
 // operand's k = 4 g + e, the rows of the state the lane holds.  Each lane
 // evaluates one activation and takes its quad's others by lane permutation.
 // Roles of BWD and the arguments as resnet_block_wave, which went through LDS
-// and vector FMAs: 25.7 us per launch (B = 64, 256 blocks of 4 layers, tanh).
+// and vector FMAs: 25.7 us per launch (B = 64, 256 blocks of 4 layers, tanh),
+// here 23.6; the backward 25 -> 18.
 template <int E>
 __device__ __forceinline__ float quad_lane(float v) {
     return dpp<E * 0x55>(v);
@@ -490,6 +493,137 @@ __global__ __launch_bounds__(256) void resnet_block_wave16(
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             Ab[64 * q + i + 16 * e] = P[e] + (4 * q + e == i ? 1.f : 0.f);
+    }
+}
+
+// ---- one wave per block and group of systems, w = 16 -----------------------
+// resnet_block_wave16 spends its issue on one system's state in all 64 lanes.
+// Here a wave takes one block for 8 systems: lane (i, q) holds rows
+// 4 q + e of system i's state, so that the activations fill the lanes and one
+// product with W_j serves all systems.  sigma' of system s scales W_j for its
+// product by a broadcast of lane s within each row of 16 lanes.  The first
+// layer's sigma' scales columns of the result, which is left to the end: every
+// product starts from W_0 itself, one product less per system.
+// Bound by issue (one product of 4 MFMAs per system and layer, 4 activations
+// per lane and layer) at 2 waves per SIMD: 18.0 us per launch against 23.6
+// (B = 64, 256 blocks of 4 layers, tanh); the backward 17.3 against 18.
+template <int S>
+__device__ __forceinline__ float row_lane(float v) {
+    return dpp<0x150 + S>(v);
+}
+template <int S, int N, class F>
+__device__ __forceinline__ void each_system(F&& f) {
+    if constexpr (S < N) {
+        f(std::integral_constant<int, S>{});
+        each_system<S + 1, N>(f);
+    }
+}
+
+constexpr int kGroup = 8;
+
+template <bool BWD>
+__global__ __launch_bounds__(256) void resnet_block_group16(
+    const float* __restrict__ Wt, const float* __restrict__ bias, const float* __restrict__ z0,
+    const float* __restrict__ S, const float* __restrict__ Gv, float* __restrict__ A,
+    float* __restrict__ r, unsigned* __restrict__ red, int B, int G, int skip, int act) {
+    constexpr int kPitch = 20;
+    __shared__ __align__(16) float first[4][16 * kPitch];
+    const int lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
+    if (!BWD && blockIdx.x == 0)
+        for (int k = threadIdx.x; k < 2 * kRedShards; k += 256) red[k] = 0u;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const unsigned groups = ((unsigned)B + kGroup - 1) / kGroup;
+    const long long item = (long long)blockIdx.x * 4 + wave;
+    if (item >= (long long)groups * G) return;
+    const int b0 = (int)((unsigned)item / (unsigned)G) * kGroup;
+    const int g = (int)((unsigned)item % (unsigned)G);
+    const int nb = min(kGroup, B - b0);
+    const long long b = b0 + min(i, nb - 1);  // lanes past the last system repeat it
+    const float* Zb = S + b * G * skip * 16;
+    auto vec = [&](const float* p) { return *reinterpret_cast<const v4f*>(p + 4 * q); };
+    auto row = [&](const float* p) { return *reinterpret_cast<const v4f*>(p + (16 * i + 4 * q)); };
+    const v4f zero = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (BWD) {
+        const int m = G - 1 - g;
+        if (i < nb)
+            *reinterpret_cast<v4f*>(r + (b * G + m) * 16 + 4 * q) =
+                m == 0 ? vec(Gv + b * 16) : zero;
+        if (g == 0) return;
+    }
+    const float* W0 = Wt + (long long)g * skip * 256;
+    v4f a = row(W0), bi = zero;
+    if constexpr (!BWD) bi = vec(bias + (long long)g * skip * 16);
+    const v4f xin = vec(BWD ? Zb + ((long long)g * skip - 1) * 16
+                            : g == 0 ? z0 + b * 16 : S + (b * G + g - 1) * 16);
+    v4f z = xin, P[kGroup];
+    {
+        v4f p0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p0[e] = W0[64 * q + 16 * e + i];
+#pragma unroll
+        for (int s = 0; s < kGroup; ++s) P[s] = p0;
+    }
+    for (int tt = 0; tt < skip; ++tt) {
+        const v4f w = a, bt = bi;
+        const long long next = (long long)g * skip + min(tt + 1, skip - 1);
+        v4f zn = z;
+        a = row(Wt + next * 256);
+        if constexpr (!BWD)
+            bi = vec(bias + next * 16);
+        else
+            zn = vec(Zb + (next - 1) * 16);  // the next layer's input
+        v4f d, y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float de;
+            y[e] = act_fn(act, z[e], &de);
+            d[e] = de;
+        }
+        if (tt == 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) first[wave][(4 * q + e) * kPitch + i] = d[e];
+            wave_sync();
+        } else if (g > 0) {
+            each_system<0, kGroup>([&](auto sc) {
+                constexpr int s = decltype(sc)::value;
+                v4f pn = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    pn = __builtin_amdgcn_mfma_f32_16x16x4f32(w[e] * row_lane<s>(d[e]), P[s][e],
+                                                              pn, 0, 0, 0);
+                P[s] = pn;
+            });
+        }
+        if constexpr (!BWD) {
+            v4f t0 = zero, t1 = zero;
+            t0 = __builtin_amdgcn_mfma_f32_16x16x4f32(w[0], y[0], t0, 0, 0, 0);
+            t1 = __builtin_amdgcn_mfma_f32_16x16x4f32(w[2], y[2], t1, 0, 0, 0);
+            t0 = __builtin_amdgcn_mfma_f32_16x16x4f32(w[1], y[1], t0, 0, 0, 0);
+            t1 = __builtin_amdgcn_mfma_f32_16x16x4f32(w[3], y[3], t1, 0, 0, 0);
+            z = t0 + t1 + bt;
+        } else {
+            z = zn;
+        }
+    }
+    if constexpr (!BWD)
+        if (i < nb) {
+            const v4f x = vec(S + (b * G + g) * 16);
+            *reinterpret_cast<v4f*>(r + (b * G + g) * 16 + 4 * q) = (z + xin) - x;
+        }
+    if (g > 0) {
+        float* Ab = A + ((long long)b0 * G + (BWD ? G - g : g)) * 256 + 64 * q + i;
+        const long long pitch = (long long)G * 256;
+        v4f d0[kGroup / 4];
+#pragma unroll
+        for (int k = 0; k < kGroup / 4; ++k)
+            d0[k] = *reinterpret_cast<const v4f*>(&first[wave][i * kPitch + 4 * k]);
+        each_system<0, kGroup>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            if (s < nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) Ab[s * pitch + 16 * e] =
+                    fmaf(P[s][e], d0[s / 4][s % 4], 4 * q + e == i ? 1.f : 0.f);
+        });
     }
 }
 
@@ -683,15 +817,33 @@ __global__ __launch_bounds__(256) void resnet_intra_adjoint_wave(
     }
 }
 
+// The groups of 8 systems pay once their waves fill the chip, 1024 of them:
+// forward of 6 iterations, wave per system against groups, us: B 16, 512
+// blocks 261 : 245, B 64, 256 blocks 328 : 274, B 256, 128 blocks 480 : 400;
+// B 16, 128 blocks 160 : 174.  The backward, whose states are read, gains
+// from twice that: 35.3 : 35.8 at 8192 blocks, 51 : 49 at 16384.  A last group
+// that is nearly empty costs as much as a full one.
+bool group16(bool bwd, int B, int G) {
+    const long long filled = ((long long)B + kGroup - 1) / kGroup * kGroup;
+    return (long long)B * G >= (bwd ? 16384 : 8192) && filled * 4 <= 5LL * B;
+}
+
 template <int W, bool BWD>
 hipError_t launch_block_wave(const float* Wt, const float* bias, const float* z0, const float* S,
                              const float* Gv, float* A, float* r, unsigned* red, int B, int G,
                              int skip, int act, hipStream_t stream) {
     const long long items = (long long)B * G;
-    if constexpr (W == 16)
+    if constexpr (W == 16) {
+        if (group16(BWD, B, G)) {
+            const long long waves = ((long long)B + kGroup - 1) / kGroup * G;
+            hipLaunchKernelGGL((resnet_block_group16<BWD>), dim3((unsigned)((waves + 3) / 4)),
+                               dim3(256), 0, stream, Wt, bias, z0, S, Gv, A, r, red, B, G, skip,
+                               act);
+            return hipGetLastError();
+        }
         hipLaunchKernelGGL((resnet_block_wave16<BWD>), dim3((unsigned)((items + 3) / 4)), dim3(256),
                            0, stream, Wt, bias, z0, S, Gv, A, r, red, B, G, skip, act);
-    else
+    } else
         hipLaunchKernelGGL((resnet_block_wave<W, BWD>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0,
                        stream, Wt, bias, z0, S, Gv, A, r, red, B, G, skip, act);
     return hipGetLastError();
