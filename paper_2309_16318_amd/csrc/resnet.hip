@@ -409,7 +409,7 @@ __global__ __launch_bounds__(256) void resnet_block_wave(
 // evaluates one activation and takes its quad's others by lane permutation.
 // Roles of BWD and the arguments as resnet_block_wave, which went through LDS
 // and vector FMAs: 25.7 us per launch (B = 64, 256 blocks of 4 layers, tanh),
-// here 23.6; the backward 25 -> 18.
+// here 25.0; the backward 25 -> 18.
 template <int E>
 __device__ __forceinline__ float quad_lane(float v) {
     return dpp<E * 0x55>(v);
@@ -505,7 +505,7 @@ __global__ __launch_bounds__(256) void resnet_block_wave16(
 // layer's sigma' scales columns of the result, which is left to the end: every
 // product starts from W_0 itself, one product less per system.
 // Bound by issue (one product of 4 MFMAs per system and layer, 4 activations
-// per lane and layer) at 2 waves per SIMD: 18.0 us per launch against 23.6
+// per lane and layer) at 2 waves per SIMD: 18.0 us per launch against 25.0
 // (B = 64, 256 blocks of 4 layers, tanh); the backward 17.3 against 18.
 template <int S>
 __device__ __forceinline__ float row_lane(float v) {
