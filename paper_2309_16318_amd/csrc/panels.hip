@@ -19,7 +19,9 @@
 // value is split into three bf16 parts (round to nearest, exact: 8 + 8 + 8
 // significant bits), and of the nine products of two split values the six
 // above 2^-24 are accumulated in float32, the five small ones in an
-// accumulator of their own.  Measured on one MI355X, the six cost 32 cycles
+// accumulator of their own.  Infinities, and values that round up to one in
+// bf16, have no parts: a row of a vector that meets them is summed again in
+// plain float32.  Measured on one MI355X, the six cost 32 cycles
 // each per 32 x 32 x 16 tile against 8 x 64 cycles of float32 instructions:
 // 2.7 times the rate, with fewer roundings (one per 16 terms and part).
 #include "internal.h"
@@ -65,6 +67,9 @@ __device__ __forceinline__ Parts2 split2(float x, float y) {
     p.l = pack2(x1 - lo_f(p.m), y1 - hi_f(p.m));
     return p;
 }
+// Values from here on have no parts: they round up to an infinity.
+constexpr float kNoParts = 3.38e38f;
+
 // Eight values as three operand registers.
 struct Parts8 {
     b8 h, m, l;
@@ -120,7 +125,8 @@ struct VecShape {
     static constexpr int KT = WP / 32;             // k tiles
     static constexpr int WPG = WP / (16 * MTW);    // waves per group
     static constexpr int GPW = 4 / WPG;            // groups per workgroup
-    static constexpr int BUF = KT * 3 * 1024;      // one vector panel in LDS, bytes
+    static constexpr int RAW = KT * 3 * 1024;      // a vector panel's parts in LDS, bytes
+    static constexpr int BUF = RAW + 16 * WP * 4;  // and its float32 values
     static constexpr int LDS = GPW * 2 * BUF;
 };
 // Product panels: 32 columns of one system's P per wave, all rows.
@@ -218,6 +224,24 @@ __device__ __forceinline__ void put_panel(char* buf, int r0, int n,
     }
 }
 
+// Element k of system n of a vector panel: the sum of its parts or, where it
+// has none (infinities, NaN and what rounds up to an infinity), its float32
+// value, which vector_panel stores beside them then.
+template <int WP>
+__device__ __forceinline__ float panel_value(const char* buf, int n, int k) {
+    using S = VecShape<WP>;
+    const int u = k % 16 / 4;
+    const char* p =
+        buf + k / 32 * 1024 + (n + 16 * (2 * (k / 16 % 2) + u % 2)) * 16 + 8 * (u / 2) + 2 * (k % 4);
+    auto part = [&](int i) {
+        return __uint_as_float(
+            (unsigned)*reinterpret_cast<const unsigned short*>(p + i * S::KT * 1024) << 16);
+    };
+    const float x = part(0) + part(1) + part(2);
+    return fabsf(x) < __builtin_inff() ? x
+                                       : reinterpret_cast<const float*>(buf + S::RAW)[n * WP + k];
+}
+
 // ------------------------------------------------------------ vector panels
 // One chunk of the recurrence for 16 systems per group.  APPLY: from x_in to
 // every row; otherwise from zero to the chunk's last row, q.
@@ -310,16 +334,47 @@ __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int 
     };
     float x[NR];
     int m = m0;
-    // the B operand of row m: x, scaled by row m's own d when transposed
+    // the B operand of row m: x, scaled by row m's own d when transposed;
+    // whether all of it has parts
     auto put = [&](int buf, const float (&d)[NR]) {
-        if constexpr (BWD) {
-            float y[NR];
+        float y[NR], size = 0.f;
 #pragma unroll
-            for (int j = 0; j < NR; ++j) y[j] = d[j] * x[j];
-            put_panel<WP>(panel + buf * S::BUF, r0, n, y);
-        } else {
-            put_panel<WP>(panel + buf * S::BUF, r0, n, x);
+        for (int j = 0; j < NR; ++j) {
+            y[j] = BWD ? d[j] * x[j] : x[j];
+            size += fabsf(y[j]);
         }
+        put_panel<WP>(panel + buf * S::BUF, r0, n, y);
+        return size < kNoParts;
+    };
+    auto put_values = [&](int buf, const float (&d)[NR]) {
+        float y[NR];
+#pragma unroll
+        for (int j = 0; j < NR; ++j) y[j] = BWD ? d[j] * x[j] : x[j];
+        store_row<NR, true>(reinterpret_cast<float*>(panel + buf * S::BUF + S::RAW) + n * WP, r0,
+                            WP, y);
+    };
+    // Row m's product as plain sums from the panel `buf`, where that of the
+    // parts is not finite (a factor has none, or the sum overflows), through
+    // the space of the other panel's float32 values.  Rare: the addresses are
+    // made anew, so that nothing of it is kept in registers.
+    auto plain = [&](int m, int buf, float (&y)[NR]) {
+        int nn = n, rr = r0;
+        asm volatile("" : "+v"(nn), "+v"(rr));
+        const float* Wl = a.W + (long long)(BWD ? L - m : m) * w * w;
+        float* out = reinterpret_cast<float*>(panel + (buf ^ 1) * S::BUF + S::RAW) + nn * WP + rr;
+#pragma unroll 1
+        for (int j = 0; j < NR; ++j) {
+            float v = 0.f;
+            const int i = rr + j;
+            if (i < w)
+#pragma unroll 1
+                for (int k = 0; k < w; ++k)
+                    v = fmaf(Wl[BWD ? k * w + i : i * w + k],
+                             panel_value<WP>(panel + buf * S::BUF, nn, k), v);
+            out[j] = v;
+        }
+#pragma unroll
+        for (int j = 0; j < NR; ++j) y[j] = out[j];
     };
     {
         float d0[NR] = {}, rr[NR], z0[NR];
@@ -336,7 +391,7 @@ __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int 
             emit(m, x, z0);
             ++m;
         }
-        if (m < m1) put(0, d0);
+        if (m < m1 && __builtin_expect(!put(0, d0), 0)) put_values(0, d0);
     }
     if (m < m1) {
         unrolled<0, D>([&](auto s) { request(m + decltype(s)::value, s); });
@@ -369,19 +424,32 @@ __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int 
 #pragma unroll
                     for (int q = 0; q < S::MTW; ++q) mac(acc[q], A[q][k], p);
                 }
+                float y[NR], xp[NR];
 #pragma unroll
                 for (int q = 0; q < S::MTW; ++q)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int j = S::MTW * e + q;
-                        float y = acc[q].x[e] + acc[q].s[e];
-                        if constexpr (!BWD) y *= ad[s][j];
-                        if (a.residual) y += x[j];
-                        if constexpr (!BWD) y += ar[s][j];
-                        x[j] = EXACT || r0 + j < w ? y : 0.f;
+                    for (int e = 0; e < 4; ++e)
+                        y[S::MTW * e + q] = acc[q].x[e] + acc[q].s[e];
+#pragma unroll
+                for (int j = 0; j < NR; ++j) xp[j] = x[j];
+                auto finish = [&] {
+#pragma unroll
+                    for (int j = 0; j < NR; ++j) {
+                        float z = y[j];
+                        if constexpr (!BWD) z *= ad[s][j];
+                        if (a.residual) z += xp[j];
+                        if constexpr (!BWD) z += ar[s][j];
+                        x[j] = EXACT || r0 + j < w ? z : 0.f;
                     }
+                };
+                finish();
                 buf ^= 1;
-                put(buf, ad[s]);
+                if (__builtin_expect(!put(buf, ad[s]), 0)) {
+                    plain(row, buf ^ 1, y);
+                    finish();
+                    put(buf, ad[s]);
+                    put_values(buf, ad[s]);
+                }
                 emit(row, x, az[s]);
             });
         }
@@ -755,9 +823,8 @@ __global__ __launch_bounds__(kThr) void layer_vectors(
             for (int e = 0; e < 4; ++e) {
                 const int j = S::MTW * e + q;
                 float y = acc[q].x[e] + acc[q].s[e] + bi[j];
-                // an infinity has no split, and a value that rounds up to one
-                // none either: such a row is summed as it stands
-                if (__builtin_expect(!(fabsf(y) <= 3.0e38f), 0)) {
+                // where a factor has no parts the row is summed as it stands
+                if (__builtin_expect(!(fabsf(y) < kNoParts), 0)) {
                     const float* zp = l == 0 ? z0 : Z;
                     y = bi[j];
                     if (EXACT || r0 + j < w)
