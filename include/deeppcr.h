@@ -44,9 +44,12 @@
  *     DEEPPCR_EINVAL (or DEEPPCR_EWORKSPACE for a short workspace) and
  *     launches nothing.  A HIP runtime error returns DEEPPCR_EHIP; its text is
  *     available from deeppcr_last_error().
- *   - Arithmetic is float32 with float32 accumulation.  Where products run
- *     on the bf16 matrix cores, each float32 value is carried by three bf16
- *     parts that add up to it exactly.  Results are deterministic run to run.
+ *   - Arithmetic is float32 with float32 accumulation, over float32's whole
+ *     range.  Where products run on the bf16 matrix cores, each float32 value
+ *     is carried by three bf16 parts that add up to it exactly, after scaling
+ *     by a power of two where it is small or large (of a block's column or of
+ *     a layer's 32 rows: against the largest there); rows with infinities are
+ *     summed in plain float32.  Results are deterministic run to run.
  */
 #ifndef DEEPPCR_H
 #define DEEPPCR_H

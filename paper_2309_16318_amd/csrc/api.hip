@@ -423,7 +423,7 @@ hipError_t read_measures(const unsigned* red, unsigned* hw, hipStream_t st, unsi
 // operator buffers A, which this path does not store.
 struct PanelPlan {
     int C = 0, Lc = 0;  // C = 0: not for this shape
-    size_t P, q, xe, space;
+    size_t P, q, xe, space, scale;
     bool split = false;  // the weights are split once, at S
     size_t S;
 };
@@ -447,6 +447,7 @@ PanelPlan panel_plan(int B, int L, int w, bool bwd) {
         pl.q = off; off += nq;
         pl.xe = off; off += nq;
         pl.space = off; off += Ce > 1 ? nP / 2 : 0;
+        pl.scale = off; off += align_up(split_scales(L, w) * sizeof(float));
         if (off > lo.r[0]) continue;
         pl.S = off;
         pl.split = off + split_bytes(L, w) <= lo.r[0];
@@ -456,12 +457,15 @@ PanelPlan panel_plan(int B, int L, int w, bool bwd) {
     return pl;
 }
 
-// Splits the weights if the plan says so, once per call.
+// The weights split if the plan says so, and their factors, once per call.
 hipError_t panel_split(bool bwd, const float* W, int L, int w, const PanelPlan& pl, void* ws_base,
                        hipStream_t st) {
-    if (pl.C == 0 || !pl.split) return hipSuccess;
-    return timed(DEEPPCR_KCLASS_OTHER, 4.0 * L * w * w + (double)split_bytes(L, w), 0.0, st, [&] {
-        return launch_split_weights(bwd, W, (char*)ws_base + pl.S, L, w, st);
+    if (pl.C == 0) return hipSuccess;
+    char* base = (char*)ws_base;
+    const double bytes = 4.0 * L * w * w + (pl.split ? (double)split_bytes(L, w) : 0.0);
+    return timed(DEEPPCR_KCLASS_OTHER, bytes, 0.0, st, [&] {
+        return launch_split_weights(bwd, W, pl.split ? base + pl.S : nullptr,
+                                    (float*)(base + pl.scale), L, w, st);
     });
 }
 
@@ -474,6 +478,7 @@ hipError_t panel_solve(bool bwd, PanelArgs a, const PanelPlan& pl, void* ws_base
     a.Lc = pl.Lc;
     a.C = pl.C;
     if (pl.split) a.S = base + pl.S;
+    a.scale = (const float*)(base + pl.scale);
     a.P = (float*)(base + pl.P);
     a.q = (float*)(base + pl.q);
     float* xe = (float*)(base + pl.xe);

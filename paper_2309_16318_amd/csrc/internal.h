@@ -189,6 +189,7 @@ hipError_t launch_block_down(const BlockSrc& A, const LayerScale* y, const VecSr
 struct PanelArgs {
     const float* W;   // [L, w, w]
     const char* S;    // the weights split (launch_split_weights), or null
+    const float* scale;  // their factors (launch_split_weights)
     const float* d;   // [B, L, w] c sigma'
     const float* r;   // [B, L, w] residuals; transposed: G [B, w]
     const float* xe;  // [B, C-1, WP] solution at the chunk ends
@@ -211,9 +212,12 @@ int panel_chunks(int B, int rows, int w);
 hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, const float* z0,
                                 const float* Z, float* d, float* r, unsigned* red, bool want_max,
                                 int B, int L, int w, int layer, float alpha, hipStream_t st);
-// The weights (bwd: transposed) as bf16 parts in operand order, split_bytes.
+// The weights (bwd: transposed) as bf16 parts in operand order, split_bytes,
+// and the factors of their results, split_scales; out null: these alone.
 size_t split_bytes(int L, int w);
-hipError_t launch_split_weights(bool bwd, const float* W, char* out, int L, int w, hipStream_t st);
+size_t split_scales(int L, int w);
+hipError_t launch_split_weights(bool bwd, const float* W, char* out, float* scale, int L, int w,
+                                hipStream_t st);
 // P of chunks 1 .. C-2 and q of chunks 0 .. C-2 (C >= 2).
 hipError_t launch_chunk_pass(bool bwd, const PanelArgs& a, hipStream_t st);
 // Every row from its chunk's x_in (xe of the chunk before; 0 in the first).

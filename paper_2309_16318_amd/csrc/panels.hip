@@ -16,12 +16,11 @@
 // systems through the caches, and writes vectors only.
 //
 // All products run on the bf16 matrix cores at float32 precision: a float32
-// value is split into three bf16 parts (round to nearest, exact: 8 + 8 + 8
-// significant bits), and of the nine products of two split values the six
+// value, scaled where it is near the ends of the range, is split into three
+// bf16 parts (round to nearest, exact: 8 + 8 + 8 significant bits), and of the nine products of two split values the six
 // above 2^-24 are accumulated in float32, the five small ones in an
-// accumulator of their own.  Infinities, and values that round up to one in
-// bf16, have no parts: a row of a vector that meets them is summed again in
-// plain float32.  Measured on one MI355X, the six cost 32 cycles
+// accumulator of their own.  Infinities have no parts: a row of a vector that
+// meets one is summed again in plain float32.  Measured on one MI355X, the six cost 32 cycles
 // each per 32 x 32 x 16 tile against 8 x 64 cycles of float32 instructions:
 // 2.7 times the rate, with fewer roundings (one per 16 terms and part).
 #include "internal.h"
@@ -67,18 +66,21 @@ __device__ __forceinline__ Parts2 split2(float x, float y) {
     p.l = pack2(x1 - lo_f(p.m), y1 - hi_f(p.m));
     return p;
 }
-// Values from here on have no parts: they round up to an infinity.
-constexpr float kNoParts = 3.38e38f;
+// bf16 has float32's exponents and 16 bits less, so the parts of x add up to
+// it only if its last bit is at least 2^-133, bf16's smallest value (which the
+// matrix cores keep).  Vectors are therefore split as 2^16 x, which is exact
+// for every x below 2^111; values from 2^110 on count as having no parts.
+constexpr float kShift = 0x1p16f, kUnshift = 0x1p-16f, kNoParts = 0x1p110f;
 
 // Eight values as three operand registers.
 struct Parts8 {
     b8 h, m, l;
 };
-__device__ __forceinline__ Parts8 split8(const float (&v)[8]) {
+__device__ __forceinline__ Parts8 split8(const float (&v)[8], float shift = 1.f) {
     u4 h, m, l;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const Parts2 p = split2(v[2 * j], v[2 * j + 1]);
+        const Parts2 p = split2(shift * v[2 * j], shift * v[2 * j + 1]);
         h[j] = p.h;
         m[j] = p.m;
         l[j] = p.l;
@@ -217,7 +219,8 @@ __device__ __forceinline__ void put_panel(char* buf, int r0, int n,
     for (int j = 0; j < S::NR; j += 4) {
         const int u = (r0 % 16 + j) / 4;  // the quarter of its 16 rows
         char* p = buf + r0 / 32 * 1024 + (n + 16 * (2 * (r0 / 16 % 2) + u % 2)) * 16 + 8 * (u / 2);
-        const Parts2 a = split2(x[j], x[j + 1]), b = split2(x[j + 2], x[j + 3]);
+        const Parts2 a = split2(kShift * x[j], kShift * x[j + 1]),
+                     b = split2(kShift * x[j + 2], kShift * x[j + 3]);
         *reinterpret_cast<u2*>(p) = u2{a.h, b.h};
         *reinterpret_cast<u2*>(p + S::KT * 1024) = u2{a.m, b.m};
         *reinterpret_cast<u2*>(p + 2 * S::KT * 1024) = u2{a.l, b.l};
@@ -225,8 +228,8 @@ __device__ __forceinline__ void put_panel(char* buf, int r0, int n,
 }
 
 // Element k of system n of a vector panel: the sum of its parts or, where it
-// has none (infinities, NaN and what rounds up to an infinity), its float32
-// value, which vector_panel stores beside them then.
+// has none (infinities, NaN and the largest values), its float32 value, which
+// vector_panel stores beside them then.
 template <int WP>
 __device__ __forceinline__ float panel_value(const char* buf, int n, int k) {
     using S = VecShape<WP>;
@@ -238,7 +241,7 @@ __device__ __forceinline__ float panel_value(const char* buf, int n, int k) {
             (unsigned)*reinterpret_cast<const unsigned short*>(p + i * S::KT * 1024) << 16);
     };
     const float x = part(0) + part(1) + part(2);
-    return fabsf(x) < __builtin_inff() ? x
+    return fabsf(x) < __builtin_inff() ? kUnshift * x
                                        : reinterpret_cast<const float*>(buf + S::RAW)[n * WP + k];
 }
 
@@ -395,12 +398,28 @@ __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int 
     }
     if (m < m1) {
         unrolled<0, D>([&](auto s) { request(m + decltype(s)::value, s); });
+        // (weights out of the ordinary range are multiplied by 1 / scale)
+        const float* const scale = a.scale + base / 32;
+        bool scaled = false;
+        for (int k = m + lane; k < m1; k += 64)
+            scaled = scaled || scale[(BWD ? L - k : k) * (WP / 32)] != 1.f;
+        scaled = __builtin_amdgcn_ballot_w64(scaled) != 0;
         int buf = 0;
         for (int mb = m; mb < m1; mb += NB) {
             unrolled<0, NB>([&](auto sc) {
                 constexpr int s = decltype(sc)::value;
                 const int row = mb + s;
                 if (row >= m1) return;  // uniform over the workgroup
+                float factor = kUnshift;
+                if (__builtin_expect(scaled, 0)) {
+                    const float f = scale[(BWD ? L - row : row) * (WP / 32)];
+                    factor *= f;
+                    if constexpr (!PRE)
+#pragma unroll
+                        for (int q = 0; q < S::MTW; ++q)
+#pragma unroll
+                            for (int k = 0; k < 8 * S::KT; ++k) raw[s][q][k / 8][k % 8] *= 1.f / f;
+                }
                 Parts8 A[S::MTW][S::KT];
 #pragma unroll
                 for (int q = 0; q < S::MTW; ++q)
@@ -429,7 +448,7 @@ __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int 
                 for (int q = 0; q < S::MTW; ++q)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        y[S::MTW * e + q] = acc[q].x[e] + acc[q].s[e];
+                        y[S::MTW * e + q] = factor * (acc[q].x[e] + acc[q].s[e]);
 #pragma unroll
                 for (int j = 0; j < NR; ++j) xp[j] = x[j];
                 auto finish = [&] {
@@ -489,6 +508,9 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
     const int b = live ? bb : a.B - 1;
     const int m0 = c * a.Lc, m1 = min(a.rows, m0 + a.Lc);
     const Src<EXACT> sd(a.d, (unsigned)a.B * L * w);
+    // (weights out of the ordinary range are multiplied by 1 / scale)
+    auto scale_at = [&](int m, int mt) { return a.scale[(long long)(BWD ? L - m : m) * S::MT + mt]; };
+    bool scaled = false;
 
     // this thread's 4 x 4 weights of a stage: rows 4 rg .., columns 4 cg .. of
     // the stage's 32-row block blk
@@ -536,7 +558,8 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
     };
     char* const dst = lds + (blk * S::KT + cg / 4) * 1024 + (4 * rg + 32 * (cg & 1)) * 16 +
                       8 * ((cg >> 1) & 1);
-    auto put = [&](int buf) {
+    auto put = [&](int st) {
+        const int buf = st & 1;
         if constexpr (PRE) {
 #pragma unroll
             for (int j = 0; j < 6; ++j) {
@@ -545,6 +568,12 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
                 *reinterpret_cast<u4*>(lds + buf * S::STAGE + o) = pre[j];
             }
         } else {
+            if (__builtin_expect(scaled, 0)) {
+                const int m = min(m1 - 1, m0 + (WP == 128 ? st / 4 : WP == 64 ? st : 4 * st + blk));
+                const float f = 1.f / scale_at(m, WP == 128 ? st % 4 : WP == 64 ? blk : 0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) raw[e] *= f;
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const f4 x = BWD ? f4{raw[0][e], raw[1][e], raw[2][e], raw[3][e]} : raw[e];
@@ -578,24 +607,56 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
             for (int e = 0; e < 4; ++e) d[4 * q + e] = x[e];
         }
     };
-    // the operand parts of P (transposed system: of diag(d) P, d of the next
-    // row; before the first row P = I, scaled by the first row's d)
+    // A column of P, which a wave holds whole (lanes n and n + 32), stays within
+    // 2^-60 .. 2^60 in its largest element, so that its elements have parts and
+    // no product of a long chunk leaves the range before its end: P stands for
+    // P 2^ex.  The check is 8 maxima per 32 x 32 elements, which cost 4% of the
+    // pass at w = 32 and 1% at 128 (33.7 -> 35.1 us at B 256, L 256, w 32; 340 ->
+    // 342 us at B 16, L 1024, w 128).
+    int ex = 0;
+    auto settle = [&] {
+        // (the columns beyond w are zeros)
+        float m = EXACT || col < w ? 0.f : 1.f;
+#pragma unroll
+        for (int mt = 0; mt < S::MT; ++mt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) m = fmaxf(m, fabsf(P[mt][e]));
+        const unsigned low = __float_as_uint(0x1p-60f), high = __float_as_uint(0x1p60f);
+        if (__builtin_expect(
+                __builtin_amdgcn_ballot_w64(__float_as_uint(m) - low > high - low) != 0, 0)) {
+            m = fmaxf(m, __shfl_xor(m, 32, 64));
+            const float f = m > 0x1p60f ? 0x1p-64f : m > 0.f && m < 0x1p-60f ? 0x1p64f : 1.f;
+            ex += m > 0x1p60f ? 64 : m > 0.f && m < 0x1p-60f ? -64 : 0;
+#pragma unroll
+            for (int mt = 0; mt < S::MT; ++mt) P[mt] *= f;
+        }
+    };
+    // Transposed system: a product meets diag(d) P, d of its own row.  Without
+    // residuals P is kept as that (so that its columns are settled as they are
+    // split), with them it is needed as it is.
+    auto first_slopes = [&](int mt, float (&d)[16]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float x[4];
+            load_row<4>(sd, ((unsigned)b * L + L - m0) * w, 32 * mt + 8 * q + 4 * h, w, x);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) d[4 * q + e] = x[e];
+        }
+    };
     auto operands = [&](const float* dd, bool first) {
+        settle();
 #pragma unroll
         for (int mt = 0; mt < S::MT; ++mt) {
             float d[16];
             if constexpr (BWD) {
-                if (first)
+                if (!a.residual) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float x[4];
-                        load_row<4>(sd, ((unsigned)b * L + L - m0) * w, 32 * mt + 8 * q + 4 * h, w,
-                                    x);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) d[4 * q + e] = x[e];
-                    }
-                else
+                    for (int e = 0; e < 16; ++e) d[e] = 1.f;
+                } else if (first) {
+                    first_slopes(mt, d);
+                } else {
                     scale(dd, mt, d);
+                }
             }
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
@@ -609,9 +670,20 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
             }
         }
     };
+    if (BWD && !a.residual)
+#pragma unroll
+        for (int mt = 0; mt < S::MT; ++mt) {
+            float d[16];
+            first_slopes(mt, d);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) P[mt][e] *= d[e];
+        }
     const float* const dbase =
         reinterpret_cast<const float*>(lds + S::WB) + v / S::MT * WP + 4 * h;
     request(0);
+    for (int k = m0 * S::MT + lane; k < m1 * S::MT; k += 64)
+        scaled = scaled || scale_at(k / S::MT, k % S::MT) != 1.f;
+    scaled = __builtin_amdgcn_ballot_w64(scaled) != 0;
     put(0);
     request(1);
     operands(nullptr, true);
@@ -636,7 +708,7 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
             A.h = *reinterpret_cast<const b8*>(in);
             if (SPL == 4 || (mt == 0 && (m - m0) % LPS == 0)) {
                 // (past the last stage: its weights again, never read)
-                put((st + 1) & 1);
+                put(st + 1);
                 request(st + 2);
             }
             constexpr int kMove = 0x2 | 0x4 | 0x10 | 0x200;
@@ -657,6 +729,11 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
                 if (more) A.h = *reinterpret_cast<const b8*>(next);
                 __builtin_amdgcn_sched_barrier(kMove);
             }
+            if (__builtin_expect(scaled, 0)) {
+                const float f = scale_at(m, mt);
+                acc.x *= f;
+                acc.s *= f;
+            }
             float d[16];
             if constexpr (!BWD) scale(dd, mt, d);
             if (a.residual) {
@@ -665,9 +742,16 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
                     P[mt][e] = BWD ? P[mt][e] + (acc.x[e] + acc.s[e])
                                    : fmaf(d[e], acc.x[e] + acc.s[e], P[mt][e]);
             } else {
+                if constexpr (BWD) {
+                    if (m + 1 < m1) {
+                        scale(dd, mt, d);
+                    } else {
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    P[mt][e] = BWD ? acc.x[e] + acc.s[e] : d[e] * (acc.x[e] + acc.s[e]);
+                        for (int e = 0; e < 16; ++e) d[e] = 1.f;
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e) P[mt][e] = d[e] * (acc.x[e] + acc.s[e]);
             }
         }
         const int last = st0 + SPL - 1;
@@ -675,6 +759,11 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
             operands(dbase + (last & 1) * (S::STAGE / 4) + 128 * ((m - m0) % LPS), false);
     }
     if (!live) return;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(ex != 0) != 0, 0))
+#pragma unroll
+        for (int mt = 0; mt < S::MT; ++mt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) P[mt][e] = ldexpf(P[mt][e], ex);
     float* out = a.P + ((long long)b * (a.C - 1) + c) * WP * WP + col;
 #pragma unroll
     for (int mt = 0; mt < S::MT; ++mt)
@@ -713,11 +802,15 @@ __global__ __launch_bounds__(kThr) void apply_pass(PanelArgs a) {
 }
 
 // ------------------------------------------------------------ split weights
-// The tiles of SplitShape from W (BWD: of W^T), 4 x 4 weights per thread.
+// The tiles of SplitShape from W (BWD: of W^T), 4 x 4 weights per thread, and
+// per layer and 32 rows the factor that the results are to be multiplied by:
+// 1, unless the largest weight of these rows is below 2^-60 or from 2^60 on.
+// Without `out`, the factors alone.
 template <int WP, bool BWD, bool EXACT>
 __global__ __launch_bounds__(kThr) void split_weights(const float* __restrict__ W,
-                                                      char* __restrict__ out, int L, int w_) {
-    constexpr int UNITS = WP * WP / 16;
+                                                      char* __restrict__ out, float* __restrict__ scale,
+                                                      int L, int w_) {
+    constexpr int UNITS = WP * WP / 16, WAVES = WP / 32;  // threads per layer, waves per 32 rows
     const int w = EXACT ? WP : w_;
     const int id = blockIdx.x * kThr + threadIdx.x;
     const int l = __builtin_amdgcn_readfirstlane(id / UNITS), u = id % UNITS;
@@ -732,6 +825,26 @@ __global__ __launch_bounds__(kThr) void split_weights(const float* __restrict__ 
         load_row<4>(Wl, ((BWD ? k : i) + e) * w, BWD ? i : k, w, x);
         raw[e] = f4{x[0], x[1], x[2], x[3]};
     }
+    unsigned big = 0u;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) big = max(big, __float_as_uint(fabsf(raw[e / 4][e % 4])));
+    for (int off = 32; off > 0; off >>= 1)
+        big = max(big, (unsigned)__shfl_xor((int)big, off, 64));
+    if constexpr (WAVES > 1) {  // (all of a workgroup has a layer, or none)
+        __shared__ unsigned part[4];
+        const int v = threadIdx.x >> 6;
+        if ((threadIdx.x & 63) == 0) part[v] = big;
+        __syncthreads();
+        for (int k = 0; k < WAVES; ++k) big = max(big, part[v / WAVES * WAVES + k]);
+    }
+    const float m = __uint_as_float(big);
+    const float f = m >= 0x1p60f && m < __builtin_inff() ? 0x1p-64f
+                    : m > 0.f && m < 0x1p-60f            ? 0x1p64f
+                                                         : 1.f;
+    if (u % (2 * WP) == 0) scale[(long long)l * (WP / 32) + mt] = 1.f / f;
+    if (!out) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) raw[e] *= f;
     char* dst = out + (long long)l * SplitShape<WP>::LAYER +
                 (WP == 128 ? mt * SplitShape<WP>::SLICE : mt * (WP / 16) * 1024) + cg / 4 * 1024 +
                 (4 * rg + 32 * (cg & 1)) * 16 + 8 * ((cg >> 1) & 1);
@@ -790,7 +903,7 @@ __global__ __launch_bounds__(kThr) void layer_vectors(
 #pragma unroll
             for (int q = 0; q < S::MTW; ++q)
 #pragma unroll
-                for (int k = 0; k < S::KT; ++k) A[q][k] = split8(raw[q][k]);
+                for (int k = 0; k < S::KT; ++k) A[q][k] = split8(raw[q][k], kShift);
             have = l;
         }
         const int bb = gr * 16 + n;
@@ -812,7 +925,7 @@ __global__ __launch_bounds__(kThr) void layer_vectors(
         Acc<f4> acc[S::MTW] = {};
 #pragma unroll
         for (int k = 0; k < S::KT; ++k) {
-            const Parts8 p = split8(x[k]);
+            const Parts8 p = split8(x[k], kShift);
 #pragma unroll
             for (int q = 0; q < S::MTW; ++q) mac(acc[q], A[q][k], p);
         }
@@ -822,9 +935,10 @@ __global__ __launch_bounds__(kThr) void layer_vectors(
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int j = S::MTW * e + q;
-                float y = acc[q].x[e] + acc[q].s[e] + bi[j];
-                // where a factor has no parts the row is summed as it stands
-                if (__builtin_expect(!(fabsf(y) < kNoParts), 0)) {
+                float y = fmaf(acc[q].x[e] + acc[q].s[e], kUnshift * kUnshift, bi[j]);
+                // where a factor has no parts, or the sum no shift, the row is
+                // summed as it stands
+                if (__builtin_expect(!(fabsf(y) < __builtin_inff()), 0)) {
                     const float* zp = l == 0 ? z0 : Z;
                     y = bi[j];
                     if (EXACT || r0 + j < w)
@@ -950,13 +1064,14 @@ hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, con
 }
 
 size_t split_bytes(int L, int w) { return (size_t)L * padded(w) * padded(w) * 6; }
+size_t split_scales(int L, int w) { return (size_t)L * (padded(w) / 32); }
 
-hipError_t launch_split_weights(bool bwd, const float* W, char* out, int L, int w,
+hipError_t launch_split_weights(bool bwd, const float* W, char* out, float* scale, int L, int w,
                                 hipStream_t st) {
     const int WP = padded(w), a_w = w;
     const long long grid = ((long long)L * WP * WP / 16 + kThr - 1) / kThr;
-    if (bwd) DEEPPCR_PANEL(SPLIT_B, grid, W, out, L, w);
-    else DEEPPCR_PANEL(SPLIT_F, grid, W, out, L, w);
+    if (bwd) DEEPPCR_PANEL(SPLIT_B, grid, W, out, scale, L, w);
+    else DEEPPCR_PANEL(SPLIT_F, grid, W, out, scale, L, w);
     return hipGetLastError();
 }
 
