@@ -600,12 +600,36 @@ double block_plan(int B, int L, int w, BlockPlan* plan) {
         }                                         \
     } while (0)
 
-hipError_t launch_block_up(const BlockSrc& A, const LayerScale* y, const VecSrc& r, float* P,
-                           float* q, int B, int L, int w, int Lc, int C, hipStream_t st) {
-    if (y && w > 16) return hipErrorInvalidValue;
-    const LayerScale ly = y ? *y : LayerScale{};
-    // (items beyond 2^31 would need a workspace beyond the card's memory)
-    const int items = (int)((long long)B * (C - 1));
+// A launch has at most 2^32 - 1 threads: more systems than that takes go in
+// several, launch(first system, systems).
+template <class F>
+static hipError_t by_systems(int B, long long threads_per_system, F&& launch) {
+    const long long most = 0xffffffffLL / threads_per_system;
+    if (most < 1) return hipErrorInvalidValue;
+    for (long long b = 0; b < B; b += most) {
+        const hipError_t e = launch(b, (int)(B - b < most ? B - b : most));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+static BlockSrc from(const BlockSrc& A, long long b) {
+    return {A.base + b * A.bstride, A.bstride, A.rstride, A.trans};
+}
+static VecSrc from(const VecSrc& v, long long b) {
+    return {v.base + b * v.bstride, v.bstride, v.rstride};
+}
+static VecDst from(const VecDst& v, long long b) {
+    return {v.base + b * v.bstride, v.bstride, v.rstride};
+}
+static LayerScale from(const LayerScale* y, long long b) {
+    return y ? LayerScale{y->d + b * y->bstride, y->bstride, y->rstride, y->residual}
+             : LayerScale{};
+}
+
+static hipError_t block_up_some(const BlockSrc& A, const LayerScale* y, const LayerScale& ly,
+                                const VecSrc& r, float* P, float* q, int B, int L, int w, int Lc,
+                                int C, hipStream_t st) {
+    const int items = B * (C - 1);
     const int WP = block_pad(w), per = WP == 16 ? 1 : 128 / WP;
     const dim3 grid((unsigned)((items + per - 1) / per));
 #define UP16_AS(T, EX, LY) \
@@ -629,11 +653,20 @@ hipError_t launch_block_up(const BlockSrc& A, const LayerScale* y, const VecSrc&
     return hipGetLastError();
 }
 
-hipError_t launch_block_down(const BlockSrc& A, const LayerScale* y, const VecSrc& r,
-                             const VecDst& x, const float* xe, const float* P, unsigned* red,
-                             int B, int L, int w, int Lc, int C, hipStream_t st) {
+hipError_t launch_block_up(const BlockSrc& A, const LayerScale* y, const VecSrc& r, float* P,
+                           float* q, int B, int L, int w, int Lc, int C, hipStream_t st) {
     if (y && w > 16) return hipErrorInvalidValue;
-    const LayerScale ly = y ? *y : LayerScale{};
+    const long long ends = C - 1;
+    return by_systems(B, ends * (w <= 16 ? 64 : 256), [&](long long b, int n) {
+        return block_up_some(from(A, b), y, from(y, b), from(r, b), P + b * ends * w * w,
+                             q + b * ends * w, n, L, w, Lc, C, st);
+    });
+}
+
+static hipError_t block_down_some(const BlockSrc& A, const LayerScale* y, const LayerScale& ly,
+                                  const VecSrc& r, const VecDst& x, const float* xe,
+                                  const float* P, unsigned* red, int B, int L, int w, int Lc,
+                                  int C, hipStream_t st) {
     const dim3 grid((unsigned)((long long)B * C));
 #define DOWN_AS(K, NT)                                                                         \
     hipLaunchKernelGGL(K, grid, dim3(NT), 0, st, A, r, x, xe, P, red, L, w, Lc, C)
@@ -663,6 +696,19 @@ hipError_t launch_block_down(const BlockSrc& A, const LayerScale* y, const VecSr
 #undef DOWN16_AS
 #undef DOWN_AS
     return hipGetLastError();
+}
+
+hipError_t launch_block_down(const BlockSrc& A, const LayerScale* y, const VecSrc& r,
+                             const VecDst& x, const float* xe, const float* P, unsigned* red,
+                             int B, int L, int w, int Lc, int C, hipStream_t st) {
+    if (y && w > 16) return hipErrorInvalidValue;
+    const long long ends = C - 1;
+    return by_systems(B, (long long)C * (w <= 16 ? 64 : w <= 64 ? 256 : 1024),
+                      [&](long long b, int n) {
+        return block_down_some(from(A, b), y, from(y, b), from(r, b), from(x, b),
+                               xe ? xe + b * ends * w : nullptr,
+                               P ? P + b * ends * w * w : nullptr, red, n, L, w, Lc, C, st);
+    });
 }
 
 }  // namespace deeppcr

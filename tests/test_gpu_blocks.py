@@ -90,3 +90,19 @@ def test_layer_blocks(dev, w, B, L, layer, alpha):
     assert normwise_rel_err(got, np.concatenate([rz[:, None], rl], 1)) <= tol
     assert normwise_rel_err(dW.cpu().numpy(), rW, axes="all") <= tol
     assert normwise_rel_err(db.cpu().numpy(), rb, axes="all") <= tol
+
+
+@pytest.mark.parametrize("L", [2, 3])
+def test_many_systems(dev, L):
+    """More systems of width 4 than one launch has threads for (64 each, of
+    2^32 - 1): copies of 1024 different ones, all with the same solution."""
+    print(f"blocks: 2^26 + 1024 systems, L={L}", flush=True)
+    B = 2 ** 26 + 1024
+    d = synth.random_system(1024, L, 4, seed=11 + L, scale=0.9)
+    J, r = (torch.from_numpy(d[k]).to(dev)[None].expand(B // 1024, *[-1] * d[k].ndim)
+            .reshape(B, *d[k].shape[1:]).contiguous() for k in ("J", "r"))
+    x = deeppcr.pcr_solve_block_bidiag(J, r).view(B // 1024, 1024, L, 4)
+    assert bool((x == x[:1]).all())
+    assert normwise_rel_err(x[0].cpu().numpy(), oracle.seq_solve(d["J"], d["r"])) <= 40 * 2.0 ** -24
+    del J, r, x
+    torch.cuda.empty_cache()
