@@ -432,8 +432,6 @@ PanelPlan panel_plan(int B, int L, int w, bool bwd) {
     PanelPlan pl;
     if (!panel_width(w)) return pl;
     const int WP = panel_pad(w);
-    // rows that are not whole 16-byte vectors are addressed by 32-bit bytes
-    if (w != WP && (double)B * L * w >= (double)(1 << 30)) return pl;
     const int rows = L + (bwd ? 1 : 0);
     const Layout lo = layout(bwd ? DEEPPCR_OP_BWD : DEEPPCR_OP_FWD, B, L, w);
     for (int C = panel_chunks(B, rows, w); C > 0; C = C * 3 / 4) {
@@ -508,9 +506,7 @@ hipError_t panel_solve(bool bwd, PanelArgs a, const PanelPlan& pl, void* ws_base
 
 // MLP layers of widths up to 16 whose blocks the chunked solve forms from the
 // weights as it goes.
-bool layer_blocks(int B, int L, int w) {
-    return w > 8 && w <= 16 && (double)B * L * w < (double)(1 << 30);
-}
+bool layer_blocks(int w) { return w > 8 && w <= 16; }
 
 // Argument checks shared by the two forward entry points.
 int check_forward_args(const float* W, const float* bias, const float* z0, float* Z,
@@ -589,7 +585,7 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
     const VecDst xd{ws.r[(num_levels(L) + 1) & 1], (long long)L * w, (long long)w};
     const PanelPlan pl = panel_plan(B, L, w, false);
     DEEPPCR_HIP(panel_split(false, W, L, w, pl, workspace, st));
-    const bool layers16 = layer_blocks(B, L, w);
+    const bool layers16 = layer_blocks(w);
     const bool wide_sub = wide_width(w) && wide_substitution(B, L, w);
     unsigned* fslots = ws.red + kRedF;
     if (rule.residual) {
@@ -1094,7 +1090,7 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
         if (e != hipSuccess) return hip_fail(e, "wgrad");
         return DEEPPCR_OK;
     }
-    if (layer_blocks(B, L, w)) {
+    if (layer_blocks(w)) {
         hipError_t e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 2.0 * B * L * w),
                              2.0 * B * L * w2, st, [&] {
             return launch_layer_vectors(true, W, bias, z0, Z, ws.dscale, nullptr, nullptr, false,
@@ -1146,8 +1142,7 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
     });
     if (e != hipSuccess) return hip_fail(e, "backward_assemble");
     const VecDst lam{Lambda + (long long)(L - 1) * w, (long long)L * w, -(long long)w};
-    e = pcr_sweep(BlockSrc{ws.A[1], (long long)L * w * w, (long long)w * w,
-                           backward_blocks_transposed(w) ? 1 : 0},
+    e = pcr_sweep(BlockSrc{ws.A[1], (long long)L * w * w, (long long)w * w, 1},
                   VecSrc{ws.r[1], (long long)L * w, (long long)w}, lam, B, L, w, ws.A, ws.r, st);
     if (e != hipSuccess) return hip_fail(e, "pcr_sweep");
     e = timed(DEEPPCR_KCLASS_OTHER, 4.0 * (w2 + 3.0 * B * w), 2.0 * B * w2, st, [&] {

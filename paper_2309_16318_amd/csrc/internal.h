@@ -84,7 +84,8 @@ struct VecDst {
 // (z0[b] for l = 0), write r[b,l] = f_l(Zprev) - Z[b,l] and, for l >= 1,
 // the Jacobian block J_l into A ([B, L, w, w], forward row order).  The grid
 // also clears the max|dZ| and max|Z| slots of `red` and reduces max|r| into
-// its kRedF slots.
+// its kRedF slots.  Widths up to 8 and above kMaxWidth (launch_layer_vectors
+// has the others).
 hipError_t launch_forward_eval(const float* W, const float* bias, const float* z0,
                                const float* Z, float* A, float* r, unsigned* red,
                                int B, int L, int w, int layer, float alpha,
@@ -102,11 +103,9 @@ hipError_t launch_update_reduce(float* Z, const float* x, long long n, unsigned*
                                 hipStream_t stream);
 
 // Backward: Jacobian blocks of the transposed system in reversed row order,
-// blocks[m = L-l] = J_l^T for l >= 1 (stored as J_l itself, i.e. to be read
-// transposed, when backward_blocks_transposed(w)), right-hand side
-// rrev[m] = G if m == 0 else 0, and dscale[b, l] = c * (1 - tanh(a_l)^2) in
-// natural order.  For w = 16, 32, 64, 128 a null `blocks` skips the blocks.
-bool backward_blocks_transposed(int w);
+// A[m = L-l] = J_l^T for l >= 1 (stored as J_l itself, i.e. to be read
+// transposed), right-hand side rrev[m] = G if m == 0 else 0, and dscale[b, l]
+// = c sigma'(a_l) in natural order; widths as launch_forward_eval.
 hipError_t launch_backward_assemble(const float* W, const float* bias, const float* z0,
                                     const float* Z, const float* G, float* A, float* rrev,
                                     float* dscale, int B, int L, int w, int layer,

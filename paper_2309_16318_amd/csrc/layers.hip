@@ -25,66 +25,7 @@ __device__ inline unsigned wave_umax(unsigned v) {
     return v;
 }
 
-// a_i = sum_j W[i][j] z[j] + b[i] for all rows i < w; one wave per row,
-// lanes stride over j.  z lives in LDS.  Results go to out[i] in LDS.
-__device__ inline void preactivations(const float* __restrict__ Wl, const float* __restrict__ bl,
-                                      const float* z, float* out, int w) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i = wave; i < w; i += kWaves) {
-        float acc = 0.f;
-        for (int j = lane; j < w; j += 64) acc = fmaf(Wl[(long long)i * w + j], z[j], acc);
-        acc = wave_sum(acc);
-        if (lane == 0) out[i] = acc + bl[i];
-    }
-}
-
 // ---------------------------------------------------------------- forward
-__global__ __launch_bounds__(kThreads) void forward_eval_kernel(
-    const float* __restrict__ W, const float* __restrict__ bias, const float* __restrict__ z0,
-    const float* __restrict__ Z, float* __restrict__ A, float* __restrict__ r,
-    unsigned* __restrict__ red, int L, int w, int layer, float alpha) {
-    const long long row = blockIdx.x;
-    const int l = (int)(row % L);
-    const int b = (int)(row / L);
-    const int t = threadIdx.x;
-    if (row == 0)
-        for (int k = t; k < 2 * kRedShards; k += kThreads) red[k] = 0u;
-
-    __shared__ float zp[kMaxWidth];
-    __shared__ float a[kMaxWidth];
-    __shared__ float dsc[kMaxWidth];
-    const float* zprev = (l == 0) ? z0 + (long long)b * w : Z + (row - 1) * w;
-    for (int i = t; i < w; i += kThreads) zp[i] = zprev[i];
-    __syncthreads();
-    const float* Wl = W + (long long)l * w * w;
-    preactivations(Wl, bias + (long long)l * w, zp, a, w);
-    __syncthreads();
-    const bool res = layer_residual(layer);
-    unsigned mr = 0u;  // max |r| bits
-    for (int i = t; i < w; i += kThreads) {
-        float d;
-        const float y = activate(layer, a[i], &d);
-        const float f = res ? fmaf(alpha, y, zp[i]) : y;
-        const float rv = f - Z[row * w + i];
-        r[row * w + i] = rv;
-        mr = max(mr, __float_as_uint(fabsf(rv)));
-        dsc[i] = res ? alpha * d : d;
-    }
-    if ((t >> 6) * 64 < w) {  // waves holding residual elements
-        mr = wave_umax(mr);
-        if ((t & 63) == 0) atomicMax(red + kRedF + (int)(row % kRedShards), mr);
-    }
-    __syncthreads();
-    if (l == 0) return;
-    float* Ab = A + row * w * w;
-    for (int idx = t; idx < w * w; idx += kThreads) {
-        const int i = idx / w, j = idx - (idx / w) * w;
-        float v = dsc[i] * Wl[idx];
-        if (res && i == j) v += 1.f;
-        Ab[idx] = v;
-    }
-}
-
 // Bound by the latency of reading W_0 and by its stores: up to 16 lanes share a
 // row and the rows go out 16 bytes at a time (B 256, L 256, w 32: 15.2 us with
 // a wave per row, single words and a division each, now 7.7; B 16, L 1024,
@@ -163,45 +104,6 @@ __global__ __launch_bounds__(kThreads) void update_reduce_kernel(
 }
 
 // --------------------------------------------------------------- backward
-__global__ __launch_bounds__(kThreads) void backward_assemble_kernel(
-    const float* __restrict__ W, const float* __restrict__ bias, const float* __restrict__ z0,
-    const float* __restrict__ Z, const float* __restrict__ G, float* __restrict__ A,
-    float* __restrict__ rrev, float* __restrict__ dscale, int L, int w, int layer, float alpha) {
-    const long long row = blockIdx.x;  // natural (b, l)
-    const int l = (int)(row % L);
-    const int b = (int)(row / L);
-    const int t = threadIdx.x;
-    __shared__ float zp[kMaxWidth];
-    __shared__ float a[kMaxWidth];
-    __shared__ float dsc[kMaxWidth];
-    const float* zprev = (l == 0) ? z0 + (long long)b * w : Z + (row - 1) * w;
-    for (int i = t; i < w; i += kThreads) zp[i] = zprev[i];
-    __syncthreads();
-    const float* Wl = W + (long long)l * w * w;
-    preactivations(Wl, bias + (long long)l * w, zp, a, w);
-    __syncthreads();
-    const int m = L - 1 - l;  // reversed row of this layer's adjoint
-    const bool res = layer_residual(layer);
-    for (int i = t; i < w; i += kThreads) {
-        float d;
-        activate(layer, a[i], &d);
-        const float c = res ? alpha * d : d;
-        dsc[i] = c;
-        dscale[row * w + i] = c;
-        rrev[((long long)b * L + m) * w + i] = (m == 0) ? G[(long long)b * w + i] : 0.f;
-    }
-    __syncthreads();
-    if (l == 0) return;
-    // Reversed row L - l holds J_l^T: element (i, k) = J_l[k][i] = dsc[k] W_l[k][i] (+ delta).
-    float* Ab = A + ((long long)b * L + (L - l)) * w * w;
-    for (int idx = t; idx < w * w; idx += kThreads) {
-        const int i = idx / w, k = idx - (idx / w) * w;
-        float v = dsc[k] * Wl[(long long)k * w + i];
-        if (res && i == k) v += 1.f;
-        Ab[idx] = v;
-    }
-}
-
 __global__ __launch_bounds__(kThreads) void dz0_kernel(
     const float* __restrict__ W, const float* __restrict__ dscale, const float* __restrict__ Lambda,
     float* __restrict__ dz0, int L, int w, int layer) {
@@ -455,15 +357,8 @@ hipError_t launch_forward_eval(const float* W, const float* bias, const float* z
     if (small_width(w))
         return launch_eval_small(false, W, bias, z0, Z, nullptr, A, r, nullptr, red, B, L, w,
                                  layer, alpha, stream);
-    if (wide_width(w))
-        return launch_forward_eval_wide(W, bias, z0, Z, A, r, red, B, L, w, layer, alpha, stream);
-    hipLaunchKernelGGL(forward_eval_kernel, dim3((unsigned)((long long)B * L)), dim3(kThreads), 0,
-                       stream, W, bias, z0, Z, A, r, red, L, w, layer, alpha);
-    return hipGetLastError();
-}
-
-bool backward_blocks_transposed(int w) {
-    return small_width(w) || wide_width(w);
+    if (!wide_width(w)) return hipErrorInvalidValue;
+    return launch_forward_eval_wide(W, bias, z0, Z, A, r, red, B, L, w, layer, alpha, stream);
 }
 
 hipError_t launch_initial_guess(const float* W, const float* bias, const float* z0, float* Z,
@@ -496,13 +391,9 @@ hipError_t launch_backward_assemble(const float* W, const float* bias, const flo
     if (small_width(w))
         return launch_eval_small(true, W, bias, z0, Z, G, A, rrev, dscale, nullptr, B, L, w,
                                  layer, alpha, stream);
-    if (wide_width(w))
-        return launch_backward_assemble_wide(W, bias, z0, Z, G, A, rrev, dscale, B, L, w, layer,
-                                             alpha, stream);
-    hipLaunchKernelGGL(backward_assemble_kernel, dim3((unsigned)((long long)B * L)),
-                       dim3(kThreads), 0, stream, W, bias, z0, Z, G, A, rrev, dscale, L, w,
-                       layer, alpha);
-    return hipGetLastError();
+    if (!wide_width(w)) return hipErrorInvalidValue;
+    return launch_backward_assemble_wide(W, bias, z0, Z, G, A, rrev, dscale, B, L, w, layer,
+                                         alpha, stream);
 }
 
 hipError_t launch_dz0(const float* W, const float* dscale, const float* Lambda, float* dz0,

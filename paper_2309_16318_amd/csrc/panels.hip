@@ -1044,9 +1044,42 @@ int panel_chunks(int B, int rows, int w) {
     return best;
 }
 
-hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, const float* z0,
-                                const float* Z, float* d, float* r, unsigned* red, bool want_max,
-                                int B, int L, int w, int layer, float alpha, hipStream_t st) {
+// The kernels address the vectors of a batch by 32-bit bytes: more systems
+// than that takes go in several launches, launch(first system, systems).
+template <class F>
+static hipError_t by_systems(int B, int L, int w, F&& launch) {
+    const long long most = ((1LL << 30) - 1) / ((long long)L * w);
+    if (most < 1) return hipErrorInvalidValue;
+    for (long long b = 0; b < B; b += most) {
+        const hipError_t e = launch(b, (int)(B - b < most ? B - b : most));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+// The arguments of systems b .. b + n - 1.
+static PanelArgs systems(PanelArgs a, bool bwd, long long b, int n) {
+    const long long v = b * a.L * a.w, WP = padded(a.w), ends = b * (a.C - 1) * WP;
+    a.d += v;
+    a.r += bwd ? b * a.w : v;
+    if (bwd) {
+        a.Lambda += v;
+        a.dz0 += b * a.w;
+    } else {
+        a.Z += v;
+    }
+    if (a.C > 1) {
+        a.P += ends * WP;
+        a.q += ends;
+        if (a.xe) a.xe += ends;
+    }
+    a.B = n;
+    return a;
+}
+
+static hipError_t layer_vectors_some(bool bwd, const float* W, const float* bias, const float* z0,
+                                     const float* Z, float* d, float* r, unsigned* red,
+                                     bool want_max, int B, int L, int w, int layer, float alpha,
+                                     hipStream_t st) {
     // one item per group of waves, or up to 2048 workgroups
     const int WP = padded(w), groups = WP == 32 ? 2 : 1;
     const int items = L * ((B + 15) / 16);
@@ -1063,6 +1096,16 @@ hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, con
     return hipGetLastError();
 }
 
+hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, const float* z0,
+                                const float* Z, float* d, float* r, unsigned* red, bool want_max,
+                                int B, int L, int w, int layer, float alpha, hipStream_t st) {
+    return by_systems(B, L, w, [&](long long b, int n) {
+        const long long v = b * L * w;
+        return layer_vectors_some(bwd, W, bias, z0 + b * w, Z + v, d + v, bwd ? r : r + v, red,
+                                  want_max, n, L, w, layer, alpha, st);
+    });
+}
+
 size_t split_bytes(int L, int w) { return (size_t)L * padded(w) * padded(w) * 6; }
 size_t split_scales(int L, int w) { return (size_t)L * (padded(w) / 32); }
 
@@ -1075,7 +1118,7 @@ hipError_t launch_split_weights(bool bwd, const float* W, char* out, float* scal
     return hipGetLastError();
 }
 
-hipError_t launch_chunk_pass(bool bwd, const PanelArgs& a, hipStream_t st) {
+static hipError_t chunk_pass_some(bool bwd, const PanelArgs& a, hipStream_t st) {
     const int WP = padded(a.w), a_w = a.w;
     const long long nv = (long long)vector_groups(a.B, WP) * (a.C - 1);
     const long long np = (long long)product_groups(a.B, WP) * (a.C - 2);
@@ -1087,7 +1130,7 @@ hipError_t launch_chunk_pass(bool bwd, const PanelArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_apply_pass(bool bwd, const PanelArgs& a, hipStream_t st) {
+static hipError_t apply_pass_some(bool bwd, const PanelArgs& a, hipStream_t st) {
     const int a_w = a.w;
     const long long grid = (long long)vector_groups(a.B, padded(a.w)) * a.C;
     if (bwd && a.S) DEEPPCR_PANEL(APPLY_BP, grid, a);
@@ -1095,6 +1138,18 @@ hipError_t launch_apply_pass(bool bwd, const PanelArgs& a, hipStream_t st) {
     else if (a.S) DEEPPCR_PANEL(APPLY_FP, grid, a);
     else DEEPPCR_PANEL(APPLY_F, grid, a);
     return hipGetLastError();
+}
+
+hipError_t launch_chunk_pass(bool bwd, const PanelArgs& a, hipStream_t st) {
+    return by_systems(a.B, a.L, a.w, [&](long long b, int n) {
+        return chunk_pass_some(bwd, systems(a, bwd, b, n), st);
+    });
+}
+
+hipError_t launch_apply_pass(bool bwd, const PanelArgs& a, hipStream_t st) {
+    return by_systems(a.B, a.L, a.w, [&](long long b, int n) {
+        return apply_pass_some(bwd, systems(a, bwd, b, n), st);
+    });
 }
 
 }  // namespace deeppcr
