@@ -150,21 +150,26 @@ def test_wide_newton_step_generic(dev):
 
 
 def test_wide_forward_iterations_past_the_watch(dev):
-    """Newton iterations long enough (w = 1024, L = 96, B = 1: about ten
-    milliseconds each) that the host's 5 ms watch of the measures word runs
-    out and the read-back falls back to waiting for the stream: the same
-    solution and iteration count as the oracle's Newton run."""
+    """A first Newton iteration that waits for work put on the stream before it
+    (some 50 ms of matrix products), so that the host's 5 ms watch of the
+    measures word runs out and the read-back falls back to waiting for the
+    stream: the same solution and iteration count as the oracle's Newton run."""
     import time
     B, L, w, layer = 1, 96, 1024, 1
     d = synth.mlp_inputs(B, L, w, seed=9400)
     t = {k: g(v, dev) for k, v in d.items()}
     deeppcr.deeppcr_mlp_forward(t["W"], t["bias"], t["z0"], layer=layer, alpha=0.1, tol=0.0,
                                 max_iter=1)
+    a = torch.full((8192, 8192), 1e-4, device=dev)
+    a = a @ a
     torch.cuda.synchronize()
+    for _ in range(6):
+        a = a @ a
     t0 = time.perf_counter()
     res = deeppcr.deeppcr_mlp_forward(t["W"], t["bias"], t["z0"], layer=layer, alpha=0.1,
                                       tol=1e-5, max_iter=20)
     ms = (time.perf_counter() - t0) * 1e3
+    assert ms > 15.0, "the first iteration was not held up long enough"
     assert res.status == deeppcr.OK
     ref = oracle.seq_forward(layer, 0.1, d["W"], d["bias"], d["z0"])
     err = normwise_rel_err(h(res.Z), ref)
@@ -173,3 +178,60 @@ def test_wide_forward_iterations_past_the_watch(dev):
          f"err {err:.2e}, oracle {k_ref}")
     assert err <= TOL
     assert ok and abs(res.iters - k_ref) <= 1
+
+
+def solve_classes(call):
+    """The result of `call` and the launches of the two solve classes in it."""
+    names = deeppcr.KCLASS_NAMES
+    deeppcr.profile_reset()
+    deeppcr.profile_enable(True)
+    try:
+        out = call()
+        torch.cuda.synchronize()
+    finally:
+        deeppcr.profile_enable(False)
+    n = [deeppcr.profile_read(names.index(c))["launches"] for c in ("pcr_level", "pcr_tail")]
+    deeppcr.profile_reset()
+    return out, n
+
+
+def check_solve_classes(n, rows):
+    """Row by row: a launch per row and no PCR level; by levels: the reverse."""
+    assert (n[0] == 0 and n[1] > 0) if rows else (n[0] > 0 and n[1] == 0), n
+
+
+# (w, L, B, whether the solves go row by row): both sides of the rule; more
+# systems than the 8 of a workgroup's tile; tiles of 2 to 8 systems per row
+# step, the last of them not full
+BOTH_SOLVES = [(129, 128, 1, False), (160, 130, 1, False), (256, 260, 1, False),
+               (129, 40, 1, True), (132, 9, 11, True), (129, 5, 65, True), (131, 4, 230, True),
+               (130, 3, 500, True), (512, 6, 35, True)]
+
+
+@pytest.mark.parametrize("w,L,B,rows", BOTH_SOLVES)
+@pytest.mark.parametrize("layer,alpha", [(0, 1.0), (1, 0.1)])
+def test_wide_both_solves(dev, w, L, B, rows, layer, alpha):
+    """Forward by both stopping rules and backward, each by the solve it is
+    meant to show."""
+    _say(f"wide solves w={w} L={L} B={B} rows={rows} layer={layer}")
+    d = synth.mlp_inputs(B, L, w, seed=9500 + w + L + layer)
+    t = {k: g(v, dev) for k, v in d.items()}
+    ref = oracle.seq_forward(layer, alpha, d["W"], d["bias"], d["z0"])
+    res, n = solve_classes(lambda: deeppcr.deeppcr_mlp_forward(
+        t["W"], t["bias"], t["z0"], layer=layer, alpha=alpha))
+    assert res.status == deeppcr.OK and normwise_rel_err(h(res.Z), ref) <= TOL
+    check_solve_classes(n, rows)
+    res, n = solve_classes(lambda: deeppcr.deeppcr_mlp_forward_residual(
+        t["W"], t["bias"], t["z0"], layer=layer, alpha=alpha, atol=1e-5, rtol=0.0))
+    assert res.status == deeppcr.OK and normwise_rel_err(h(res.Z), ref) <= TOL
+    check_solve_classes(n, rows)
+    Z32 = ref.astype(np.float32)
+    out, n = solve_classes(lambda: deeppcr.deeppcr_mlp_backward(
+        t["W"], t["bias"], t["z0"], g(Z32, dev), t["G"], layer=layer, alpha=alpha))
+    check_solve_classes(n, rows)
+    lam, dz0, dW, db = map(h, out)
+    rl, rz, rW, rb = oracle.seq_backward(layer, alpha, d["W"], d["bias"], d["z0"], Z32, d["G"])
+    errs = (normwise_rel_err(np.concatenate([dz0[:, None], lam], 1),
+                             np.concatenate([rz[:, None], rl], 1)),
+            normwise_rel_err(dW, rW, axes="all"), normwise_rel_err(db, rb, axes="all"))
+    assert max(errs) <= TOL
