@@ -268,6 +268,8 @@ hipError_t block_solve(const BlockSrc& A, const VecSrc& r, const VecDst& x, int 
     block_plan(B, L, w, &pl);
     const int Lc = pl.m ? pl.m : L, C = (L + Lc - 1) / Lc;
     const double w2 = (double)w * w, rows = (double)B * L;
+    // the blocks of n rows per system as read: stored, or (y) the weights
+    const auto block_floats = [&](double n) { return (y ? 1.0 : (double)B) * n * w2; };
     const float *xe = nullptr, *walk = nullptr;
     if (C > 1) {
         const size_t Ce = (size_t)B * (C - 1);
@@ -275,8 +277,11 @@ hipError_t block_solve(const BlockSrc& A, const VecSrc& r, const VecDst& x, int 
         float* P = space;
         float* q = P + up4(Ce * w * w);
         float* e = q + up4(Ce * w);
-        hipError_t err = timed(DEEPPCR_KCLASS_PCR_LEVEL, 4.0 * (rows * (w2 + w) + Ce * (w2 + w)),
-                               rows * 2.0 * w2 * (w + 1), st,
+        // chunks 0 .. C-2 give q, chunks 1 .. C-2 P as well
+        const double up = (double)(C - 1) * Lc, prod = (double)(C - 2) * Lc;
+        hipError_t err = timed(DEEPPCR_KCLASS_PCR_LEVEL,
+                               4.0 * (block_floats(up) + B * up * w + Ce * w + B * (C - 2.0) * w2),
+                               B * 2.0 * w2 * (prod * w + up), st,
                                [&] { return launch_block_up(A, y, r, P, q, B, L, w, Lc, C, st); });
         if (err != hipSuccess) return err;
         xe = q;
@@ -290,8 +295,10 @@ hipError_t block_solve(const BlockSrc& A, const VecSrc& r, const VecDst& x, int 
             xe = e;
         }
     }
-    return timed(DEEPPCR_KCLASS_PCR_TAIL, 4.0 * rows * (w2 + (upd_red ? 3.0 : 2.0) * w),
-                 rows * 2.0 * w2, st,
+    const double ends = walk ? (double)B * (C - 2) : 0.0;  // walked beside the rows
+    return timed(DEEPPCR_KCLASS_PCR_TAIL,
+                 4.0 * (block_floats(L) + rows * (upd_red ? 3.0 : 2.0) * w + ends * (w2 + w)),
+                 (rows + ends) * 2.0 * w2, st,
                  [&] { return launch_block_down(A, y, r, x, xe, walk, upd_red, B, L, w, Lc, C, st); });
 }
 

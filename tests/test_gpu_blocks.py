@@ -106,3 +106,36 @@ def test_many_systems(dev, L):
     assert normwise_rel_err(x[0].cpu().numpy(), oracle.seq_solve(d["J"], d["r"])) <= 40 * 2.0 ** -24
     del J, r, x
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("w,B,L", [(16, 64, 1024), (16, 1, 64), (32, 2, 33), (64, 4, 20),
+                                   (128, 3, 1000)])
+def test_counted_work(dev, w, B, L):
+    """The work the library counts for block_up's class: rows of chunks 0 to
+    C-2 read and substituted, products in chunks 1 to C-2 only, over the
+    reduction's levels, for some lengths of the chunks."""
+    print(f"blocks work w={w} B={B} L={L}", flush=True)
+    d = synth.random_system(B, L, w, seed=3, scale=0.5)
+    J, r = (torch.from_numpy(d[k]).to(dev) for k in ("J", "r"))
+    deeppcr.profile_reset()
+    deeppcr.profile_enable(True)
+    try:
+        deeppcr.pcr_solve_block_bidiag(J, r)
+        torch.cuda.synchronize()
+    finally:
+        deeppcr.profile_enable(False)
+    got = deeppcr.profile_read(deeppcr.KCLASS_NAMES.index("pcr_level"))
+    deeppcr.profile_reset()
+
+    def works(L, levels):
+        if levels == 0:
+            return [(0.0, 0.0)]
+        out = []
+        for m in range(2, L):
+            C = -(-L // m)
+            rows, prod = (C - 1) * m, (C - 2) * m
+            nbytes = 4.0 * B * (rows * (w * w + w) + (C - 1) * w + (C - 2) * w * w)
+            flops = 2.0 * B * w * w * (prod * w + rows)
+            out += [(nbytes + b, flops + f) for b, f in works(C - 1, levels - 1)]
+        return out
+    assert (got["bytes"], got["flops"]) in works(L, got["launches"])
