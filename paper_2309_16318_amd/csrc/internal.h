@@ -141,8 +141,8 @@ hipError_t launch_copy_rows(const VecSrc& src, const VecDst& dst, int B, int L, 
                             hipStream_t stream);
 
 // ----------------------------------------------------------- small widths
-// w <= 8: one PCR level with a lane group per row, and the layer evaluation
-// with one thread per state element (forward and backward layouts as in
+// One PCR level with a lane group per row (w <= 3), and the layer evaluation
+// with one thread per state element (w <= 8; forward and backward layouts as in
 // launch_forward_eval / launch_backward_assemble).
 bool small_width(int w);
 hipError_t launch_pcr_level_small(const BlockSrc& Ain, const VecSrc& rin, float* Aout,

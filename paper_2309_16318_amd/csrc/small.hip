@@ -1,11 +1,10 @@
-// Small widths (w <= 8): one PCR level (Sec. 3, Alg. 1) with w x w blocks
+// Small widths.  w <= 3: one PCR level (Sec. 3, Alg. 1) with w x w blocks
 // handled by groups of WP*WP lanes (WP = w rounded up to a power of two), so a
 // wave reduces 64 / WP^2 rows at once; lane (i, j) of a group owns element
 // (i, j) of its row's block.  Block products and mat-vecs use lane shuffles
 // inside the group.  Rows are independent within a level, so no chain walk is
-// needed: A_{l-s} is read again for row l (blocks are at most 256 bytes).
-// Also the layer / Jacobian evaluation for small widths with one thread per
-// state element.
+// needed: A_{l-s} is read again for row l (blocks are at most 36 bytes).
+// w <= 8: the layer / Jacobian evaluation with one thread per state element.
 #include "internal.h"
 
 namespace deeppcr {
@@ -116,15 +115,15 @@ bool small_width(int w) { return w <= 8; }
 hipError_t launch_pcr_level_small(const BlockSrc& Ain, const VecSrc& rin, float* Aout,
                                   const VecDst& rout, int B, int L, int w, int s,
                                   hipStream_t stream) {
+    if (w > 3) return hipErrorInvalidValue;
     const long long rows = (long long)B * L;
-    const int wp = w <= 1 ? 1 : w <= 2 ? 2 : w <= 4 ? 4 : 8;
+    const int wp = w <= 2 ? w : 4;
     const long long rows_per_wg = (kThreads / 64) * (64 / (wp * wp));
     const dim3 grid((unsigned)((rows + rows_per_wg - 1) / rows_per_wg)), block(kThreads);
     switch (wp) {
         case 1: hipLaunchKernelGGL(pcr_level_small<1>, grid, block, 0, stream, Ain, rin, Aout, rout, B, L, w, s); break;
         case 2: hipLaunchKernelGGL(pcr_level_small<2>, grid, block, 0, stream, Ain, rin, Aout, rout, B, L, w, s); break;
-        case 4: hipLaunchKernelGGL(pcr_level_small<4>, grid, block, 0, stream, Ain, rin, Aout, rout, B, L, w, s); break;
-        default: hipLaunchKernelGGL(pcr_level_small<8>, grid, block, 0, stream, Ain, rin, Aout, rout, B, L, w, s); break;
+        default: hipLaunchKernelGGL(pcr_level_small<4>, grid, block, 0, stream, Ain, rin, Aout, rout, B, L, w, s); break;
     }
     return hipGetLastError();
 }

@@ -28,13 +28,16 @@ import hashlib
 import json
 import os
 
-# the kernels of the linear solves: chunk products and substitutions, on layers
-# and on stored blocks, and the row accesses they share
+# the kernels of the linear solves and the row accesses they share
 KERNEL_SOURCES = [os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", f)
-                  for f in ("panels.hip", "blocks.hip", "rows.h")]
+                  for f in ("panels.hip", "blocks.hip", "rows.h", "strip.h", "wide.hip",
+                            "small.hip", "tiny.hip", "chunked.hip")]
 
-# kernels of the substitutions (timed as a class of their own)
-TAIL_PREFIXES = ("pcr_chain_subst", "pcr_level_tail", "block_down", "apply_pass")
+# kernels of the products and levels, and of the substitutions, as the library
+# times them in two classes
+LEVEL_PREFIXES = ("chunk_pass", "block_up", "pcr_level_small", "pcr_wide_rows", "pcr_wide_prod",
+                  "newton_tiny", "newton_wave", "chunk_level")
+TAIL_PREFIXES = ("apply_pass", "block_down", "wide_step", "chunk_chain")
 
 
 def is_tail(name: str) -> bool:
@@ -43,7 +46,7 @@ def is_tail(name: str) -> bool:
 
 def is_pcr(name: str) -> bool:
     """A kernel of a linear solve: a level, products or a substitution."""
-    return "pcr_level" in name or name.startswith(("chunk_pass", "block_up")) or is_tail(name)
+    return name.startswith(LEVEL_PREFIXES) or is_tail(name)
 
 
 def code_digest(text: str) -> str:

@@ -42,19 +42,41 @@ def test_digest_covers_every_kernel_source():
     assert len(pmc_traffic.kernel_source_sha256()) == 64
 
 
+def test_every_solve_kernel_of_the_sources_is_matched():
+    """The kernels in the digest's sources are those of a solve, by the prefixes
+    of the two classes, or are named here; every prefix names a kernel."""
+    import re
+
+    others = {"layer_vectors", "split_weights", "wide_vectors", "eval_small", "forward_eval_wide",
+              "backward_assemble_wide", "broadcast_row0", "matvec_t_wide", "wgrad_wide",
+              "seq_layer_wide", "chunk_carry_kernel", "chunk_carry_rows",
+              "chunk_apply_rows", "chunk_apply_kernel", "chunk_apply_small"}
+    found = set()
+    for fn in pmc_traffic.KERNEL_SOURCES:
+        with open(fn, encoding="utf-8") as f:
+            found |= set(re.findall(r"__global__.*?void\s+(\w+)\s*\(", f.read(), re.S))
+    solve = {k for k in found if pmc_traffic.is_pcr(k)}
+    assert {k for k in found - solve} <= others, found - solve - others
+    for p in pmc_traffic.LEVEL_PREFIXES + pmc_traffic.TAIL_PREFIXES:
+        assert any(k.startswith(p) for k in found), p
+    tails = {k for k in found if pmc_traffic.is_tail(k)}
+    assert {"apply_pass", "block_down", "block_down16", "wide_step", "wide_step_t"} <= tails
+    assert not any(k.startswith(("chunk_pass", "block_up", "pcr_")) for k in tails)
+
+
 def test_per_kernel_counts_each_dispatch_once(tmp_path):
     # rocprofv3 can list a dispatch once per agent / sample; it must count once
     d = _counter_dir(tmp_path, "f", [
-        (1, "void deeppcr::(anonymous namespace)::pcr_level2_tile<64, false, false>(a, b)",
+        (1, "void deeppcr::(anonymous namespace)::chunk_pass<64, false, true, true>(a, b)",
          "FETCH_SIZE", 100.0),
-        (1, "void deeppcr::(anonymous namespace)::pcr_level2_tile<64, false, false>(a, b)",
+        (1, "void deeppcr::(anonymous namespace)::chunk_pass<64, false, true, true>(a, b)",
          "FETCH_SIZE", 100.0),
-        (2, "void deeppcr::(anonymous namespace)::pcr_level2_tile<64, false, false>(a, b)",
+        (2, "void deeppcr::(anonymous namespace)::chunk_pass<64, false, true, true>(a, b)",
          "FETCH_SIZE", 300.0),
         (3, "copy_kernel(x)", "WRITE_SIZE", 7.0),
     ])
     k = pmc_traffic.per_kernel(d, "FETCH_SIZE")
-    assert k == {"pcr_level2_tile<64, false, false>": [2, 400.0]}
+    assert k == {"chunk_pass<64, false, true, true>": [2, 400.0]}
 
 
 def test_summary_scales_by_the_copy_and_leaves_out_the_tail(tmp_path, monkeypatch):
@@ -62,7 +84,7 @@ def test_summary_scales_by_the_copy_and_leaves_out_the_tail(tmp_path, monkeypatc
     # 1024 units (1024 B per unit)
     cf = _counter_dir(tmp_path, "cf", [(1, "copyBuffer", "FETCH_SIZE", 512.0)])
     cw = _counter_dir(tmp_path, "cw", [(1, "copyBuffer", "WRITE_SIZE", 1024.0)])
-    lvl, tail = "pcr_level2_tile<128, false, false>", "pcr_level_tail<128, 6, true>"
+    lvl, tail = "block_up<128, false, true>", "block_down<128, false, true, false>"
     f = _counter_dir(tmp_path, "f", [(1, lvl, "FETCH_SIZE", 10.0), (2, lvl, "FETCH_SIZE", 30.0),
                                      (3, tail, "FETCH_SIZE", 1000.0),
                                      (4, "other_kernel", "FETCH_SIZE", 5000.0)])
@@ -144,10 +166,10 @@ def test_calibration_scales_by_the_copy_and_checks_the_add(tmp_path):
 
 
 def test_mfma_summary_weights_by_dispatch_and_splits_the_tail(tmp_path):
-    pair, tail = "pcr_level2_tile<128, false, false>", "pcr_level_tail<128, 6, true>"
+    pair, tail = "block_up<128, false, true>", "block_down<128, false, true, false>"
     rows = [(1, pair, "MfmaUtil", 70.0), (1, pair, "SQ_BUSY_CYCLES", 10.0),
             (2, pair, "MfmaUtil", 74.0), (2, pair, "SQ_BUSY_CYCLES", 30.0),
-            (3, "pcr_level2_tile_layer<128>", "MfmaUtil", 60.0),
+            (3, "chunk_pass<128, false, true, true>", "MfmaUtil", 60.0),
             (4, tail, "MfmaUtil", 50.0), (5, "other", "MfmaUtil", 1.0)]
     d = _counter_dir(tmp_path, "m", rows)
     out = pmc_traffic.mfma(["--workload", "x", "--dir", d, "--out", str(tmp_path / "m.json")])
