@@ -139,3 +139,28 @@ def test_counted_work(dev, w, B, L):
             out += [(nbytes + b, flops + f) for b, f in works(C - 1, levels - 1)]
         return out
     assert (got["bytes"], got["flops"]) in works(L, got["launches"])
+
+
+@pytest.mark.parametrize("w,B", [(4, 5), (9, 3), (24, 300), (128, 70)])
+def test_one_row(dev, w, B):
+    """A system of one row is its right-hand side: a copy, or the update with
+    its maxima, and no substitution."""
+    print(f"blocks one row w={w} B={B}", flush=True)
+    d = synth.random_system(B, 1, w, seed=w)
+    J, r = (torch.from_numpy(d[k]).to(dev) for k in ("J", "r"))
+    Z = torch.ones_like(r)
+    deeppcr.profile_reset()
+    deeppcr.profile_enable(True)
+    try:
+        x = [deeppcr.pcr_solve_block_bidiag(J, r, transpose=t) for t in (0, 1)]
+        res = deeppcr.deeppcr_newton_step(J, r, Z, tol=0.0)
+        torch.cuda.synchronize()
+    finally:
+        deeppcr.profile_enable(False)
+    tail = deeppcr.profile_read(deeppcr.KCLASS_NAMES.index("pcr_tail"))["launches"]
+    deeppcr.profile_reset()
+    assert tail == 0
+    assert torch.equal(x[0], r) and torch.equal(x[1], r)
+    ref = d["r"] - np.float32(1)
+    assert np.array_equal(Z.cpu().numpy(), np.float32(1) + ref)
+    assert res.max_update == res.residual == np.max(np.abs(ref))
