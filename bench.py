@@ -285,8 +285,8 @@ def cpu_baseline(wl, budget_s):
 
 
 def measured_traffic(workload):
-    """HBM bytes per PCR-level launch from the committed rocprofv3 counter
-    summary of this workload (FETCH_SIZE + WRITE_SIZE, scaled by a plain copy
+    """HBM bytes per launch of the products' class from the committed rocprofv3
+    counter summary of this workload (FETCH_SIZE + WRITE_SIZE, scaled by a plain copy
     of known size), or None if there is none or the kernel source changed
     since the counters were taken."""
     from paper_2309_16318_amd import pmc_traffic
@@ -302,8 +302,8 @@ def measured_traffic(workload):
 
 
 def measured_mfma_util(workload):
-    """Mean MfmaUtil (percent of cycles the MFMA units are busy) of the PCR
-    level launches and of the tail pass, from the committed rocprofv3
+    """Mean MfmaUtil (percent of cycles the MFMA units are busy) of the
+    products' class and of the substitutions, from the committed rocprofv3
     summary of this workload, or None if there is none or the kernel source
     changed since it was taken."""
     from paper_2309_16318_amd import pmc_traffic
@@ -330,7 +330,7 @@ def products_peak(wl):
 def roofline(cls, w, by_intensity=False, peak=PEAK_FP32_TFLOPS):
     """Roofline position of one kernel class from the library's counts:
     algorithmic flops and bytes of its launches over their summed event
-    time; MFMA-bound at an intensity above the ridge (or, for the PCR level
+    time; MFMA-bound at an intensity above the ridge (or, for the products'
     class, at w >= 64, the widths the workload targets rate against MFMA)."""
     intensity = cls["flops"] / max(cls["bytes"], 1.0)
     tflops = cls["flops"] / (cls["ms"] * 1e-3) / 1e12

@@ -389,20 +389,20 @@ int deeppcr_seq_backward(const float* W, const float* bias, const float* z0, con
  * stream and records, per kernel class, the launch count, the summed device
  * time and the algorithmic bytes and flops of each launch.  Consecutive
  * launches of one class on one stream (no host wait or other class between
- * them, e.g. the levels of one PCR sweep) share one event pair, so the time
+ * them, e.g. the passes of one solve) share one event pair, so the time
  * of such a run includes the gaps between its kernels but no event overhead
  * per kernel; where a run of one class follows a run of another, one event
  * ends the first and starts the second.  The state is per host thread: a
  * thread's enable, select, reset and read see only that thread's launches.
  */
 enum {
-    DEEPPCR_KCLASS_PCR_LEVEL = 0,  /* one PCR level (Alg. 1 inner parfor)      */
+    DEEPPCR_KCLASS_PCR_LEVEL = 0,  /* chunk products, or one PCR level (Alg. 1) */
     DEEPPCR_KCLASS_LAYER = 1,      /* layers + Jacobian blocks + residual      */
     DEEPPCR_KCLASS_UPDATE = 2,     /* Newton update and convergence reduction  */
     DEEPPCR_KCLASS_WGRAD = 3,      /* parameter gradients                      */
     DEEPPCR_KCLASS_OTHER = 4,      /* initial guess, copies, dz0               */
     DEEPPCR_KCLASS_SEQUENTIAL = 5, /* sequential baseline passes               */
-    DEEPPCR_KCLASS_PCR_TAIL = 6,   /* last levels: substitution along the chains */
+    DEEPPCR_KCLASS_PCR_TAIL = 6,   /* substitution inside chunks, or row by row */
     DEEPPCR_KCLASS_COUNT = 7
 };
 int deeppcr_profile_enable(int on);

@@ -991,9 +991,9 @@ int deeppcr_newton_step(const float* J, const float* F, float* Z, int B, int L, 
     e = timed(DEEPPCR_KCLASS_LAYER, 12.0 * n, (double)n, st,
               [&] { return launch_residual(F, Z, ws.r[1], n, ws.red, st); });
     if (e != hipSuccess) return hip_fail(e, "residual");
-    // Eq. 3 with the caller's blocks (J[:, 0] unused) by PCR, then Z += dZ:
-    // applied by the substitution pass of the last levels where the sweep
-    // ends in one, else by the update kernel
+    // Eq. 3 with the caller's blocks (J[:, 0] unused), then Z += dZ: applied
+    // by the substitution inside the chunks, or after PCR levels by the update
+    // kernel
     const BlockSrc J0{J, (long long)L * w * w, (long long)w * w, 0};
     const VecSrc r0{ws.r[1], (long long)L * w, (long long)w};
     if (by_chunks(w)) {
@@ -1237,9 +1237,9 @@ int deeppcr_resnet_forward(const float* W, const float* bias, const float* z0, f
         });
         if (e != hipSuccess) return hip_fail(e, "resnet_block_eval");
         if (upd_in_tail) {
-            // the substitution pass of the last levels adds the solution to
-            // the iterate and reduces the convergence maxima itself (the
-            // block evaluation cleared their slots)
+            // the substitution inside the chunks adds the solution to the
+            // iterate and reduces the convergence maxima itself (the block
+            // evaluation cleared their slots)
             e = pcr_sweep(BlockSrc{ws.A[1], (long long)G * w * w, (long long)w * w, 0},
                           VecSrc{ws.r[1], (long long)G * w, (long long)w},
                           VecDst{X, (long long)G * w, (long long)w}, B, G, w, ws.A, ws.r, st,

@@ -11,8 +11,8 @@
 //
 // The kernels here work on whole blocks, one workgroup per (system, block),
 // with the state vectors and the w x w running Jacobian product in LDS
-// (dynamic, sized by w).  The PCR levels, the Newton update and its
-// reductions are those of the MLP path.
+// (dynamic, sized by w).  The block system's solve, with the Newton update
+// and its reductions, is that of stored blocks (blocks.hip).
 #include "internal.h"
 #include "strip.h"
 
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(kThreads) void resnet_expand_kernel(
 
 // Backward: blocks of the transposed block system in reversed row order.
 // Reversed row m = G - g holds A_g = I + P_g (g >= 1) with P_g evaluated at
-// the stored layer inputs, stored untransposed (the first PCR level reads it
+// the stored layer inputs, stored untransposed (the solve reads it
 // transposed); the right-hand side is G at reversed row 0 and 0 elsewhere.
 __global__ __launch_bounds__(kThreads) void resnet_block_jac_kernel(
     const float* __restrict__ W, const float* __restrict__ z0, const float* __restrict__ Z,
@@ -629,7 +629,7 @@ __global__ __launch_bounds__(256) void resnet_block_group16(
 
 // ---- one workgroup per (system, block), w = 64 or 128 ----------------------
 // The running product on fp32 MFMA: one wave per 32-row strip (the register
-// strips of the PCR kernels).  Layer j of the block multiplies the product
+// strips of strip.h).  Layer j of the block multiplies the product
 // from the left by J_j = W_j diag(sigma'(z_{j-1})): the lane's strip of W_j
 // comes from global memory (L2-resident, shared by every system), first
 // serves the state update W_j sigma(z) + b_j (forward), then has its columns
@@ -821,8 +821,11 @@ __global__ __launch_bounds__(256) void resnet_intra_adjoint_wave(
 // forward of 6 iterations, wave per system against groups, us: B 16, 512
 // blocks 261 : 245, B 64, 256 blocks 328 : 274, B 256, 128 blocks 480 : 400;
 // B 16, 128 blocks 160 : 174.  The backward, whose states are read, gains
-// from twice that: 35.3 : 35.8 at 8192 blocks, 51 : 49 at 16384.  A last group
-// that is nearly empty costs as much as a full one.
+// from twice that.  Over B 8-1024 and 1, 2 and 4 layers per block, groups
+// against waves: at 8192 blocks 0.98-1.03 of the time (42.2 : 42.4 at B 32, 4
+// layers), at 16384 0.96-1.02 (54.2 : 53.1 at B 64, 4 layers), at 32768
+// 0.93-0.99 (80.2 : 74.7); forward 0.93-0.99 at 8192, 0.99-1.09 at 1024-4096.
+// A last group that is nearly empty costs as much as a full one.
 bool group16(bool bwd, int B, int G) {
     const long long filled = ((long long)B + kGroup - 1) / kGroup * kGroup;
     return (long long)B * G >= (bwd ? 16384 : 8192) && filled * 4 <= 5LL * B;

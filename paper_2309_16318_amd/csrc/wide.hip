@@ -536,8 +536,9 @@ __global__ __launch_bounds__(kThreads) void wgrad_wide(
 // (wide_substitution): one launch per row, every block W_l read once for a
 // tile of systems, no block stored.  B = 1, L = 256, w = 1024, forward and
 // backward: 212 ms by PCR levels, 10.0 ms by rows.  What bounds a row is the
-// launch and the latency of its two dependent reads (3.6 us at w = 256, 4.5
-// at 1024, where reading W_l at the copy rate would take 0.8).
+// launch and the latency of its two dependent reads: 3.3-3.9 us at w = 129 to
+// 512 in either direction; at 1024 4.2 us forward and 6.2 transposed (64
+// workgroups of it on 256 CUs), where reading W_l at the copy rate takes 0.8.
 constexpr int kSubB = 8;      // systems per workgroup
 constexpr int kEvalRows = 4;  // rows per wave of the layer evaluation
 
@@ -777,10 +778,14 @@ static int step_tile(int B, int w) {
 }
 
 bool wide_substitution(int B, int rows, int w) {
-    // Measured (B 1-64, L 16-1024): a row by substitution 3-4 us and 0.8 us
-    // per system of a tile (w = 1024: 4.5 and 6); a PCR level 15 us + 0.15
-    // w at the least, its products 15, 29, 36, 60 and 110 TFLOP/s at w = 129,
-    // 160, 200, 256, 1024 (tiles of 128 x 128).
+    // Measured (w 129-1024, L 16-512, B 1-64, forward and transposed): a row
+    // by substitution 3-4 us and 0.8 us per system of a tile; a PCR level 15 us
+    // + 0.15 w at the least, its products 15, 29, 36, 60 and 110 TFLOP/s at w =
+    // 129, 160, 200, 256, 1024 (tiles of 128 x 128).  The transposed row costs
+    // what the forward one does where the line lies (w 129-256, B 1-2: 3.2-3.8
+    // us both); at w = 1024 it is the dearer by half, and the levels by 15 to 30
+    // times.  The choice is within 5% of the better one in all 618 timings
+    // (B 2, L 256, w 129: rows 919 us, levels 958; B 1, L 256, w 256: 864, 824).
     const double fill = (double)w / ((w + kTile - 1) / kTile * kTile);
     double flops = 0.0, us = 0.0;
     for (long long s = 1; s < rows; s *= 2) {

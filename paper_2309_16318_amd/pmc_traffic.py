@@ -1,4 +1,4 @@
-"""Summaries of rocprofv3 counter runs of the PCR level kernels.
+"""Summaries of rocprofv3 counter runs of the linear solves' kernels.
 
 HBM traffic.  Two counter runs of the same command are needed (FETCH_SIZE,
 then WRITE_SIZE; rocprofv3 cannot collect both at once), plus the same two
@@ -190,10 +190,10 @@ def per_kernel_all(d: str) -> dict:
 
 
 def mfma(argv=None) -> dict:
-    """Per PCR kernel: mean MfmaUtil (percent of the cycles the MFMA units
+    """Per solve kernel: mean MfmaUtil (percent of the cycles the MFMA units
     are busy) and mean SQ cycle counters per dispatch; plus the
-    dispatch-weighted MfmaUtil of the level class (pair and single-level
-    passes) and of the tail pass."""
+    dispatch-weighted MfmaUtil of the class of products and levels and of the
+    substitutions."""
     p = argparse.ArgumentParser(prog="pmc_traffic mfma")
     p.add_argument("--workload", required=True)
     p.add_argument("--dir", required=True)
@@ -254,8 +254,8 @@ def traffic():
         kernels[name] = {"launches": n,
                          "read_bytes_per_launch": fetch[name][1] * ff / n,
                          "write_bytes_per_launch": write[name][1] * wf / write[name][0]}
-    # The tail pass is timed as a class of its own, so the per-launch average
-    # that goes with the PCR-level roofline leaves it out.
+    # The substitutions are timed as a class of their own, so the per-launch
+    # average that goes with the products' roofline leaves them out.
     level = {k: v for k, v in kernels.items() if not is_tail(k)}
     n_all = sum(v["launches"] for v in level.values())
     rd = sum(v["read_bytes_per_launch"] * v["launches"] for v in level.values()) / n_all

@@ -1,9 +1,7 @@
-"""GPU parity of the last levels' substitution pass (the chains left after
-the first PCR levels, solved row by row) across the shapes where the number
-of substituted levels changes (3 to 6), with odd depths (chains of unequal
-length, the last shorter than the others) and short chains, for the
-standalone solve (both orientations), the Newton forward (the pass adds the
-solution to the iterate and reduces the stopping measures) and the backward.
+"""GPU parity of solves over deep and shallow systems: odd depths (chunks of
+unequal length, the last shorter than the others) and short ones, for the
+standalone solve (both orientations), the Newton forward (the substitution adds
+the solution to the iterate and reduces the stopping measures) and the backward.
 Against the CPU oracle on the same seeded float32 inputs; normwise relative
 error <= 1e-4."""
 import sys

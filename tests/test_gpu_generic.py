@@ -37,8 +37,8 @@ def h(t):
     return t.detach().cpu().numpy()
 
 
-# the last three end in the substitution pass of the last levels, which then
-# also applies the update and reduces the step's measures
+# the substitution inside the chunks also applies the update and reduces the
+# step's measures (L = 1: the update kernel)
 @pytest.mark.parametrize("w,L,B", [(4, 50, 3), (16, 300, 2), (32, 129, 2), (64, 40, 2),
                                    (128, 17, 2), (17, 33, 2), (16, 1, 2), (32, 2, 3),
                                    (32, 256, 64), (16, 1024, 16), (64, 130, 64)])

@@ -195,14 +195,9 @@ def test_forward_all_layer_kinds(dev, w, L, B, layer, alpha):
     assert ok and abs(res.iters - k_ref) <= 1
 
 
-# Tile widths with several elements per workgroup segment in every pass
-# (w = 64, B = 40 and w = 128, B = 16), even and odd level counts (L = 130
-# and 203: 8 levels, L = 300: 9), and the one-pass tail of the last levels
-# at w = 32 (L = 130, B = 64: 6 tail levels right after the first pair with
-# the layers; L = 300, B = 40: that pair, one more pair and 5 tail levels;
-# L = 17, B = 128 and L = 33, B = 64: 3 and 4 tail levels on chains of 4-5
-# and 8-9 elements, shorter than and just past the tail's ring of blocks in
-# flight), 64 and 128.
+# Tile widths with more systems than a group's 16 (w = 64, B = 40; w = 32, B =
+# 64), a whole group (w = 128, B = 16) and half of one, deep and shallow, no
+# depth a multiple of the chunks.
 @pytest.mark.parametrize("w,L,B", [(64, 130, 40), (64, 300, 8), (128, 203, 16), (32, 130, 64),
                                    (32, 300, 40), (32, 17, 128), (32, 33, 64)])
 @pytest.mark.parametrize("layer,alpha", ALL_KINDS)
@@ -265,9 +260,9 @@ def test_forward_reports_non_finite(dev):
     assert res.status == deeppcr.ENONFINITE and res.iters == 1
 
 
-# The same reports from the multi-kernel paths: the fused last level (w = 16),
-# the update kernel (w = 64, one workgroup row per level) and the tail pass
-# that applies the update itself (w = 32, 64, 128 with enough chains).
+# The same reports from the multi-kernel paths, whose substitution applies the
+# update itself: blocks formed from the weights on the way (w = 16), split
+# weights (w = 32, 64, 128).
 @pytest.mark.parametrize("w,L,B", [(16, 100, 3), (64, 40, 2), (32, 130, 64), (64, 300, 8),
                                    (128, 203, 16)])
 def test_forward_status_reports_every_path(dev, w, L, B):
@@ -282,7 +277,7 @@ def test_forward_status_reports_every_path(dev, w, L, B):
 
 
 def test_profiling_times_selected_classes_and_changes_nothing(dev):
-    """Instrumentation on (only the PCR level and tail classes timed, with
+    """Instrumentation on (only the products' and the substitutions' classes timed, with
     events shared at span boundaries) leaves the result bitwise unchanged."""
     _say("profiling on a w=32 forward")
     d = synth.mlp_inputs(64, 130, 32, seed=31)
@@ -460,11 +455,8 @@ def test_backward_shapes(dev, w, L, B, layer, alpha):
     _backward_check(d, Z32, dev, layer, alpha)
 
 
-# Tile widths with several elements per workgroup segment in every pass of
-# the transposed sweep (the first pass forms its blocks from the weights),
-# odd and even level counts (L = 130: 8 levels; L = 203 and 300: 8 and 9),
-# and the tail of the last levels at w = 32, 64, 128 (at w = 32 also on
-# chains shorter than its ring of blocks in flight: L = 17 and 33).
+# The transposed solve at the same kinds of shapes; at w = 32 also a few rows
+# per chunk, less than the rows requested ahead (L = 17 and 33).
 @pytest.mark.parametrize("w,L,B", [(64, 130, 40), (64, 300, 8), (128, 203, 16), (32, 130, 64),
                                    (32, 300, 40), (32, 17, 128), (32, 33, 64)])
 @pytest.mark.parametrize("layer,alpha", ALL_KINDS)
@@ -508,8 +500,7 @@ def test_residual_forward_then_backward_workload(dev):
     assert abs(res.iters - k_ref) <= 1
 
 
-# w = 64 with B >= 16 and 513 <= L <= 1024: the last six levels run as one
-# tail pass (strides 16 .. 512), forward (with the Newton update) and
+# w = 64 with B >= 16 and 513 <= L <= 1024, forward (with the Newton update) and
 # backward; residual layers keep the adjoints of early layers in range, so
 # every layer is compared.
 @pytest.mark.parametrize("L,B", [(1000, 16), (600, 20)])

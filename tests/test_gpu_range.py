@@ -171,3 +171,23 @@ def test_small_states(dev, w, B, layer):
     err = np.max(row_errors(res.Z.cpu().numpy(), ref, 2.0 ** -122))
     print(f"  err {err:.1e}", flush=True)
     assert err <= 60 * np.sqrt(w) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("w", [9, 16] + WIDTHS)
+def test_infinite_state_saturates(dev, w):
+    """An infinite input, and one of 3.4e38, through the layer evaluation: the
+    activation is 1 there, as of a plain sum, and the layers after it see that."""
+    print(f"range: infinite state w={w}", flush=True)
+    d = synth.mlp_inputs(3, 30, w, seed=w)
+    z0, W = d["z0"].copy(), d["W"].copy()
+    z0[1, w - 1], z0[2, 3] = np.inf, 3.4e38
+    W[0, :, w - 1] = np.abs(W[0, :, w - 1]) + 0.1
+    W[0, :, 3] = np.abs(W[0, :, 3]) + 0.1
+    t = [torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(dev)
+         for a in (W, d["bias"], z0)]
+    res = deeppcr.deeppcr_mlp_forward(*t)
+    assert res.status == deeppcr.OK
+    Z = res.Z.cpu().numpy()
+    assert np.all(Z[1:, 0] == 1.0)
+    ref = oracle.seq_forward(0, 1.0, W[1:], d["bias"][1:], np.ones((1, w), np.float32))
+    assert np.max(np.abs(Z[1:, 1:] - ref)) <= 4 * w * 2.0 ** -24
