@@ -608,7 +608,7 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
         }
     };
     // A column of P, which a wave holds whole (lanes n and n + 32), stays within
-    // 2^-60 .. 2^60 in its largest element, so that its elements have parts and
+    // 2^-60 .. 2^40 in its largest element, so that its elements have parts and
     // no product of a long chunk leaves the range before its end: P stands for
     // P 2^ex.  The check is 8 maxima per 32 x 32 elements, which cost 4% of the
     // pass at w = 32 and 1% at 128 (33.7 -> 35.1 us at B 256, L 256, w 32; 340 ->
@@ -621,12 +621,12 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
         for (int mt = 0; mt < S::MT; ++mt)
 #pragma unroll
             for (int e = 0; e < 16; ++e) m = fmaxf(m, fabsf(P[mt][e]));
-        const unsigned low = __float_as_uint(0x1p-60f), high = __float_as_uint(0x1p60f);
+        const unsigned low = __float_as_uint(0x1p-60f), high = __float_as_uint(0x1p40f);
         if (__builtin_expect(
                 __builtin_amdgcn_ballot_w64(__float_as_uint(m) - low > high - low) != 0, 0)) {
             m = fmaxf(m, __shfl_xor(m, 32, 64));
-            const float f = m > 0x1p60f ? 0x1p-64f : m > 0.f && m < 0x1p-60f ? 0x1p64f : 1.f;
-            ex += m > 0x1p60f ? 64 : m > 0.f && m < 0x1p-60f ? -64 : 0;
+            const float f = m > 0x1p40f ? 0x1p-64f : m > 0.f && m < 0x1p-60f ? 0x1p64f : 1.f;
+            ex += m > 0x1p40f ? 64 : m > 0.f && m < 0x1p-60f ? -64 : 0;
 #pragma unroll
             for (int mt = 0; mt < S::MT; ++mt) P[mt] *= f;
         }
