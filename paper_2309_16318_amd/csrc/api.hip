@@ -443,13 +443,16 @@ hipError_t read_measures(const unsigned* red, unsigned* hw, hipStream_t st, unsi
 struct PanelPlan {
     int C = 0, Lc = 0;  // C = 0: not for this shape
     size_t P, q, xe, space, scale;
+    unsigned stamp;  // of this call's factors (launch_split_weights)
     bool split = false;  // the weights are split once, at S
     size_t S;
 };
 
 PanelPlan panel_plan(int B, int L, int w, bool bwd) {
+    static std::atomic<unsigned> stamps{0u};
     PanelPlan pl;
     if (!panel_width(w)) return pl;
+    pl.stamp = ++stamps;
     const int WP = panel_pad(w);
     const int rows = L + (bwd ? 1 : 0);
     const Layout lo = layout(bwd ? DEEPPCR_OP_BWD : DEEPPCR_OP_FWD, B, L, w);
@@ -482,7 +485,7 @@ hipError_t panel_split(bool bwd, const float* W, int L, int w, const PanelPlan& 
     const double bytes = 4.0 * L * w * w + (pl.split ? (double)split_bytes(L, w) : 0.0);
     return timed(DEEPPCR_KCLASS_OTHER, bytes, 0.0, st, [&] {
         return launch_split_weights(bwd, W, pl.split ? base + pl.S : nullptr,
-                                    (float*)(base + pl.scale), L, w, st);
+                                    (float*)(base + pl.scale), pl.stamp, L, w, st);
     });
 }
 
@@ -496,6 +499,8 @@ hipError_t panel_solve(bool bwd, PanelArgs a, const PanelPlan& pl, void* ws_base
     a.C = pl.C;
     if (pl.split) a.S = base + pl.S;
     a.scale = (const float*)(base + pl.scale);
+    a.odd = (const unsigned*)(a.scale + split_scales(a.L, a.w) - 1);
+    a.stamp = pl.stamp;
     a.P = (float*)(base + pl.P);
     a.q = (float*)(base + pl.q);
     float* xe = (float*)(base + pl.xe);

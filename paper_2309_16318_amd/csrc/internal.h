@@ -188,7 +188,9 @@ hipError_t launch_block_down(const BlockSrc& A, const LayerScale* y, const VecSr
 struct PanelArgs {
     const float* W;   // [L, w, w]
     const char* S;    // the weights split (launch_split_weights), or null
-    const float* scale;  // their factors (launch_split_weights)
+    const float* scale;  // their factors (launch_split_weights), and whether
+    const unsigned* odd;  // there may be any but 1: *odd == stamp
+    unsigned stamp;
     const float* d;   // [B, L, w] c sigma'
     const float* r;   // [B, L, w] residuals; transposed: G [B, w]
     const float* xe;  // [B, C-1, WP] solution at the chunk ends
@@ -212,11 +214,12 @@ hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, con
                                 const float* Z, float* d, float* r, unsigned* red, bool want_max,
                                 int B, int L, int w, int layer, float alpha, hipStream_t st);
 // The weights (bwd: transposed) as bf16 parts in operand order, split_bytes,
-// and the factors of their results, split_scales; out null: these alone.
+// and the factors of their results with the word for PanelArgs::odd behind them,
+// split_scales words in all; out null: these alone.
 size_t split_bytes(int L, int w);
 size_t split_scales(int L, int w);
-hipError_t launch_split_weights(bool bwd, const float* W, char* out, float* scale, int L, int w,
-                                hipStream_t st);
+hipError_t launch_split_weights(bool bwd, const float* W, char* out, float* scale, unsigned stamp,
+                                int L, int w, hipStream_t st);
 // P of chunks 1 .. C-2 and q of chunks 0 .. C-2 (C >= 2).
 hipError_t launch_chunk_pass(bool bwd, const PanelArgs& a, hipStream_t st);
 // Every row from its chunk's x_in (xe of the chunk before; 0 in the first).

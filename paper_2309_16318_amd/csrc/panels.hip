@@ -400,10 +400,7 @@ __device__ __forceinline__ void vector_panel(const PanelArgs& a, char* lds, int 
         unrolled<0, D>([&](auto s) { request(m + decltype(s)::value, s); });
         // (weights out of the ordinary range are multiplied by 1 / scale)
         const float* const scale = a.scale + base / 32;
-        bool scaled = false;
-        for (int k = m + lane; k < m1; k += 64)
-            scaled = scaled || scale[(BWD ? L - k : k) * (WP / 32)] != 1.f;
-        scaled = __builtin_amdgcn_ballot_w64(scaled) != 0;
+        const bool scaled = *a.odd == a.stamp;
         int buf = 0;
         for (int mb = m; mb < m1; mb += NB) {
             unrolled<0, NB>([&](auto sc) {
@@ -510,7 +507,7 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
     const Src<EXACT> sd(a.d, (unsigned)a.B * L * w);
     // (weights out of the ordinary range are multiplied by 1 / scale)
     auto scale_at = [&](int m, int mt) { return a.scale[(long long)(BWD ? L - m : m) * S::MT + mt]; };
-    bool scaled = false;
+    const bool scaled = *a.odd == a.stamp;
 
     // this thread's 4 x 4 weights of a stage: rows 4 rg .., columns 4 cg .. of
     // the stage's 32-row block blk
@@ -607,26 +604,34 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
             for (int e = 0; e < 4; ++e) d[4 * q + e] = x[e];
         }
     };
-    // A column of P, which a wave holds whole (lanes n and n + 32), stays within
-    // 2^-60 .. 2^40 in its largest element, so that its elements have parts and
-    // no product of a long chunk leaves the range before its end: P stands for
-    // P 2^ex.  The check is 8 maxima per 32 x 32 elements, which cost 4% of the
-    // pass at w = 32 and 1% at 128 (33.7 -> 35.1 us at B 256, L 256, w 32; 340 ->
-    // 342 us at B 16, L 1024, w 128).
+    // A column of P, which a wave holds whole (lanes n and n + 32), stays above
+    // 2^-60 in its largest element, so that its elements have parts, and P stands
+    // for P 2^ex (large columns are scaled down as well, where float32 would
+    // overflow).  A few elements of each half show that as a rule, and only
+    // where they do not all are looked at.  The pass without any of the range's
+    // checks, with all maxima at every row, and with these, us: 33.4, 35.1, 34.3
+    // at B 256, L 256, w 32; 184, 191, 188 at B 64, L 1024, w 64 (transposed);
+    // 330, 341, 329 at B 16, L 1024, w 128.
     int ex = 0;
+    auto largest = [&](int tiles, int count) {
+        float m = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < tiles; ++mt)
+#pragma unroll
+            for (int e = 0; e < count; ++e) m = fmaxf(m, fabsf(P[mt][3 * e % 16]));
+        return m;
+    };
     auto settle = [&] {
         // (the columns beyond w are zeros)
-        float m = EXACT || col < w ? 0.f : 1.f;
-#pragma unroll
-        for (int mt = 0; mt < S::MT; ++mt)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) m = fmaxf(m, fabsf(P[mt][e]));
+        const float some = EXACT || col < w ? largest(1, 5) : 1.f;
         const unsigned low = __float_as_uint(0x1p-60f), high = __float_as_uint(0x1p40f);
         if (__builtin_expect(
-                __builtin_amdgcn_ballot_w64(__float_as_uint(m) - low > high - low) != 0, 0)) {
+                __builtin_amdgcn_ballot_w64(__float_as_uint(some) - low > high - low) != 0, 0)) {
+            float m = largest(S::MT, 16);
             m = fmaxf(m, __shfl_xor(m, 32, 64));
-            const float f = m > 0x1p40f ? 0x1p-64f : m > 0.f && m < 0x1p-60f ? 0x1p64f : 1.f;
-            ex += m > 0x1p40f ? 64 : m > 0.f && m < 0x1p-60f ? -64 : 0;
+            const int k = m > 0x1p40f ? 64 : m > 0.f && m < 0x1p-60f ? -64 : 0;
+            const float f = k > 0 ? 0x1p-64f : k < 0 ? 0x1p64f : 1.f;
+            ex += k;
 #pragma unroll
             for (int mt = 0; mt < S::MT; ++mt) P[mt] *= f;
         }
@@ -681,9 +686,6 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
     const float* const dbase =
         reinterpret_cast<const float*>(lds + S::WB) + v / S::MT * WP + 4 * h;
     request(0);
-    for (int k = m0 * S::MT + lane; k < m1 * S::MT; k += 64)
-        scaled = scaled || scale_at(k / S::MT, k % S::MT) != 1.f;
-    scaled = __builtin_amdgcn_ballot_w64(scaled) != 0;
     put(0);
     request(1);
     operands(nullptr, true);
@@ -804,11 +806,14 @@ __global__ __launch_bounds__(kThr) void apply_pass(PanelArgs a) {
 // ------------------------------------------------------------ split weights
 // The tiles of SplitShape from W (BWD: of W^T), 4 x 4 weights per thread, and
 // per layer and 32 rows the factor that the results are to be multiplied by:
-// 1, unless the largest weight of these rows is below 2^-60 or from 2^60 on.
-// Without `out`, the factors alone.
+// 1, unless the largest weight of these rows is below 2^-60 or from 2^60 on;
+// then *odd becomes the call's stamp.  (What is in *odd before needs no
+// clearing: a stamp left there only makes a call read its factors.)  Without
+// `out`, the factors alone.
 template <int WP, bool BWD, bool EXACT>
 __global__ __launch_bounds__(kThr) void split_weights(const float* __restrict__ W,
                                                       char* __restrict__ out, float* __restrict__ scale,
+                                                      unsigned* __restrict__ odd, unsigned stamp,
                                                       int L, int w_) {
     constexpr int UNITS = WP * WP / 16, WAVES = WP / 32;  // threads per layer, waves per 32 rows
     const int w = EXACT ? WP : w_;
@@ -841,7 +846,10 @@ __global__ __launch_bounds__(kThr) void split_weights(const float* __restrict__ 
     const float f = m >= 0x1p60f && m < __builtin_inff() ? 0x1p-64f
                     : m > 0.f && m < 0x1p-60f            ? 0x1p64f
                                                          : 1.f;
-    if (u % (2 * WP) == 0) scale[(long long)l * (WP / 32) + mt] = 1.f / f;
+    if (u % (2 * WP) == 0) {
+        scale[(long long)l * (WP / 32) + mt] = 1.f / f;
+        if (f != 1.f) *odd = stamp;
+    }
     if (!out) return;
 #pragma unroll
     for (int e = 0; e < 4; ++e) raw[e] *= f;
@@ -1107,14 +1115,15 @@ hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, con
 }
 
 size_t split_bytes(int L, int w) { return (size_t)L * padded(w) * padded(w) * 6; }
-size_t split_scales(int L, int w) { return (size_t)L * (padded(w) / 32); }
+size_t split_scales(int L, int w) { return (size_t)L * (padded(w) / 32) + 1; }
 
-hipError_t launch_split_weights(bool bwd, const float* W, char* out, float* scale, int L, int w,
-                                hipStream_t st) {
+hipError_t launch_split_weights(bool bwd, const float* W, char* out, float* scale, unsigned stamp,
+                                int L, int w, hipStream_t st) {
+    unsigned* const odd = (unsigned*)(scale + split_scales(L, w) - 1);
     const int WP = padded(w), a_w = w;
     const long long grid = ((long long)L * WP * WP / 16 + kThr - 1) / kThr;
-    if (bwd) DEEPPCR_PANEL(SPLIT_B, grid, W, out, scale, L, w);
-    else DEEPPCR_PANEL(SPLIT_F, grid, W, out, scale, L, w);
+    if (bwd) DEEPPCR_PANEL(SPLIT_B, grid, W, out, scale, odd, stamp, L, w);
+    else DEEPPCR_PANEL(SPLIT_F, grid, W, out, scale, odd, stamp, L, w);
     return hipGetLastError();
 }
 
