@@ -28,7 +28,7 @@ __device__ inline unsigned wave_umax(unsigned v) {
 // ---------------------------------------------------------------- forward
 // Bound by the latency of reading W_0 and by its stores: up to 16 lanes share a
 // row and the rows go out 16 bytes at a time (B 256, L 256, w 32: 15.2 us with
-// a wave per row, single words and a division each, now 7.7; B 16, L 1024,
+// a wave per row, single words and a division each, now 7.6-9; B 16, L 1024,
 // w 128: 35 -> 14.7).
 __global__ __launch_bounds__(kThreads) void initial_guess_kernel(
     const float* __restrict__ W, const float* __restrict__ bias, const float* __restrict__ z0,
