@@ -443,7 +443,7 @@ hipError_t read_measures(const unsigned* red, unsigned* hw, hipStream_t st, unsi
 struct PanelPlan {
     int C = 0, Lc = 0;  // C = 0: not for this shape
     size_t P, q, xe, space, scale;
-    unsigned stamp;  // of this call's factors (launch_split_weights)
+    unsigned stamp;  // of this call's factors (PanelSplit)
     bool split = false;  // the weights are split once, at S
     size_t S;
 };
@@ -467,7 +467,7 @@ PanelPlan panel_plan(int B, int L, int w, bool bwd) {
         pl.q = off; off += nq;
         pl.xe = off; off += nq;
         pl.space = off; off += Ce > 1 ? nP / 2 : 0;
-        pl.scale = off; off += align_up(split_scales(L, w) * sizeof(float));
+        pl.scale = off; off += align_up((split_scales(L, w) + 1) * sizeof(float));
         if (off > lo.r[0]) continue;
         pl.S = off;
         pl.split = off + split_bytes(L, w) <= lo.r[0];
@@ -477,16 +477,19 @@ PanelPlan panel_plan(int B, int L, int w, bool bwd) {
     return pl;
 }
 
-// The weights split if the plan says so, and their factors, once per call.
-hipError_t panel_split(bool bwd, const float* W, int L, int w, const PanelPlan& pl, void* ws_base,
-                       hipStream_t st) {
-    if (pl.C == 0) return hipSuccess;
+// Where the plan has the weights' factors, the word for PanelArgs::odd behind
+// them, and the split weights.
+PanelSplit panel_split(const PanelPlan& pl, void* ws_base, int L, int w) {
     char* base = (char*)ws_base;
-    const double bytes = 4.0 * L * w * w + (pl.split ? (double)split_bytes(L, w) : 0.0);
-    return timed(DEEPPCR_KCLASS_OTHER, bytes, 0.0, st, [&] {
-        return launch_split_weights(bwd, W, pl.split ? base + pl.S : nullptr,
-                                    (float*)(base + pl.scale), pl.stamp, L, w, st);
-    });
+    float* scale = (float*)(base + pl.scale);
+    return {pl.split ? base + pl.S : nullptr, scale, (unsigned*)(scale + split_scales(L, w)),
+            pl.stamp};
+}
+
+// What layer_vectors reads and writes: W, the states, d (and r), and the split.
+double layer_vectors_bytes(double vectors, int L, int w, const PanelPlan& pl, bool first) {
+    return 4.0 * ((double)L * w * w + vectors) +
+           (pl.C > 0 && pl.split && first ? (double)split_bytes(L, w) : 0.0);
 }
 
 // The solve of Eq. 3 (Eq. 12) for the layers described by `a`, whose d and r
@@ -497,10 +500,11 @@ hipError_t panel_solve(bool bwd, PanelArgs a, const PanelPlan& pl, void* ws_base
     a.rows = a.L + (bwd ? 1 : 0);
     a.Lc = pl.Lc;
     a.C = pl.C;
-    if (pl.split) a.S = base + pl.S;
-    a.scale = (const float*)(base + pl.scale);
-    a.odd = (const unsigned*)(a.scale + split_scales(a.L, a.w) - 1);
-    a.stamp = pl.stamp;
+    const PanelSplit split = panel_split(pl, ws_base, a.L, a.w);
+    a.S = split.out;
+    a.scale = split.scale;
+    a.odd = split.odd;
+    a.stamp = split.stamp;
     a.P = (float*)(base + pl.P);
     a.q = (float*)(base + pl.q);
     float* xe = (float*)(base + pl.xe);
@@ -608,7 +612,7 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
     // the buffer that the last PCR level's vectors do not come from
     const VecDst xd{ws.r[(num_levels(L) + 1) & 1], (long long)L * w, (long long)w};
     const PanelPlan pl = panel_plan(B, L, w, false);
-    DEEPPCR_HIP(panel_split(false, W, L, w, pl, workspace, st));
+    const PanelSplit split = panel_split(pl, workspace, L, w);
     const bool layers16 = layer_blocks(w);
     const bool wide_sub = wide_width(w) && wide_substitution(B, L, w);
     unsigned* fslots = ws.red + kRedF;
@@ -625,9 +629,11 @@ int newton_forward(const float* W, const float* bias, const float* z0, float* Z,
         // order) and residuals into ws A[1], r[1].
         hipError_t e;
         if (pl.C > 0 || layers16) {
-            e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 4.0 * n), 2.0 * B * L * w2, st, [&] {
+            e = timed(DEEPPCR_KCLASS_LAYER, layer_vectors_bytes(4.0 * n, L, w, pl, k == 0),
+                      2.0 * B * L * w2, st, [&] {
                 return launch_layer_vectors(false, W, bias, z0, Z, ws.r[1], ws.r[0], ws.red,
-                                            rule.residual, B, L, w, layer, alpha, st);
+                                            rule.residual, B, L, w, layer, alpha,
+                                            pl.C > 0 && k == 0 ? &split : nullptr, st);
             });
         } else if (wide_sub) {
             e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 4.0 * n), 2.0 * B * L * w2, st, [&] {
@@ -1090,13 +1096,14 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
     const double w2 = (double)w * w;
     const PanelPlan pl = panel_plan(B, L, w, true);
     if (pl.C > 0) {
-        hipError_t e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 2.0 * B * L * w),
+        const PanelSplit split = panel_split(pl, workspace, L, w);
+        hipError_t e = timed(DEEPPCR_KCLASS_LAYER,
+                             layer_vectors_bytes(2.0 * B * L * w, L, w, pl, true),
                              2.0 * B * L * w2, st, [&] {
             return launch_layer_vectors(true, W, bias, z0, Z, ws.dscale, nullptr, nullptr, false,
-                                        B, L, w, layer, alpha, st);
+                                        B, L, w, layer, alpha, &split, st);
         });
         if (e != hipSuccess) return hip_fail(e, "layer_vectors");
-        DEEPPCR_HIP(panel_split(true, W, L, w, pl, workspace, st));
         PanelArgs pa{};
         pa.W = W;
         pa.d = ws.dscale;
@@ -1118,7 +1125,7 @@ int deeppcr_mlp_backward(const float* W, const float* bias, const float* z0, con
         hipError_t e = timed(DEEPPCR_KCLASS_LAYER, 4.0 * (L * w2 + 2.0 * B * L * w),
                              2.0 * B * L * w2, st, [&] {
             return launch_layer_vectors(true, W, bias, z0, Z, ws.dscale, nullptr, nullptr, false,
-                                        B, L, w, layer, alpha, st);
+                                        B, L, w, layer, alpha, nullptr, st);
         });
         if (e != hipSuccess) return hip_fail(e, "layer_vectors");
         // row m of the transposed system: W_{L-m}^T, d_{L-m}; G at row 0

@@ -187,9 +187,9 @@ hipError_t launch_block_down(const BlockSrc& A, const LayerScale* y, const VecSr
 // panel_width accepts; WP = panel_pad(w) is the padded width of P, q, xe.
 struct PanelArgs {
     const float* W;   // [L, w, w]
-    const char* S;    // the weights split (launch_split_weights), or null
-    const float* scale;  // their factors (launch_split_weights), and whether
-    const unsigned* odd;  // there may be any but 1: *odd == stamp
+    const char* S;    // the weights split (PanelSplit), or null
+    const float* scale;  // their factors, and whether there may be any
+    const unsigned* odd;  // but 1: *odd == stamp
     unsigned stamp;
     const float* d;   // [B, L, w] c sigma'
     const float* r;   // [B, L, w] residuals; transposed: G [B, w]
@@ -205,21 +205,25 @@ struct PanelArgs {
     int Lc, C;        // rows per chunk, ceil(rows / Lc)
     int residual;
 };
+// The weights (bwd: transposed) as bf16 parts in operand order, split_bytes
+// (out null: not), and the factors of their results, split_scales of them.
+struct PanelSplit {
+    char* out;
+    float* scale;
+    unsigned* odd;
+    unsigned stamp;
+};
+size_t split_bytes(int L, int w);
+size_t split_scales(int L, int w);
 bool panel_width(int w);
 int panel_pad(int w);
 int panel_chunks(int B, int rows, int w);
 // d (and, forward, r and, if want_max, its maximum; clears the max|dZ|, max|Z|
-// slots of red).
+// slots of red); with split the weights as well, once per call.
 hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, const float* z0,
                                 const float* Z, float* d, float* r, unsigned* red, bool want_max,
-                                int B, int L, int w, int layer, float alpha, hipStream_t st);
-// The weights (bwd: transposed) as bf16 parts in operand order, split_bytes,
-// and the factors of their results with the word for PanelArgs::odd behind them,
-// split_scales words in all; out null: these alone.
-size_t split_bytes(int L, int w);
-size_t split_scales(int L, int w);
-hipError_t launch_split_weights(bool bwd, const float* W, char* out, float* scale, unsigned stamp,
-                                int L, int w, hipStream_t st);
+                                int B, int L, int w, int layer, float alpha,
+                                const PanelSplit* split, hipStream_t st);
 // P of chunks 1 .. C-2 and q of chunks 0 .. C-2 (C >= 2).
 hipError_t launch_chunk_pass(bool bwd, const PanelArgs& a, hipStream_t st);
 // Every row from its chunk's x_in (xe of the chunk before; 0 in the first).

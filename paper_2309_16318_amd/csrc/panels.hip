@@ -607,11 +607,13 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
     // A column of P, which a wave holds whole (lanes n and n + 32), stays above
     // 2^-60 in its largest element, so that its elements have parts, and P stands
     // for P 2^ex (large columns are scaled down as well, where float32 would
-    // overflow).  A few elements of each half show that as a rule, and only
-    // where they do not all are looked at.  The pass without any of the range's
-    // checks, with all maxima at every row, and with these, us: 33.4, 35.1, 34.3
-    // at B 256, L 256, w 32; 184, 191, 188 at B 64, L 1024, w 64 (transposed);
-    // 330, 341, 329 at B 16, L 1024, w 128.
+    // overflow).  Six elements of each half show that as a rule (of ReLU units
+    // all six are idle once in 64), and only where they do not all are looked at.
+    // A forward call without any of the range's checks, with all maxima at every
+    // row, and with these, us: 357, 370, 363 at B 256, L 256, w 32; 1279, 1342,
+    // 1254 at B 64, L 1024, w 64; 2322, 2350, 2305 at B 16, L 1024, w 128 (an odd
+    // number of elements costs 5% at w = 64, in every other respect the same
+    // code: where its loop falls).
     int ex = 0;
     auto largest = [&](int tiles, int count) {
         float m = 0.f;
@@ -623,7 +625,7 @@ __device__ __forceinline__ void product_panel(const PanelArgs& a, char* lds, int
     };
     auto settle = [&] {
         // (the columns beyond w are zeros)
-        const float some = EXACT || col < w ? largest(1, 5) : 1.f;
+        const float some = EXACT || col < w ? largest(1, 6) : 1.f;
         const unsigned low = __float_as_uint(0x1p-60f), high = __float_as_uint(0x1p40f);
         if (__builtin_expect(
                 __builtin_amdgcn_ballot_w64(__float_as_uint(some) - low > high - low) != 0, 0)) {
@@ -809,15 +811,13 @@ __global__ __launch_bounds__(kThr) void apply_pass(PanelArgs a) {
 // 1, unless the largest weight of these rows is below 2^-60 or from 2^60 on;
 // then *odd becomes the call's stamp.  (What is in *odd before needs no
 // clearing: a stamp left there only makes a call read its factors.)  Without
-// `out`, the factors alone.
+// `out`, the factors alone.  The work of one workgroup, of those that
+// layer_vectors' first launch of a call has beyond its own.
 template <int WP, bool BWD, bool EXACT>
-__global__ __launch_bounds__(kThr) void split_weights(const float* __restrict__ W,
-                                                      char* __restrict__ out, float* __restrict__ scale,
-                                                      unsigned* __restrict__ odd, unsigned stamp,
-                                                      int L, int w_) {
+__device__ __forceinline__ void split_weights(const float* __restrict__ W, const PanelSplit& job,
+                                              int block, int L, int w) {
     constexpr int UNITS = WP * WP / 16, WAVES = WP / 32;  // threads per layer, waves per 32 rows
-    const int w = EXACT ? WP : w_;
-    const int id = blockIdx.x * kThr + threadIdx.x;
+    const int id = block * kThr + threadIdx.x;
     const int l = __builtin_amdgcn_readfirstlane(id / UNITS), u = id % UNITS;
     if (l >= L) return;
     const int rg = u & 7, cg = (u >> 3) % (WP / 4), mt = u / (2 * WP);
@@ -847,13 +847,13 @@ __global__ __launch_bounds__(kThr) void split_weights(const float* __restrict__ 
                     : m > 0.f && m < 0x1p-60f            ? 0x1p64f
                                                          : 1.f;
     if (u % (2 * WP) == 0) {
-        scale[(long long)l * (WP / 32) + mt] = 1.f / f;
-        if (f != 1.f) *odd = stamp;
+        job.scale[(long long)l * (WP / 32) + mt] = 1.f / f;
+        if (f != 1.f) *job.odd = job.stamp;
     }
-    if (!out) return;
+    if (!job.out) return;
 #pragma unroll
     for (int e = 0; e < 4; ++e) raw[e] *= f;
-    char* dst = out + (long long)l * SplitShape<WP>::LAYER +
+    char* dst = job.out + (long long)l * SplitShape<WP>::LAYER +
                 (WP == 128 ? mt * SplitShape<WP>::SLICE : mt * (WP / 16) * 1024) + cg / 4 * 1024 +
                 (4 * rg + 32 * (cg & 1)) * 16 + 8 * ((cg >> 1) & 1);
 #pragma unroll
@@ -873,13 +873,14 @@ __global__ __launch_bounds__(kThr) void split_weights(const float* __restrict__ 
 // weights in registers for all its systems.  Bound by one read of W and of the
 // states and the write of d and r.  One atomic per workgroup, at most 2048 of
 // them (L = 8192, w = 32, B = 1: 42 us with one per wave and a workgroup per
-// layer).
+// layer).  Workgroups from `own` on split the weights, which shares the read of W
+// and saves a launch per call (2-3 us where B and L are small).
 template <int WP, bool BWD, bool EXACT>
 __global__ __launch_bounds__(kThr) void layer_vectors(
     const float* __restrict__ W, const float* __restrict__ bias, const float* __restrict__ z0,
     const float* __restrict__ Z, float* __restrict__ d_out, float* __restrict__ r_out,
     unsigned* __restrict__ clear, unsigned* __restrict__ red, int B, int L, int w_, int layer,
-    float alpha, int per) {
+    float alpha, int per, int own, PanelSplit job) {
     using S = VecShape<WP>;
     constexpr int NR = S::NR;
     const int t = threadIdx.x, v = t >> 6, lane = t & 63;
@@ -887,6 +888,10 @@ __global__ __launch_bounds__(kThr) void layer_vectors(
     const int n = lane & 15, g = lane >> 4;
     const int w = EXACT ? WP : w_;
     const int base = wv * 16 * S::MTW, r0 = base + NR * g;
+    if ((int)blockIdx.x >= own) {
+        split_weights<WP, BWD, EXACT>(W, job, blockIdx.x - own, L, w);
+        return;
+    }
     if constexpr (!BWD)
         if (blockIdx.x == 0)
             for (int k = t; k < 2 * kRedShards; k += kThr) clear[k] = 0u;
@@ -998,8 +1003,6 @@ int padded(int w) { return w <= 32 ? 32 : w <= 64 ? 64 : 128; }
     } while (0)
 #define LAYER_VECTORS_F(WP, EX) (layer_vectors<WP, false, EX>)
 #define LAYER_VECTORS_B(WP, EX) (layer_vectors<WP, true, EX>)
-#define SPLIT_F(WP, EX) (split_weights<WP, false, EX>)
-#define SPLIT_B(WP, EX) (split_weights<WP, true, EX>)
 #define CHUNK_F(WP, EX) (chunk_pass<WP, false, EX, false>)
 #define CHUNK_B(WP, EX) (chunk_pass<WP, true, EX, false>)
 #define CHUNK_FP(WP, EX) (chunk_pass<WP, false, EX, true>)
@@ -1087,45 +1090,39 @@ static PanelArgs systems(PanelArgs a, bool bwd, long long b, int n) {
 static hipError_t layer_vectors_some(bool bwd, const float* W, const float* bias, const float* z0,
                                      const float* Z, float* d, float* r, unsigned* red,
                                      bool want_max, int B, int L, int w, int layer, float alpha,
-                                     hipStream_t st) {
+                                     const PanelSplit* split, hipStream_t st) {
     // one item per group of waves, or up to 2048 workgroups
     const int WP = padded(w), groups = WP == 32 ? 2 : 1;
     const int items = L * ((B + 15) / 16);
     const int per = (items + 2048 * groups - 1) / (2048 * groups);
-    const int grid = (items + per * groups - 1) / (per * groups);
+    const int own = (items + per * groups - 1) / (per * groups);
+    const long long grid =
+        own + (split ? ((long long)L * WP * WP / 16 + kThr - 1) / kThr : 0);
+    const PanelSplit job = split ? *split : PanelSplit{};
     unsigned* const mx = want_max ? red : nullptr;
     const int a_w = w;
     if (bwd)
         DEEPPCR_PANEL(LAYER_VECTORS_B, grid, W, bias, z0, Z, d, r, red, mx, B, L, w, layer,
-                      alpha, per);
+                      alpha, per, own, job);
     else
         DEEPPCR_PANEL(LAYER_VECTORS_F, grid, W, bias, z0, Z, d, r, red, mx, B, L, w, layer,
-                      alpha, per);
+                      alpha, per, own, job);
     return hipGetLastError();
 }
 
 hipError_t launch_layer_vectors(bool bwd, const float* W, const float* bias, const float* z0,
                                 const float* Z, float* d, float* r, unsigned* red, bool want_max,
-                                int B, int L, int w, int layer, float alpha, hipStream_t st) {
+                                int B, int L, int w, int layer, float alpha,
+                                const PanelSplit* split, hipStream_t st) {
     return by_systems(B, L, w, [&](long long b, int n) {
         const long long v = b * L * w;
         return layer_vectors_some(bwd, W, bias, z0 + b * w, Z + v, d + v, bwd ? r : r + v, red,
-                                  want_max, n, L, w, layer, alpha, st);
+                                  want_max, n, L, w, layer, alpha, b == 0 ? split : nullptr, st);
     });
 }
 
 size_t split_bytes(int L, int w) { return (size_t)L * padded(w) * padded(w) * 6; }
-size_t split_scales(int L, int w) { return (size_t)L * (padded(w) / 32) + 1; }
-
-hipError_t launch_split_weights(bool bwd, const float* W, char* out, float* scale, unsigned stamp,
-                                int L, int w, hipStream_t st) {
-    unsigned* const odd = (unsigned*)(scale + split_scales(L, w) - 1);
-    const int WP = padded(w), a_w = w;
-    const long long grid = ((long long)L * WP * WP / 16 + kThr - 1) / kThr;
-    if (bwd) DEEPPCR_PANEL(SPLIT_B, grid, W, out, scale, odd, stamp, L, w);
-    else DEEPPCR_PANEL(SPLIT_F, grid, W, out, scale, odd, stamp, L, w);
-    return hipGetLastError();
-}
+size_t split_scales(int L, int w) { return (size_t)L * (padded(w) / 32); }
 
 static hipError_t chunk_pass_some(bool bwd, const PanelArgs& a, hipStream_t st) {
     const int WP = padded(a.w), a_w = a.w;

@@ -47,7 +47,7 @@ def test_every_solve_kernel_of_the_sources_is_matched():
     of the two classes, or are named here; every prefix names a kernel."""
     import re
 
-    others = {"layer_vectors", "split_weights", "wide_vectors", "eval_small", "forward_eval_wide",
+    others = {"layer_vectors", "wide_vectors", "eval_small", "forward_eval_wide",
               "backward_assemble_wide", "broadcast_row0", "matvec_t_wide", "wgrad_wide",
               "seq_layer_wide", "chunk_carry_kernel", "chunk_carry_rows",
               "chunk_apply_rows", "chunk_apply_kernel", "chunk_apply_small"}
