@@ -447,8 +447,10 @@ __global__ __launch_bounds__(256) void resnet_block_wave16(
     const v4f xin = vec(BWD ? Zb + ((long long)g * skip - 1) * 16
                             : g == 0 ? z0 + (long long)b * 16 : S + (item - 1) * 16);
     v4f z = xin, P;
+    // W_0 as it stands, not its product with I, in which an infinite or NaN
+    // weight would meet zeros and spread over its row
 #pragma unroll
-    for (int e = 0; e < 4; ++e) P[e] = 4 * q + e == i ? 1.f : 0.f;
+    for (int e = 0; e < 4; ++e) P[e] = Wj[64 * q + 16 * e + i];
     const int own = lane & 3;
     for (int tt = 0; tt < skip; ++tt) {
         const v4f w = a, bt = bi;
@@ -462,7 +464,12 @@ __global__ __launch_bounds__(256) void resnet_block_wave16(
         const float x = own == 0 ? z[0] : own == 1 ? z[1] : own == 2 ? z[2] : z[3];
         float d;
         const float s = act_fn(act, x, &d);
-        if (g > 0) {
+        if (g > 0 && tt == 0) {
+            // sigma' of element i, the column of this lane's elements
+            const float di = __shfl(d, 16 * (i >> 2) + (i & 3), 64);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) P[e] *= di;
+        } else if (g > 0) {
             const v4f f = {w[0] * quad_lane<0>(d), w[1] * quad_lane<1>(d), w[2] * quad_lane<2>(d),
                            w[3] * quad_lane<3>(d)};
             v4f pn = {0.f, 0.f, 0.f, 0.f};

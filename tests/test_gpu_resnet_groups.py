@@ -49,3 +49,28 @@ def test_groups(B, G, skip, act):
             normwise_rel_err(db.cpu().numpy(), rb, axes="all")]
     print("  errors", " ".join(f"{e:.1e}" for e in errs), flush=True)
     assert max(errs) <= TOL
+
+
+@pytest.mark.parametrize("B,G", [(3, 12), (1, 40), (256, 64)])
+@pytest.mark.parametrize("skip", [1, 2, 4])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_weight_that_is_no_number(B, G, skip, bad):
+    """The adjoints are finite exactly where the plain backward pass has them
+    finite: a NaN or infinite weight reaches the one element of its column in
+    its own layer, and all of the layers before."""
+    print(f"resnet {bad} weight B={B} blocks={G} skip={skip}", flush=True)
+    dev = torch.device("cuda:0")
+    L = G * skip
+    d = synth.resnet_inputs(B, L, 16, seed=5300 + B + G)
+    Z32 = R.resnet_seq_forward(R.ACT_TANH, skip, d["W"], d["bias"], d["z0"]).astype(np.float32)
+    for layer in range((G // 2) * skip, (G // 2 + 1) * skip):  # every place of a block
+        W = d["W"].copy()
+        W[layer, 13, 2] = bad
+        t = [torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(dev)
+             for a in (W, d["z0"], Z32, d["G"])]
+        lam, dz0, _, _ = deeppcr.deeppcr_resnet_backward(*t, skip=skip, act=R.ACT_TANH)
+        with np.errstate(invalid="ignore"):
+            rl, rz, _, _ = R.resnet_seq_backward(R.ACT_TANH, skip, W, d["bias"], d["z0"], Z32,
+                                                 d["G"])
+        assert np.array_equal(np.isfinite(lam.cpu().numpy()), np.isfinite(rl)), layer
+        assert np.array_equal(np.isfinite(dz0.cpu().numpy()), np.isfinite(rz)), layer
